@@ -158,7 +158,7 @@ GAPA_API int gapa_eval_population_noalloc(gapa_graph *g, const int32_t *genes, i
 
 /* ---------------------------------------------------------------------------
  * The paper's dense reachability fitness (Section III-D, eq. 13-17, the
- * "SixDST" function), on the matrix cores.
+ * "SixDST" function).
  *
  * For each row S of genes: M = Normalizer((A_S + I)^hops), A_S the
  * adjacency matrix with every edge of a removed node deleted (eq. 13), the
@@ -169,8 +169,10 @@ GAPA_API int gapa_eval_population_noalloc(gapa_graph *g, const int32_t *genes, i
  * mcn: int32 [P] out, the largest row sum over surviving nodes (0 if none).
  * With hops >= the diameter of every component these are PC and MCN of
  * gapa_eval_population exactly; the paper uses hops = 6 (eq. 15).
- * Dense n x n int8 matrices (three per individual in flight, within a 2 GiB
- * workspace): n <= GAPA_SIXDST_MAX_N, hops >= 1, else GAPA_E_INVALID_ARG.
+ * Computed from the nodes' reachable sets, hop by hop, or for many hops on
+ * dense graphs as products of n x n int8 matrices on the matrix cores (three
+ * per individual in flight, within a 2 GiB workspace).
+ * n <= GAPA_SIXDST_MAX_N, hops >= 1, else GAPA_E_INVALID_ARG.
  * Genes, flags (GAPA_DEVICE_PTRS, GAPA_TRUST_INPUT), stream and errors as for
  * gapa_eval_population; results are exact integers.
  * ------------------------------------------------------------------------- */

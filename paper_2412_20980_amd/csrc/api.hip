@@ -240,10 +240,10 @@ constexpr int kMinBand = 16384;  // at n = 200k the 8.9k nodes of BFS levels 3+ 
 // Also returns each source's index among its instance's sources (the t-th
 // source is order[voff[b] + t]; -1 for every other node) and, when band 0
 // holds exactly the sources (no merge took them into band 1), its size in
-// src_band (else 0).
+// src_band (else 0), and the number of breadth-first levels.
 void graph_orderings(int32_t n, const int32_t *rp, const int32_t *ci, const std::vector<int32_t> &voff,
                      std::vector<int32_t> &order, std::vector<int32_t> &colD, std::vector<int32_t> &band_v,
-                     std::vector<int32_t> &band_off, std::vector<int8_t> &src_idx, int32_t &src_band)
+                     std::vector<int32_t> &band_off, std::vector<int8_t> &src_idx, int32_t &src_band, int32_t &levels)
 {
     std::vector<int32_t> deg(n);
     for (int32_t v = 0; v < n; ++v) deg[v] = rp[v + 1] - rp[v];
@@ -284,6 +284,7 @@ void graph_orderings(int32_t n, const int32_t *rp, const int32_t *ci, const std:
             if (deg[v] > 0 && level[v] < 0) level[v] = lv;
         nlev = std::max(nlev, lv + 1);
     }
+    levels = nlev;
     band_v.clear();
     for (int32_t v = 0; v < n; ++v)
         if (deg[v] > 0) band_v.push_back(v);
@@ -415,7 +416,8 @@ int graph_build(int dev, int32_t n, int64_t nnz, const int32_t *row_ptr, const i
         for (int32_t e = row_ptr[v]; e < row_ptr[v + 1]; ++e) src[e] = v;
     std::vector<int32_t> order, colD, band_v;
     std::vector<int8_t> src_idx;
-    graph_orderings(n, row_ptr, col_idx, voff, order, colD, band_v, g->band_off, src_idx, g->src_band);
+    graph_orderings(n, row_ptr, col_idx, voff, order, colD, band_v, g->band_off, src_idx, g->src_band,
+                    g->levels);
     g->n_noniso = (int32_t)band_v.size();
     std::vector<uint32_t> noniso_bits((size_t)g->words, 0u);
     for (int32_t v = 0; v < n; ++v)
@@ -462,6 +464,30 @@ int graph_build(int dev, int32_t n, int64_t nnz, const int32_t *row_ptr, const i
         if ((e = hipMemcpy(g->d_band_rec, rec.data(), rec.size() * sizeof(int4), hipMemcpyHostToDevice)) != hipSuccess)
             return fail(hip_fail(e, "hipMemcpy"));
     }
+    if (n <= GAPA_SIXDST_MAX_N && voff.size() == 2) {
+        // neighbour lists of the dense reachability fitness
+        std::vector<uint16_t> rank((size_t)n), ids;
+        std::vector<int32_t> off((size_t)n + 1, 0);
+        for (int32_t r = 0; r < n; ++r) rank[order[r]] = (uint16_t)r;
+        ids.reserve((size_t)nnz + 3 * (size_t)n);
+        for (int32_t r = 0; r < n; ++r) {
+            const int32_t v = order[r];
+            g->n_hub += row_ptr[v + 1] - row_ptr[v] > kHubDegree;
+            for (int32_t e = row_ptr[v]; e < row_ptr[v + 1]; ++e) ids.push_back(rank[col_idx[e]]);
+            while (ids.size() % 4 != 0) ids.push_back((uint16_t)r);
+            off[r + 1] = (int32_t)(ids.size() / 4);
+        }
+        g->reach_chunks = off[n];
+        // one allocation: ids (8-byte chunks), offsets, ranks
+        const size_t b_ids = ids.size() * 2, b_off = off.size() * 4, b_rank = rank.size() * 2;
+        std::vector<unsigned char> host(b_ids + b_off + b_rank);
+        if (b_ids) std::memcpy(host.data(), ids.data(), b_ids);
+        std::memcpy(host.data() + b_ids, off.data(), b_off);
+        std::memcpy(host.data() + b_ids + b_off, rank.data(), b_rank);
+        if ((e = hipMalloc(&g->d_reach, host.size())) != hipSuccess) return fail(hip_fail(e, "hipMalloc"));
+        if ((e = hipMemcpy(g->d_reach, host.data(), host.size(), hipMemcpyHostToDevice)) != hipSuccess)
+            return fail(hip_fail(e, "hipMemcpy"));
+    }
     *out = g;
     return GAPA_OK;
 }
@@ -485,6 +511,7 @@ void graph_release(gapa_graph *g)
         if (g->d_noniso) (void)hipFree(g->d_noniso);
         if (g->d_src_idx) (void)hipFree(g->d_src_idx);
         if (g->d_band_rec) (void)hipFree(g->d_band_rec);
+        if (g->d_reach) (void)hipFree(g->d_reach);
         release_workspace(g->ws);
     }
     delete g;
@@ -737,14 +764,9 @@ int gapa_sixdst_eval(gapa_graph *g, const int32_t *genes, int32_t P, int32_t k, 
     }
     hipStream_t s = static_cast<hipStream_t>(stream);
     FitnessWorkspace &w = g->ws;
-    // individuals in flight: three dense matrices each, within a 2 GiB workspace
-    const size_t per = sixdst_bytes_per_individual(g->n);
-    const int32_t chunk = (int32_t)std::max<size_t>(1, std::min<size_t>((size_t)P, ((size_t)2 << 30) / per));
+    const bool sparse = sixdst_sparse(g, hops);
     int rc;
-    if ((rc = w.flag.reserve(16)) != GAPA_OK || (rc = w.masks.reserve((size_t)P * g->words * 4)) != GAPA_OK ||
-        (rc = w.alive.reserve((size_t)P * 4)) != GAPA_OK || (rc = w.six_mats.reserve((size_t)chunk * per)) != GAPA_OK ||
-        (rc = w.six_tot.reserve((size_t)chunk * 8)) != GAPA_OK)
-        return rc;
+    if ((rc = w.flag.reserve(16)) != GAPA_OK) return rc;
     const int32_t *d_genes = genes;
     int64_t *d_pc = pc;
     int32_t *d_mcn = mcn;
@@ -758,13 +780,26 @@ int gapa_sixdst_eval(gapa_graph *g, const int32_t *genes, int32_t P, int32_t k, 
         d_pc = w.fitness.as<int64_t>();
         d_mcn = w.mcn.as<int32_t>();
     }
-    if ((rc = launch_fill_u32(w.flag.ptr, 0u, 4, s)) != GAPA_OK) return fail_handle(&g->failed, rc);
-    if ((rc = launch_mask_build(d_genes, P, k, g->n, g->words, g->d_noniso, g->n_noniso, w.masks.as<uint32_t>(),
-                                w.alive.as<int32_t>(), w.flag.as<int32_t>(), s)) != GAPA_OK)
-        return fail_handle(&g->failed, rc);
-    if ((rc = sixdst_eval_masks(g, w.masks.as<uint32_t>(), P, hops, chunk, w.six_mats.as<uint8_t>(),
-                                w.six_tot.as<unsigned long long>(), d_pc, d_mcn, s)) != GAPA_OK)
-        return fail_handle(&g->failed, rc);
+    if (sparse) {
+        if ((rc = sixdst_eval_genes(g, d_genes, P, k, hops, d_pc, d_mcn, w.flag.as<int32_t>(), s)) != GAPA_OK)
+            return fail_handle(&g->failed, rc);
+    } else {
+        // individuals in flight: three dense matrices each, within a 2 GiB workspace
+        const size_t per = sixdst_bytes_per_individual(g->n);
+        const int32_t chunk = (int32_t)std::max<size_t>(1, std::min<size_t>((size_t)P, ((size_t)2 << 30) / per));
+        if ((rc = w.masks.reserve((size_t)P * g->words * 4)) != GAPA_OK ||
+            (rc = w.alive.reserve((size_t)P * 4)) != GAPA_OK ||
+            (rc = w.six_mats.reserve((size_t)chunk * per)) != GAPA_OK ||
+            (rc = w.six_tot.reserve((size_t)chunk * 8)) != GAPA_OK)
+            return rc;
+        if ((rc = launch_fill_u32(w.flag.ptr, 0u, 4, s)) != GAPA_OK) return fail_handle(&g->failed, rc);
+        if ((rc = launch_mask_build(d_genes, P, k, g->n, g->words, g->d_noniso, g->n_noniso, w.masks.as<uint32_t>(),
+                                    w.alive.as<int32_t>(), w.flag.as<int32_t>(), s)) != GAPA_OK)
+            return fail_handle(&g->failed, rc);
+        if ((rc = sixdst_eval_masks(g, w.masks.as<uint32_t>(), P, hops, chunk, w.six_mats.as<uint8_t>(),
+                                    w.six_tot.as<unsigned long long>(), d_pc, d_mcn, s)) != GAPA_OK)
+            return fail_handle(&g->failed, rc);
+    }
     if (dev_ptrs && trust) return GAPA_OK;
     int32_t hflag[4] = {0, 0, 0, 0};
     hipError_t e = hipMemcpyAsync(hflag, w.flag.ptr, 16, hipMemcpyDeviceToHost, s);

@@ -78,4 +78,45 @@ __device__ __forceinline__ int32_t xcd_tile(int32_t b, int32_t nblk)
     return x * q + min(x, r) + (b >> 3);
 }
 
+// The value of lane l ^ kXor of the calling lane's row of 16 (kXor 1, 2, 4, 8)
+// or half-wave (16), without a trip through the LDS permute unit but for 16:
+// quad permutes, and the row mirrors (l ^ 7, l ^ 15) composed with them.
+template <int kCtrl>
+__device__ __forceinline__ uint32_t dpp_mov(uint32_t x)
+{
+    return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, kCtrl, 0xF, 0xF, true);
+}
+
+template <int kXor>
+__device__ __forceinline__ uint32_t lane_xor(uint32_t x)
+{
+    constexpr int kXor1 = 0xB1, kXor2 = 0x4E, kXor3 = 0x1B, kXor7 = 0x141, kXor15 = 0x140;
+    if constexpr (kXor == 1) return dpp_mov<kXor1>(x);
+    else if constexpr (kXor == 2) return dpp_mov<kXor2>(x);
+    else if constexpr (kXor == 4) return dpp_mov<kXor3>(dpp_mov<kXor7>(x));
+    else if constexpr (kXor == 8) return dpp_mov<kXor7>(dpp_mov<kXor15>(x));
+    else return (uint32_t)__builtin_amdgcn_ds_swizzle((int)x, 0x401F);
+}
+
+// One round of transpose32: swaps the off-diagonal blocks of kXor bits
+// between lanes r and r ^ kXor (m: the bits of the low blocks).
+template <int kXor>
+__device__ __forceinline__ uint32_t transpose_round(uint32_t x, int l32, uint32_t m)
+{
+    const uint32_t y = lane_xor<kXor>(x);
+    return (l32 & kXor) ? (((y >> kXor) & m) | (x & ~m)) : ((x & m) | ((y & m) << kXor));
+}
+
+// 32 x 32 bit-matrix transpose across the 32 lanes of a half-wave: lane r
+// holds row r (bit c = entry (r, c)); afterwards lane c holds column c (bit r =
+// entry (r, c)).
+__device__ __forceinline__ uint32_t transpose32(uint32_t x, int l32)
+{
+    x = transpose_round<16>(x, l32, 0x0000FFFFu);
+    x = transpose_round<8>(x, l32, 0x00FF00FFu);
+    x = transpose_round<4>(x, l32, 0x0F0F0F0Fu);
+    x = transpose_round<2>(x, l32, 0x33333333u);
+    return transpose_round<1>(x, l32, 0x55555555u);
+}
+
 }  // namespace gapa

@@ -123,23 +123,6 @@ __host__ __device__ constexpr int32_t transpose_lds_words(int32_t log_wd)
                                                                                      : 32 * ((kTileWords * 32) >> log_wd));
 }
 
-// 32 x 32 bit-matrix transpose across the 32 lanes of a half-wave: lane r
-// holds row r (bit c = entry (r, c)); afterwards lane c holds column c (bit r =
-// entry (r, c)).  Five rounds swap the off-diagonal blocks of 16, 8, 4, 2 and 1
-// bits between lanes r and r ^ j.
-__device__ __forceinline__ uint32_t transpose32(uint32_t x, int l32)
-{
-    const uint32_t masks[5] = {0x0000FFFFu, 0x00FF00FFu, 0x0F0F0F0Fu, 0x33333333u, 0x55555555u};
-#pragma unroll
-    for (int s = 0; s < 5; ++s) {
-        const int j = 16 >> s;
-        const uint32_t m = masks[s];
-        const uint32_t y = __shfl_xor(x, j, 64);
-        x = (l32 & j) ? (((y >> j) & m) | (x & ~m)) : ((x & m) | ((y & m) << j));
-    }
-    return x;
-}
-
 __global__ __launch_bounds__(kBlk) void k_dead_transpose(const uint32_t *__restrict__ masks, const Insts I,
                                                          int32_t log_wd, uint32_t *__restrict__ dead,
                                                          uint32_t *__restrict__ reach)

@@ -147,8 +147,16 @@ struct gapa_graph {
     uint32_t *d_noniso = nullptr; // [words] bit v set: v has at least one edge
     int8_t *d_src_idx = nullptr;  // [n] index of a band source among its instance's (order[voff + t]), else -1
     std::vector<int32_t> band_off;  // host: band b is d_band_rec[band_off[b], band_off[b+1])
+    int32_t levels = 0;         // breadth-first levels from the highest-degree nodes
     int32_t src_band = 0;       // size of band 0 when it holds exactly the sources, else 0
     int32_t n_noniso = 0;       // nodes with at least one edge
+    // neighbour lists of the dense reachability fitness (n <= GAPA_SIXDST_MAX_N, one
+    // instance), nodes renumbered by descending degree: reach_chunks chunks of
+    // four 16-bit ids, then the int32 [n + 1] first chunk of each node, then the
+    // uint16 [n] new number of each node
+    unsigned char *d_reach = nullptr;
+    int32_t reach_chunks = 0;
+    int32_t n_hub = 0;          // nodes of more than kHubDegree neighbours
     int32_t algorithm = 0;      // 0: bit-parallel sweeps, 1: edge-parallel union-find
     gapa::Tuning tune;
     int32_t tune_version = 0;   // bumped by every tuning change (recorded graphs are re-recorded)
@@ -229,6 +237,12 @@ int launch_bits_transpose(const uint32_t *masks, int32_t P, int32_t W, int32_t n
 
 // Fills count 32-bit words at p with value (a kernel, not a memset node).
 int launch_fill_u32(void *p, uint32_t value, int64_t count, hipStream_t s);
+// Dense reachability fitness (sixdst.hip).  kHubDegree: nodes above it are
+// pulled by several lanes each.
+constexpr int32_t kHubDegree = 24;
+bool sixdst_sparse(const gapa_graph *g, int32_t hops);
+int sixdst_eval_genes(gapa_graph *g, const int32_t *genes, int32_t P, int32_t k, int32_t hops, int64_t *pc,
+                      int32_t *mcn, int32_t *flag, hipStream_t s);
 size_t sixdst_bytes_per_individual(int32_t n);
 int sixdst_eval_masks(gapa_graph *g, const uint32_t *masks, int32_t P, int32_t hops, int32_t chunk, uint8_t *mats,
                       unsigned long long *tot, int64_t *pc, int32_t *mcn, hipStream_t s);

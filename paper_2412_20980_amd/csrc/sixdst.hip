@@ -1,21 +1,28 @@
-// The paper's dense reachability fitness (Sec. III-D, eq. 13-17) on the
-// matrix cores.  For each removal set S:
+// The paper's dense reachability fitness (Sec. III-D, eq. 13-17).  For each
+// removal set S:
 //
 //   M1 = A_S + I     A_S: the adjacency with every edge of a removed node
-//                    deleted (eq. 13), an n_pad x n_pad 0/1 int8 matrix
-//                    (n_pad = n rounded up to 128; padding rows and columns
-//                    are zero)
-//   M  = Normalizer(M1^hops)   by binary exponentiation, the products
-//                    (A+I)(A+I)^2(A+I)^4... of the paper, each normalised
-//                    (entries > 0 become 1)
+//                    deleted (eq. 13)
+//   M  = Normalizer(M1^hops)   (entries > 0 become 1)
 //   pc = (sum M - n) / 2,  mcn = the largest row sum over surviving nodes
 //
 // With hops at least the diameter of every component this is (PC, MCN)
-// exactly; the paper's hops = 6 (eq. 15) truncates.  Every matrix is a
-// power of one symmetric matrix, so every product is symmetric and column j
-// of the right operand is its row j: both operands of the int8 products
-// (v_mfma_i32_16x16x64_i8) are read as rows.  Integer arithmetic throughout:
-// the result is exact.
+// exactly; the paper's hops = 6 (eq. 15) truncates.  Exact integers.  Two
+// ways to the same numbers, chosen by what each would cost (sixdst_sparse):
+//
+//   - k_six_reach: row v of M is the set of nodes within `hops` hops of v, so
+//     the product with the sparse M1 is an OR over v's neighbours.  A block
+//     keeps the sets of every node, restricted to 32 NW sources, as bits in
+//     LDS and advances them hop by hop.
+//   - k_six_gemm: M1 as an n_pad x n_pad 0/1 int8 matrix (n_pad = n rounded
+//     up to 128; padding rows and columns are zero) raised to the power by
+//     binary exponentiation on the matrix cores, the products
+//     (A+I)(A+I)^2(A+I)^4... of the paper, each normalised.  Its cost grows
+//     with log(hops) and not with the edges: for many hops on dense graphs.
+//     Every matrix is a power of one symmetric matrix, so every product is
+//     symmetric and column j of the right operand is its row j: both
+//     operands of the int8 products (v_mfma_i32_16x16x64_i8) are read as
+//     rows.
 #include <algorithm>
 
 #include "device_common.h"
@@ -197,7 +204,385 @@ __global__ void k_six_final(const unsigned long long *__restrict__ total, int32_
     if (z < count) pc[z] = ((int64_t)total[z] - n) / 2;
 }
 
+// Clears the outputs of P individuals and the gene flag.
+__global__ void k_six_clear(int64_t *__restrict__ pc, int32_t *__restrict__ mcn, int32_t P, int32_t *__restrict__ flag)
+{
+    const int32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < P) {
+        pc[i] = 0;
+        mcn[i] = 0;
+    }
+    if (i < 4) flag[i] = 0;
+}
+
+// NW words of one node's reached sources.
+template <int NW>
+struct Bits {
+    uint32_t w[NW];
+};
+
+template <int NW>
+__device__ __forceinline__ Bits<NW> ld_bits(const uint32_t *p)
+{
+    Bits<NW> b;
+    if constexpr (NW == 4) {
+        const uint4 q = *reinterpret_cast<const uint4 *>(p);
+        b.w[0] = q.x, b.w[1] = q.y, b.w[2] = q.z, b.w[3] = q.w;
+    } else {
+        const uint2 q = *reinterpret_cast<const uint2 *>(p);
+        b.w[0] = q.x, b.w[1] = q.y;
+    }
+    return b;
+}
+
+template <int NW>
+__device__ __forceinline__ void st_bits(uint32_t *p, const Bits<NW> &b)
+{
+    if constexpr (NW == 4) *reinterpret_cast<uint4 *>(p) = uint4{b.w[0], b.w[1], b.w[2], b.w[3]};
+    else *reinterpret_cast<uint2 *>(p) = uint2{b.w[0], b.w[1]};
+}
+
+// OR over the 16 lanes of a row, in every lane.
+__device__ __forceinline__ uint32_t row_or(uint32_t x)
+{
+    x |= lane_xor<1>(x);
+    x |= lane_xor<2>(x);
+    x |= lane_xor<4>(x);
+    return x | lane_xor<8>(x);
+}
+
+// Full adder on 32 bit columns: a becomes the sum, the carry is returned.
+__device__ __forceinline__ uint32_t add_bits(uint32_t &a, uint32_t b, uint32_t c)
+{
+    const uint32_t carry = (a & b) | (c & (a | b));
+    a ^= b ^ c;
+    return carry;
+}
+
+// Bit counts of the 32 columns of 15 words: plane p holds bit p of each count.
+struct Planes {
+    uint32_t p0, p1, p2, p3;
+};
+
+__device__ __forceinline__ Planes count_bits15(const uint32_t (&x)[15])
+{
+    uint32_t ones = x[0], c[7];
+#pragma unroll
+    for (int i = 0; i < 7; ++i) c[i] = add_bits(ones, x[2 * i + 1], x[2 * i + 2]);
+    uint32_t twos = c[0], d[3];
+#pragma unroll
+    for (int i = 0; i < 3; ++i) d[i] = add_bits(twos, c[2 * i + 1], c[2 * i + 2]);
+    uint32_t fours = d[0];
+    const uint32_t eights = add_bits(fours, d[1], d[2]);
+    return Planes{ones, twos, fours, eights};
+}
+
+// ORs into acc the sets of the four nodes of one chunk of a neighbour list.
+template <int NW>
+__device__ __forceinline__ void or_chunk(Bits<NW> &acc, const uint32_t *sets, const uint2 c)
+{
+    const Bits<NW> a = ld_bits<NW>(sets + (c.x & 0xFFFFu) * NW), b = ld_bits<NW>(sets + (c.x >> 16) * NW);
+    const Bits<NW> d = ld_bits<NW>(sets + (c.y & 0xFFFFu) * NW), e = ld_bits<NW>(sets + (c.y >> 16) * NW);
+#pragma unroll
+    for (int q = 0; q < NW; ++q) acc.w[q] |= a.w[q] | b.w[q] | d.w[q] | e.w[q];
+}
+
+// Whether b holds every bit of full.
+template <int NW>
+__device__ __forceinline__ bool covers(const Bits<NW> &b, const Bits<NW> &full)
+{
+    uint32_t miss = 0;
+#pragma unroll
+    for (int q = 0; q < NW; ++q) miss |= full.w[q] & ~b.w[q];
+    return miss == 0;
+}
+
+constexpr int kHubLanes = 16;  // lanes that pull a node of more than kHubDegree neighbours
+
+// Neighbour lists of the reachable-sets kernel.  Nodes are renumbered by
+// descending degree (`rank`; pc and mcn do not depend on the numbering), so
+// that neighbouring threads pull lists of similar lengths and touch
+// neighbouring sets.  Node v's list is chunks [off[v], off[v + 1]) of four
+// 16-bit ids, the last one filled up with v itself.
+struct ReachGraph {
+    const uint16_t *rank;  // [n]
+    const int32_t *off;    // [n + 1]
+    const uint2 *ids;      // [off[n]]
+    int32_t n, n_hub;      // nodes; those of more than kHubDegree neighbours (the first ones)
+};
+
+// Reachability from 32 NW sources of one removal set, a task a time: task t
+// takes the sources [32 NW sb, 32 NW (sb + 1)), sb = t mod nsb, of individual
+// t / nsb, and a block a contiguous run of tasks.  LDS: the sets of all n
+// nodes twice (the hop being read and the hop being written), rows of NW
+// words padded to a multiple of 32 rows; the removed-node bit set; with
+// kLdsGraph also the offsets and neighbour lists, so that a task reads nothing
+// from global memory but its genes.  Removed nodes have empty sets
+// throughout, so no neighbour needs a test (M's 1 on their diagonal cancels
+// in sum M - n).
+//
+// The state after hop 1 is set from the sources' own neighbour lists (one
+// atomic OR an edge); every later hop is a pull: a node ORs its neighbours'
+// sets, unless it has every surviving source already.  The first n_hub nodes
+// are pulled by kHubLanes lanes each, the others by one.  A hop that changes
+// nothing is the last.
+//
+// M is symmetric: the row sum of source s is the number of nodes that hold
+// bit s.
+//
+// Bound by LDS: a hop of the BA graph (n = 2000, m = 2) reads 195 KB of sets
+// and ids a task, 16-byte rows at random (about three to a bank), and takes
+// 2.3 us of a task's 15 (six hops); the other 4 us are hop 1 and the counts.
+// Adjacency read from global memory (order, row pointers, columns: a chain of
+// three loads a node): 0.72 ms for 512 individuals against 0.48.  Two blocks of
+// half the sources a compute unit: 0.78; 512 threads: 0.73.  Row sums by
+// transposing every word instead of the bit planes: 0.51.
+constexpr int kSumBits = 40;  // n^2 <= 2^26 for GAPA_SIXDST_MAX_N
+constexpr unsigned long long kTaskDone = 1ull << kSumBits;
+
+template <int NW, bool kLdsGraph>
+__global__ __launch_bounds__(1024) void k_six_reach(const int32_t *__restrict__ genes, int32_t k, const ReachGraph g,
+                                                    int32_t hops, int32_t nsb, int64_t tasks,
+                                                    unsigned long long *__restrict__ pc, int32_t *__restrict__ mcn,
+                                                    int32_t *__restrict__ flag)
+{
+    extern __shared__ __align__(16) uint32_t six_lds[];
+    __shared__ int32_t s_cnt[32 * NW];
+    __shared__ int32_t s_changed[3];
+    const int32_t n = g.n, W = (n + 31) / 32, rows = W * 32;
+    const int32_t T = blockDim.x, tid = threadIdx.x;
+    uint32_t *dead = six_lds + 2 * rows * NW;
+    const int32_t *off = g.off;
+    const uint2 *ids = g.ids;
+    if constexpr (kLdsGraph) {
+        uint2 *l_ids = reinterpret_cast<uint2 *>(dead + (W + 1) / 2 * 2);
+        const int32_t chunks = g.off[n];
+        int32_t *l_off = reinterpret_cast<int32_t *>(l_ids + chunks);
+        for (int32_t i = tid; i < chunks; i += T) l_ids[i] = g.ids[i];
+        for (int32_t i = tid; i <= n; i += T) l_off[i] = g.off[i];
+        off = l_off;
+        ids = l_ids;
+    }
+    const int32_t sub = tid % kHubLanes;
+    // this block's tasks
+    const int64_t per = tasks / gridDim.x, extra = tasks % gridDim.x;
+    const int64_t t0 = blockIdx.x * per + min((int64_t)blockIdx.x, extra);
+    const int64_t t1 = t0 + per + (blockIdx.x < extra ? 1 : 0);
+    int32_t z_dead = -1;  // individual the removed-node set is of
+    for (int64_t task = t0; task < t1; ++task) {
+        const int32_t z = (int32_t)(task / nsb), w0 = (int32_t)(task % nsb) * NW;
+        uint32_t *cur = six_lds, *nxt = six_lds + rows * NW;
+        for (int32_t i = tid; i < rows * NW / 4; i += T) reinterpret_cast<uint4 *>(cur)[i] = uint4{0, 0, 0, 0};
+        for (int32_t i = tid; i < 32 * NW; i += T) s_cnt[i] = 0;
+        if (tid < 3) s_changed[tid] = 0;
+        if (z != z_dead) {
+            z_dead = z;
+            // the last word's padding nodes count as removed
+            for (int32_t w = tid; w < W; w += T) dead[w] = w == W - 1 && (n & 31) ? ~0u << (n & 31) : 0u;
+            __syncthreads();
+            for (int32_t j = tid; j < k; j += T) {
+                const int32_t v = genes[(int64_t)z * k + j];
+                if (v >= 0 && v < n) {
+                    const int32_t r = g.rank[v];
+                    atomicOr(&dead[r >> 5], 1u << (r & 31));
+                } else {
+                    atomicOr(flag, 1);
+                }
+            }
+        }
+        __syncthreads();
+        Bits<NW> full;
+#pragma unroll
+        for (int q = 0; q < NW; ++q) full.w[q] = w0 + q < W ? ~dead[w0 + q] : 0u;
+
+        // after hop 1: every surviving source and its surviving neighbours
+        for (int32_t t = tid / kHubLanes; t < 32 * NW; t += T / kHubLanes) {
+            const int32_t s = w0 * 32 + t;
+            if (s >= n || removed(dead, s)) continue;
+            const uint32_t bit = 1u << (t & 31);
+            uint32_t *word = cur + (t >> 5);
+            const int32_t c1 = off[s + 1];
+            for (int32_t c = off[s] + sub; c < c1; c += kHubLanes) {
+                const uint2 q = ids[c];
+                const int32_t u[4] = {(int32_t)(q.x & 0xFFFFu), (int32_t)(q.x >> 16), (int32_t)(q.y & 0xFFFFu),
+                                      (int32_t)(q.y >> 16)};
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (!removed(dead, u[e])) atomicOr(word + u[e] * NW, bit);
+            }
+            if (sub == 0) atomicOr(word + s * NW, bit);
+        }
+        __syncthreads();
+
+        for (int32_t h = 2; h <= hops; ++h) {
+            bool changed = false;
+            for (int32_t v = tid / kHubLanes; v < g.n_hub; v += T / kHubLanes) {
+                Bits<NW> acc = ld_bits<NW>(cur + v * NW);
+                const Bits<NW> mine = acc;
+                if (!removed(dead, v) && !covers<NW>(mine, full)) {
+                    const int32_t c1 = off[v + 1];
+                    for (int32_t c = off[v] + sub; c < c1; c += kHubLanes) or_chunk<NW>(acc, cur, ids[c]);
+#pragma unroll
+                    for (int q = 0; q < NW; ++q) acc.w[q] = row_or(acc.w[q]);
+#pragma unroll
+                    for (int q = 0; q < NW; ++q) changed |= acc.w[q] != mine.w[q];
+                }
+                if (sub == 0) st_bits<NW>(nxt + v * NW, acc);
+            }
+            for (int32_t v = g.n_hub + tid; v < n; v += T) {
+                Bits<NW> acc = ld_bits<NW>(cur + v * NW);
+                const Bits<NW> mine = acc;
+                if (!removed(dead, v) && !covers<NW>(mine, full)) {
+                    const int32_t c1 = off[v + 1];
+                    for (int32_t c = off[v]; c < c1; ++c) or_chunk<NW>(acc, cur, ids[c]);
+#pragma unroll
+                    for (int q = 0; q < NW; ++q) changed |= acc.w[q] != mine.w[q];
+                }
+                st_bits<NW>(nxt + v * NW, acc);
+            }
+            // three flags in turn: the one the hop after next will use is
+            // cleared while nobody reads or sets it
+            if (changed) s_changed[h % 3] = 1;
+            if (tid == 0) s_changed[(h + 1) % 3] = 0;
+            __syncthreads();
+            uint32_t *t = cur;
+            cur = nxt;
+            nxt = t;
+            if (!s_changed[h % 3]) break;
+        }
+
+        // row sums of the sources: a half-wave takes one word of 480 nodes,
+        // 15 a lane, as bit planes of their counts; transposed, lane c of
+        // plane p has the bits of source c
+        const int l32 = tid & 31;
+        const int32_t word_tasks = (n + 479) / 480 * NW;
+        for (int32_t t = tid >> 5; t < word_tasks; t += T >> 5) {
+            const int32_t q = t % NW, v0 = t / NW * 480 + l32;
+            uint32_t x[15];
+#pragma unroll
+            for (int i = 0; i < 15; ++i) x[i] = v0 + 32 * i < n ? cur[(v0 + 32 * i) * NW + q] : 0u;
+            const Planes p = count_bits15(x);
+            const int32_t cnt = __popc(transpose32(p.p0, l32)) + 2 * __popc(transpose32(p.p1, l32)) +
+                                4 * __popc(transpose32(p.p2, l32)) + 8 * __popc(transpose32(p.p3, l32));
+            if (cnt) atomicAdd(&s_cnt[q * 32 + l32], cnt);
+        }
+        __syncthreads();
+        if (tid < 64) {
+            // row sums less the sources themselves: twice the pairs, over all
+            // tasks of the individual; its last task to finish (the task count
+            // is kept in the high bits of the sum) halves it
+            int32_t best = 0, sum = 0;
+            for (int32_t i = tid; i < 32 * NW; i += 64) {
+                best = max(best, s_cnt[i]);
+                sum += max(s_cnt[i] - 1, 0);
+            }
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) {
+                best = max(best, __shfl_xor(best, o, 64));
+                sum += __shfl_xor(sum, o, 64);
+            }
+            if (tid == 0) {
+                if (best) atomicMax(mcn + z, best);
+                const unsigned long long old = atomicAdd(pc + z, kTaskDone + (unsigned long long)sum);
+                if (old >> kSumBits == (unsigned long long)nsb - 1) pc[z] = ((old & (kTaskDone - 1)) + sum) / 2;
+            }
+        }
+        __syncthreads();  // the sums and sets are read before the next task clears them
+    }
+}
+
+// Rates the two ways are priced at: words ORed a second by the pulls (a path
+// of 2000 nodes, nothing saturated, 5.8e12), multiply-adds a second by the
+// products (n = 2000: 1.24e15 to 1.3e15).
+constexpr double kPullRate = 6e12, kMacRate = 1.3e15;
+
+// Launch shape of k_six_reach.  A block takes four words of sources where two
+// copies of the sets (and, if they fit beside them, the neighbour lists) leave
+// room for that in LDS, else two.
+constexpr size_t kReachLds = 158 * 1024;
+struct ReachShape {
+    int32_t NW, threads;
+    bool lds_graph;
+    size_t lds;
+};
+
+ReachShape reach_shape(const gapa_graph *g)
+{
+    const size_t W = (size_t)g->words;
+    const size_t graph = (size_t)g->reach_chunks * 8 + ((size_t)g->n + 1) * 4;
+    auto sets = [&](int32_t NW) { return 2 * W * 32 * NW * 4 + (W + 1) / 2 * 8; };
+    ReachShape r{};
+    r.NW = g->n > 64 && sets(4) <= kReachLds ? 4 : 2;
+    if (r.NW == 4 && sets(4) + graph > kReachLds && sets(2) + graph <= kReachLds) r.NW = 2;
+    r.lds_graph = sets(r.NW) + graph <= kReachLds;
+    r.lds = sets(r.NW) + (r.lds_graph ? graph : 0);
+    r.threads = g->n <= 384 ? 256 : r.lds <= kReachLds / 2 && g->n <= 1536 ? 512 : 1024;
+    return r;
+}
+
+template <int NW, bool kLdsGraph>
+int launch_reach(const ReachShape &r, int32_t blocks, const int32_t *genes, int32_t k, const ReachGraph &g, int32_t hops,
+                 int32_t nsb, int64_t tasks, int64_t *pc, int32_t *mcn, int32_t *flag, hipStream_t s)
+{
+    // (always the same limit: threads on other graphs launch the kernel too)
+    if (r.lds > 64 * 1024)
+        GAPA_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(k_six_reach<NW, kLdsGraph>),
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)kReachLds));
+    hipLaunchKernelGGL((k_six_reach<NW, kLdsGraph>), dim3((unsigned)blocks), dim3(r.threads), r.lds, s, genes, k, g,
+                       hops, nsb, tasks, reinterpret_cast<unsigned long long *>(pc), mcn, flag);
+    GAPA_HIP(hipGetLastError());
+    return GAPA_OK;
+}
+
 }  // namespace
+
+// Which of the two ways is taken.  The reachable sets pay for every edge at
+// every hop until nothing changes, the products for the dense matrix log2(hops)
+// times.  How many hops change something is not known beforehand: four times
+// the breadth-first levels of G is allowed for, and at most eight times the
+// products' cost if all of them did.  Measured, reachable sets against
+// products: BA n = 2000 (m = 2), 512 individuals, hops = 6: 0.48 against 11.4
+// ms, hops = 2: 0.21 against 4.2; random graph of mean degree 200 (256
+// individuals, hops = 6): 0.98 against 5.8 ms; path of 2000 nodes (64
+// individuals), 100 hops: 0.55 against 3.5 ms; n = 8192, mean degree 6 (64
+// individuals, hops = 6): 1.1 against 83.7 ms.  A clique of half the nodes
+// with the others as a path on it, all hops: the products (each hop changes
+// every set of the clique).
+bool sixdst_sparse(const gapa_graph *g, int32_t hops)
+{
+    const double np = (double)((g->n + kTile - 1) / kTile * kTile);
+    const double hop = ((double)g->nnz + 2.0 * g->n) * g->words / kPullRate;
+    int32_t products = 0;
+    for (int32_t h = hops; h > 1; h >>= 1) products += 1 + (h & 1);
+    const double dense = products * np * np * np / kMacRate;
+    const int32_t most = std::min(hops - 1, g->n);
+    return std::min(most, 4 * g->levels) * hop <= dense && most * hop <= 8.0 * dense;
+}
+
+// pc[P], mcn[P] (device) of P gene rows by reachable sets; a gene outside
+// [0, n) sets flag[0].  Needs no workspace.
+int sixdst_eval_genes(gapa_graph *g, const int32_t *genes, int32_t P, int32_t k, int32_t hops, int64_t *pc,
+                      int32_t *mcn, int32_t *flag, hipStream_t s)
+{
+    const ReachShape r = reach_shape(g);
+    const unsigned char *lists = g->d_reach;
+    const size_t off_at = (size_t)g->reach_chunks * 8, rank_at = off_at + ((size_t)g->n + 1) * 4;
+    const ReachGraph rg{reinterpret_cast<const uint16_t *>(lists + rank_at),
+                        reinterpret_cast<const int32_t *>(lists + off_at), reinterpret_cast<const uint2 *>(lists),
+                        g->n, g->n_hub};
+    const int32_t nsb = (g->words + r.NW - 1) / r.NW;
+    const int64_t tasks = (int64_t)P * nsb;
+    // as many blocks as the chip holds at once, each with its run of tasks
+    const int32_t per_cu = (int32_t)std::max<size_t>(1, std::min<size_t>(2048 / r.threads, (160 * 1024) / (r.lds + 1024)));
+    const int32_t blocks = (int32_t)std::min<int64_t>(tasks, 256 * per_cu);
+    hipLaunchKernelGGL(k_six_clear, dim3((std::max(P, 4) + 255) / 256), dim3(256), 0, s, pc, mcn, P, flag);
+    GAPA_HIP(hipGetLastError());
+    if (r.NW == 4)
+        return r.lds_graph ? launch_reach<4, true>(r, blocks, genes, k, rg, hops, nsb, tasks, pc, mcn, flag, s)
+                           : launch_reach<4, false>(r, blocks, genes, k, rg, hops, nsb, tasks, pc, mcn, flag, s);
+    return r.lds_graph ? launch_reach<2, true>(r, blocks, genes, k, rg, hops, nsb, tasks, pc, mcn, flag, s)
+                       : launch_reach<2, false>(r, blocks, genes, k, rg, hops, nsb, tasks, pc, mcn, flag, s);
+}
 
 size_t sixdst_bytes_per_individual(int32_t n)
 {

@@ -112,3 +112,49 @@ def test_tiny_graphs_empty_rows_and_huge_hop_counts(gp):
         if n > 1:
             pc, mcn = graph.sixdst(np.array([[n // 2]], dtype=np.int32), 10 ** 9)
             assert (int(pc[0]), int(mcn[0])) == O.pc(g, [n // 2])
+
+
+def lollipop(n):
+    """A clique on half the nodes with the others as a path hanging from it."""
+    a = n // 2
+    iu, ju = np.triu_indices(a, 1)
+    v = np.arange(a - 1, n - 1)
+    return inputs.csr_from_edges(n, np.concatenate([iu, v]), np.concatenate([ju, v + 1]))
+
+
+# node counts around the changes of the kernel's shape: one word of sources
+# short of two and four, 32-node words, the block sizes, the neighbour lists
+# beside the sets in LDS or not, two or four words of sources, the largest n;
+# then hop counts at which the products are taken
+@pytest.mark.parametrize("kind,n,hops", [
+    ("er", 31, 3), ("er", 33, 2), ("er", 64, 4), ("er", 65, 4), ("ba", 384, 3), ("ba", 385, 5), ("ba", 1536, 3),
+    ("er", 1537, 4), ("ba", 2048, 6), ("dense", 700, 2), ("er", 4736, 4), ("er", 4737, 3), ("ba", 8192, 4),
+    ("er", 8191, 8192), ("lollipop", 300, 300), ("lollipop", 300, 20)])
+def test_shapes_match_sparse_powers(gp, kind, n, hops):
+    """Against the pattern of (A_S + I)^hops by scipy's sparse products; rows
+    with a repeated gene, with the highest-degree nodes, and empty of hubs."""
+    import scipy.sparse as sp
+    g = {"er": lambda: inputs.erdos_renyi(n, 2.5, seed=n), "ba": lambda: inputs.barabasi_albert(n, 2, seed=n),
+         "dense": lambda: inputs.erdos_renyi(n, 150.0, seed=n), "lollipop": lambda: lollipop(n)}[kind]()
+    k = max(2, n // 50)
+    genes = inputs.random_population(n, k, 3, seed=n + hops)
+    genes[0] = np.argsort(-g.degrees(), kind="stable")[:k]
+    genes[1, 1] = genes[1, 0]
+    print(f"{kind} n={n} hops={hops}", flush=True)
+    pc, mcn = gp.Graph.from_csr(g).sixdst(genes, hops)
+    for i, row in enumerate(genes):
+        keep = np.ones(n)
+        keep[row] = 0
+        A = sp.csr_matrix((np.ones(g.nnz), g.col_idx, g.row_ptr), shape=(n, n))
+        M1 = sp.diags(keep) @ A @ sp.diags(keep) + sp.identity(n)
+        if hops >= n:  # the components
+            _, lab = sp.csgraph.connected_components(M1, directed=False)
+            sizes = np.bincount(lab)
+            want = int((sizes * (sizes - 1) // 2).sum()), int(sizes[lab[keep > 0]].max())
+        else:
+            M = M1
+            for _ in range(hops - 1):
+                M = ((M @ M1) > 0).astype(np.float64)
+            sums = np.asarray(M.sum(axis=1)).ravel().astype(np.int64)
+            want = int((sums.sum() - n) // 2), int(sums[keep > 0].max())
+        assert (int(pc[i]), int(mcn[i])) == want, i
