@@ -141,8 +141,10 @@ GAPA_API int gapa_eval_population(gapa_graph *g, const int32_t *genes, int32_t P
  *
  * Every buffer the evaluation needs comes from a fixed scratch array of
  * GAPA_NOALLOC_SCRATCH_BYTES that the library holds on every GPU it runs on
- * from the library's load to the end of the process.  The population is
- * evaluated in chunks of 32 Wd individuals, Wd the largest power of two <= 32
+ * from the library's load to the end of the process.  Larger graphs than one
+ * workgroup's LDS holds (more than 65 535 nodes; or 18 000 if the longest
+ * shortest paths are of dozens of hops) are evaluated in chunks of 32 Wd
+ * individuals, Wd the largest power of two <= 32
  * whose buffers fit: about 32 Wd (8.25 n + 8 n_noniso + 4 W + 4 sweep_grid)
  * bytes for n nodes, n_noniso of them with an edge, W = ceil(n / 32) and the
  * graph's sweep_grid (gapa_tuning); a graph on which not even 32 individuals
@@ -428,7 +430,8 @@ GAPA_API int gapa_batch_destroy(gapa_batch *b);
 
 /* Kernel timing: `enable` 1 brackets whole passes with HIP events on their
  * launch stream ("fitness_pass": the batched fitness of one chunk of up to
- * 2048 individuals; "ga_offspring", "ga_init": the operator kernel;
+ * 2048 individuals, or of a whole population evaluated by workgroups;
+ * "ga_offspring", "ga_init": the operator kernel;
  * "elitism"); 2 also brackets every kernel launch inside them (the extra
  * events add gaps, so pass totals are exact only at 1); 0 disables.
  * gapa_*_kernel_times fills up to `cap` entries with the scope name, count
@@ -448,7 +451,8 @@ GAPA_API int gapa_ga_kernel_times(gapa_ga *ga, gapa_kernel_time *out, int32_t ca
 GAPA_API int gapa_batch_set_timing(gapa_batch *b, int32_t enable);
 GAPA_API int gapa_batch_kernel_times(gapa_batch *b, gapa_kernel_time *out, int32_t cap, int32_t *count);
 
-/* Counters of the last chunk the bit-parallel fitness evaluated on a handle
+/* Counters of the last chunk the bit-parallel fitness (graphs larger than one
+ * workgroup evaluates, and batches) evaluated on a handle
  * (waits for outstanding work): out[0] individuals per chunk, out[1] nodes
  * still pending after the ordered sweep, out[2] (individual, node) pairs left
  * to the union-find pass, out[3] follow-up sweeps that still changed
@@ -456,7 +460,8 @@ GAPA_API int gapa_batch_kernel_times(gapa_batch *b, gapa_kernel_time *out, int32
 GAPA_API int gapa_graph_fitness_stats(gapa_graph *g, int64_t out[4]);
 GAPA_API int gapa_ga_fitness_stats(gapa_ga *ga, int64_t out[4]);
 
-/* Launch shapes of the bit-parallel fitness pass.  They change speed only:
+/* Launch shapes of the bit-parallel fitness pass (without effect where
+ * workgroups evaluate the individuals).  They change speed only:
  * results never depend on them.
  *   sweep_grid   blocks of the worklist, pair and union-find kernels, 1..65535
  *   band_scan    neighbours a node reads in the ordered sweep, >= 1

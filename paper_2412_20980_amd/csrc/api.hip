@@ -338,7 +338,7 @@ void release_workspace(FitnessWorkspace &w)
 {
     for (DevBuf *b : {&w.parent, &w.count, &w.dead, &w.reach, &w.ucount, &w.pairs, &w.worklist, &w.pflag, &w.small,
                       &w.masks,
-                      &w.alive, &w.genes, &w.fitness, &w.mcn, &w.flag, &w.six_mats, &w.six_tot})
+                      &w.alive, &w.genes, &w.spill, &w.fitness, &w.mcn, &w.flag, &w.six_mats, &w.six_tot})
         b->release();
     for (FitnessWorkspace *l : w.lanes) {
         release_workspace(*l);
@@ -464,8 +464,8 @@ int graph_build(int dev, int32_t n, int64_t nnz, const int32_t *row_ptr, const i
         if ((e = hipMemcpy(g->d_band_rec, rec.data(), rec.size() * sizeof(int4), hipMemcpyHostToDevice)) != hipSuccess)
             return fail(hip_fail(e, "hipMemcpy"));
     }
-    if (n <= GAPA_SIXDST_MAX_N && voff.size() == 2) {
-        // neighbour lists of the dense reachability fitness
+    if (n <= kListsMaxN && voff.size() == 2) {
+        // NeighbourLists
         std::vector<uint16_t> rank((size_t)n), ids;
         std::vector<int32_t> off((size_t)n + 1, 0);
         for (int32_t r = 0; r < n; ++r) rank[order[r]] = (uint16_t)r;
@@ -473,19 +473,35 @@ int graph_build(int dev, int32_t n, int64_t nnz, const int32_t *row_ptr, const i
         for (int32_t r = 0; r < n; ++r) {
             const int32_t v = order[r];
             g->n_hub += row_ptr[v + 1] - row_ptr[v] > kHubDegree;
-            for (int32_t e = row_ptr[v]; e < row_ptr[v + 1]; ++e) ids.push_back(rank[col_idx[e]]);
-            while (ids.size() % 4 != 0) ids.push_back((uint16_t)r);
+            for (int32_t e = row_ptr[v]; e < row_ptr[v + 1]; ++e) ids.push_back(rank[colD[e]]);
+            g->n_long += row_ptr[v + 1] - row_ptr[v] > 4;
+            while (ids.size() % 4 != 0) ids.push_back(ids[(size_t)off[r] * 4]);
             off[r + 1] = (int32_t)(ids.size() / 4);
         }
-        g->reach_chunks = off[n];
-        // one allocation: ids (8-byte chunks), offsets, ranks
+        g->list_chunks = off[n];
+        {
+            std::vector<int32_t> hop((size_t)n, -1), queue(1, order[0]);
+            hop[order[0]] = 0;
+            for (size_t q = 0; q < queue.size(); ++q)
+                for (int32_t e2 = row_ptr[queue[q]]; e2 < row_ptr[queue[q] + 1]; ++e2)
+                    if (hop[col_idx[e2]] < 0) {
+                        hop[col_idx[e2]] = hop[queue[q]] + 1;
+                        queue.push_back(col_idx[e2]);
+                    }
+            g->depth = hop[queue.back()];
+        }
         const size_t b_ids = ids.size() * 2, b_off = off.size() * 4, b_rank = rank.size() * 2;
-        std::vector<unsigned char> host(b_ids + b_off + b_rank);
-        if (b_ids) std::memcpy(host.data(), ids.data(), b_ids);
-        std::memcpy(host.data() + b_ids, off.data(), b_off);
-        std::memcpy(host.data() + b_ids + b_off, rank.data(), b_rank);
-        if ((e = hipMalloc(&g->d_reach, host.size())) != hipSuccess) return fail(hip_fail(e, "hipMalloc"));
-        if ((e = hipMemcpy(g->d_reach, host.data(), host.size(), hipMemcpyHostToDevice)) != hipSuccess)
+        std::vector<unsigned char> host((size_t)n * 8 + b_ids + b_off + b_rank);
+        unsigned char *to = host.data();
+        for (int32_t r = 0; r < n; ++r, to += 8) {
+            const uint16_t self[4] = {(uint16_t)r, (uint16_t)r, (uint16_t)r, (uint16_t)r};
+            std::memcpy(to, off[r + 1] > off[r] ? &ids[(size_t)off[r] * 4] : self, 8);
+        }
+        if (b_ids) std::memcpy(to, ids.data(), b_ids);
+        std::memcpy(to + b_ids, off.data(), b_off);
+        std::memcpy(to + b_ids + b_off, rank.data(), b_rank);
+        if ((e = hipMalloc(&g->d_lists, host.size())) != hipSuccess) return fail(hip_fail(e, "hipMalloc"));
+        if ((e = hipMemcpy(g->d_lists, host.data(), host.size(), hipMemcpyHostToDevice)) != hipSuccess)
             return fail(hip_fail(e, "hipMemcpy"));
     }
     *out = g;
@@ -511,7 +527,7 @@ void graph_release(gapa_graph *g)
         if (g->d_noniso) (void)hipFree(g->d_noniso);
         if (g->d_src_idx) (void)hipFree(g->d_src_idx);
         if (g->d_band_rec) (void)hipFree(g->d_band_rec);
-        if (g->d_reach) (void)hipFree(g->d_reach);
+        if (g->d_lists) (void)hipFree(g->d_lists);
         release_workspace(g->ws);
     }
     delete g;
@@ -933,8 +949,9 @@ int ga_allocate(gapa_ga *ga, int32_t count, const gapa_params *p, const int32_t 
     ga->objective_mcn = (p[0].flags & GAPA_MINIMISE_MCN) != 0;
     ga->objective_forest = (p[0].flags & GAPA_MAXIMISE_COMPONENTS) != 0;
     if (rc == GAPA_OK && ga->objective_mcn) rc = ga->child_mcn.reserve((size_t)slots * 4);
-    if (rc == GAPA_OK) rc = ga->masks.reserve((size_t)mask_w * 4);
-    if (rc == GAPA_OK) rc = ga->alive.reserve((size_t)slots * 4);
+    ga->by_rows = count == 1 && ga->graph->algorithm == 0 && components_fit(ga->graph);
+    if (rc == GAPA_OK && !ga->by_rows) rc = ga->masks.reserve((size_t)mask_w * 4);
+    if (rc == GAPA_OK && !ga->by_rows) rc = ga->alive.reserve((size_t)slots * 4);
     if (rc == GAPA_OK) rc = ga->src.reserve((size_t)fit_n * 4);
     if (rc == GAPA_OK) rc = ga->flag.reserve(16);
     if (rc == GAPA_OK) rc = ga->gen_ctr.reserve(16);

@@ -119,4 +119,22 @@ __device__ __forceinline__ uint32_t transpose32(uint32_t x, int l32)
     return transpose_round<1>(x, l32, 0x55555555u);
 }
 
+// Inclusive prefix sum over the wave's 64 lanes, in the vector unit alone
+// (shifts inside the rows of 16, then the rows' last lanes broadcast on).
+__device__ __forceinline__ int32_t wave_scan(int32_t x)
+{
+    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xF, 0xF, true);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xF, 0xF, true);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xF, 0xF, true);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xF, 0xF, true);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xA, 0xF, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xC, 0xF, false);
+    return x;
+}
+
+__device__ __forceinline__ int32_t wave_sum(int32_t x)
+{
+    return __builtin_amdgcn_readlane(wave_scan(x), 63);
+}
+
 }  // namespace gapa

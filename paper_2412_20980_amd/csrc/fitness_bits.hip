@@ -1171,6 +1171,16 @@ int eval_genes_bits_scratch(gapa_graph *g, const int32_t *genes, int32_t P, int3
                             int32_t *mcn, Measure measure, void *scratch, size_t bytes, int32_t **flag_out,
                             hipStream_t s)
 {
+    if (components_fit(g)) {
+        // one workgroup an individual; the scratch past the flag takes the
+        // leftover nodes that do not fit LDS
+        int32_t *flag = static_cast<int32_t *>(scratch);
+        *flag_out = flag;
+        const int rc = launch_fill_u32(flag, 0u, 4, s);
+        if (rc != GAPA_OK) return rc;
+        return eval_rows_components(g, genes, P, k, fitness, mcn, flag, static_cast<char *>(scratch) + 256,
+                                    bytes - 256, nullptr, s, measure);
+    }
     // the widest chunk that fits, and no wider than the population needs
     int32_t Wd = 1;
     while (Wd < 32 && Wd * 32 < P) Wd <<= 1;

@@ -682,7 +682,7 @@ OpArgs make_args(gapa_ga *ga, const int32_t *pop, const int64_t *fit)
     a.alive = ga->alive.as<int32_t>();
     a.flag = ga->flag.as<int32_t>();
     a.gen_ctr = ga->gen_ctr.as<uint32_t>();
-    a.rows_only = 0;
+    a.rows_only = ga->by_rows ? 1 : 0;
     return a;
 }
 
@@ -751,7 +751,7 @@ int ga_launch_init(gapa_ga *ga, hipStream_t s)
 int ga_launch_offspring(gapa_ga *ga, hipStream_t s, bool rows_only)
 {
     OpArgs a = make_args(ga, ga->pop[ga->cur].as<int32_t>(), ga->fit[ga->cur].as<int64_t>());
-    a.rows_only = rows_only ? 1 : 0;
+    a.rows_only |= rows_only ? 1 : 0;
     TimedScope ts(&ga->timer, "ga_offspring", s, 1);
     hipLaunchKernelGGL(k_offspring, dim3(ga->max_lambda, ga->count), dim3(kOpBlock), ga->op_lds_bytes, s, a);
     GAPA_HIP(hipGetLastError());
@@ -763,7 +763,11 @@ int ga_eval_children(gapa_ga *ga, bool init, hipStream_t s)
     int32_t *mcn = ga->objective_mcn ? ga->child_mcn.as<int32_t>() : nullptr;
     const Measure measure = ga->objective_forest ? kMeasureForest : kMeasurePC;
     int rc;
-    if (ga->count > 1)
+    if (ga->by_rows)
+        rc = eval_rows_components_ws(ga->graph, ga->children.as<int32_t>(), init ? ga->params.pop : ga->lambda,
+                                     ga->params.k, ga->child_fit.as<int64_t>(), mcn, ga->flag.as<int32_t>() + 3,
+                                     ga->ws, &ga->timer, s, measure);
+    else if (ga->count > 1)
         rc = eval_masks(ga->graph, ga->masks.as<uint32_t>(), ga->alive.as<int32_t>(), 0, ga->child_fit.as<int64_t>(),
                         mcn, ga->ws, &ga->timer, s, init ? &ga->tab_init : &ga->tab_gen, measure);
     else

@@ -106,6 +106,7 @@ struct FitnessWorkspace {
     DevBuf masks;    // uint32 [P][W] removed-node bit sets (eval_population)
     DevBuf alive;    // int32 [P]    surviving non-isolated nodes (eval_population)
     DevBuf genes;    // int32 [P][k]  staged host genes
+    DevBuf spill;    // int32 union-find parents of eval_rows_components beyond LDS
     DevBuf fitness;  // int64 [P]
     DevBuf mcn;      // int32 [P]
     DevBuf flag;     // int32 [4]     device error flags
@@ -147,15 +148,16 @@ struct gapa_graph {
     uint32_t *d_noniso = nullptr; // [words] bit v set: v has at least one edge
     int8_t *d_src_idx = nullptr;  // [n] index of a band source among its instance's (order[voff + t]), else -1
     std::vector<int32_t> band_off;  // host: band b is d_band_rec[band_off[b], band_off[b+1])
+    int32_t depth = 0;          // hops from the first of d_order to the farthest node it reaches (with d_lists)
     int32_t levels = 0;         // breadth-first levels from the highest-degree nodes
     int32_t src_band = 0;       // size of band 0 when it holds exactly the sources, else 0
     int32_t n_noniso = 0;       // nodes with at least one edge
-    // neighbour lists of the dense reachability fitness (n <= GAPA_SIXDST_MAX_N, one
-    // instance), nodes renumbered by descending degree: reach_chunks chunks of
-    // four 16-bit ids, then the int32 [n + 1] first chunk of each node, then the
-    // uint16 [n] new number of each node
-    unsigned char *d_reach = nullptr;
-    int32_t reach_chunks = 0;
+    // NeighbourLists of a one-instance graph of at most kListsMaxN nodes:
+    // the n first chunks of four 16-bit ids, all list_chunks chunks, the int32
+    // [n + 1] first chunk of each node, the uint16 [n] new number of each node
+    unsigned char *d_lists = nullptr;
+    int32_t list_chunks = 0;
+    int32_t n_long = 0;         // nodes of more than four neighbours
     int32_t n_hub = 0;          // nodes of more than kHubDegree neighbours
     int32_t algorithm = 0;      // 0: bit-parallel sweeps, 1: edge-parallel union-find
     gapa::Tuning tune;
@@ -237,6 +239,46 @@ int launch_bits_transpose(const uint32_t *masks, int32_t P, int32_t W, int32_t n
 
 // Fills count 32-bit words at p with value (a kernel, not a memset node).
 int launch_fill_u32(void *p, uint32_t value, int64_t count, hipStream_t s);
+// A graph's neighbour lists for the kernels that keep per-node state of whole
+// individuals in LDS.  Nodes are renumbered by descending degree (`rank`;
+// fitness values do not depend on the numbering), so that neighbouring
+// threads walk lists of similar lengths, and isolated nodes come last.  Node
+// v's list is chunks [off[v], off[v + 1]) of four 16-bit ids, ascending (so
+// by descending degree), the last one filled up with its first neighbour; head[v]
+// is its first chunk (all v for an isolated node).
+struct NeighbourLists {
+    const uint16_t *rank;  // [n]
+    const int32_t *off;    // [n + 1]
+    const uint2 *ids;      // [off[n]]
+    const uint2 *head;     // [n]
+    int32_t n;
+    int32_t n_long;        // nodes of more than one chunk: the first n_long
+};
+constexpr int32_t kListsMaxN = 65535;
+
+inline NeighbourLists neighbour_lists(const gapa_graph *g)
+{
+    const size_t ids_at = (size_t)g->n * 8, off_at = ids_at + (size_t)g->list_chunks * 8;
+    const size_t rank_at = off_at + ((size_t)g->n + 1) * 4;
+    return NeighbourLists{reinterpret_cast<const uint16_t *>(g->d_lists + rank_at),
+                          reinterpret_cast<const int32_t *>(g->d_lists + off_at),
+                          reinterpret_cast<const uint2 *>(g->d_lists + ids_at),
+                          reinterpret_cast<const uint2 *>(g->d_lists), g->n, g->n_long};
+}
+
+// Fitness of P gene rows (device, [P][k]) by one workgroup each
+// (components.hip), on graphs with neighbour lists: one launch.  A gene outside
+// [0, n) sets flag[0] and is ignored.  spill: components_spill_bytes of
+// device memory (fewer: fewer workgroups side by side).
+bool components_fit(const gapa_graph *g);
+size_t components_spill_bytes(const gapa_graph *g, int32_t P);
+int eval_rows_components(gapa_graph *g, const int32_t *genes, int32_t P, int32_t k, int64_t *fitness, int32_t *mcn,
+                         int32_t *flag, void *spill, size_t spill_bytes, KernelTimer *timer, hipStream_t s,
+                         Measure measure);
+// The same with the spill in ws (grown as needed).
+int eval_rows_components_ws(gapa_graph *g, const int32_t *genes, int32_t P, int32_t k, int64_t *fitness, int32_t *mcn,
+                            int32_t *flag, FitnessWorkspace &ws, KernelTimer *timer, hipStream_t s, Measure measure);
+
 // Dense reachability fitness (sixdst.hip).  kHubDegree: nodes above it are
 // pulled by several lanes each.
 constexpr int32_t kHubDegree = 24;
@@ -341,6 +383,7 @@ struct gapa_ga {
     int32_t slots = 0;
     bool objective_mcn = false;
     bool objective_forest = false;  // GAPA_MAXIMISE_COMPONENTS: fitness = |V minus S| - components
+    bool by_rows = false;         // fitness by eval_rows_components: no bit sets are made
     gapa::DevBuf masks;           // uint32 removed-node bit sets of the children
     gapa::DevBuf alive;           // int32 slots: surviving non-isolated nodes
     gapa::DevBuf src;             // int32 [sum P] elitism: source tag of each kept row

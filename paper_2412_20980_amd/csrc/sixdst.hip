@@ -299,18 +299,6 @@ __device__ __forceinline__ bool covers(const Bits<NW> &b, const Bits<NW> &full)
 
 constexpr int kHubLanes = 16;  // lanes that pull a node of more than kHubDegree neighbours
 
-// Neighbour lists of the reachable-sets kernel.  Nodes are renumbered by
-// descending degree (`rank`; pc and mcn do not depend on the numbering), so
-// that neighbouring threads pull lists of similar lengths and touch
-// neighbouring sets.  Node v's list is chunks [off[v], off[v + 1]) of four
-// 16-bit ids, the last one filled up with v itself.
-struct ReachGraph {
-    const uint16_t *rank;  // [n]
-    const int32_t *off;    // [n + 1]
-    const uint2 *ids;      // [off[n]]
-    int32_t n, n_hub;      // nodes; those of more than kHubDegree neighbours (the first ones)
-};
-
 // Reachability from 32 NW sources of one removal set, a task a time: task t
 // takes the sources [32 NW sb, 32 NW (sb + 1)), sb = t mod nsb, of individual
 // t / nsb, and a block a contiguous run of tasks.  LDS: the sets of all n
@@ -341,8 +329,8 @@ constexpr int kSumBits = 40;  // n^2 <= 2^26 for GAPA_SIXDST_MAX_N
 constexpr unsigned long long kTaskDone = 1ull << kSumBits;
 
 template <int NW, bool kLdsGraph>
-__global__ __launch_bounds__(1024) void k_six_reach(const int32_t *__restrict__ genes, int32_t k, const ReachGraph g,
-                                                    int32_t hops, int32_t nsb, int64_t tasks,
+__global__ __launch_bounds__(1024) void k_six_reach(const int32_t *__restrict__ genes, int32_t k, const NeighbourLists g,
+                                                    int32_t n_hub, int32_t hops, int32_t nsb, int64_t tasks,
                                                     unsigned long long *__restrict__ pc, int32_t *__restrict__ mcn,
                                                     int32_t *__restrict__ flag)
 {
@@ -416,7 +404,7 @@ __global__ __launch_bounds__(1024) void k_six_reach(const int32_t *__restrict__ 
 
         for (int32_t h = 2; h <= hops; ++h) {
             bool changed = false;
-            for (int32_t v = tid / kHubLanes; v < g.n_hub; v += T / kHubLanes) {
+            for (int32_t v = tid / kHubLanes; v < n_hub; v += T / kHubLanes) {
                 Bits<NW> acc = ld_bits<NW>(cur + v * NW);
                 const Bits<NW> mine = acc;
                 if (!removed(dead, v) && !covers<NW>(mine, full)) {
@@ -429,7 +417,7 @@ __global__ __launch_bounds__(1024) void k_six_reach(const int32_t *__restrict__ 
                 }
                 if (sub == 0) st_bits<NW>(nxt + v * NW, acc);
             }
-            for (int32_t v = g.n_hub + tid; v < n; v += T) {
+            for (int32_t v = n_hub + tid; v < n; v += T) {
                 Bits<NW> acc = ld_bits<NW>(cur + v * NW);
                 const Bits<NW> mine = acc;
                 if (!removed(dead, v) && !covers<NW>(mine, full)) {
@@ -509,7 +497,7 @@ struct ReachShape {
 ReachShape reach_shape(const gapa_graph *g)
 {
     const size_t W = (size_t)g->words;
-    const size_t graph = (size_t)g->reach_chunks * 8 + ((size_t)g->n + 1) * 4;
+    const size_t graph = (size_t)g->list_chunks * 8 + ((size_t)g->n + 1) * 4;
     auto sets = [&](int32_t NW) { return 2 * W * 32 * NW * 4 + (W + 1) / 2 * 8; };
     ReachShape r{};
     r.NW = g->n > 64 && sets(4) <= kReachLds ? 4 : 2;
@@ -521,15 +509,15 @@ ReachShape reach_shape(const gapa_graph *g)
 }
 
 template <int NW, bool kLdsGraph>
-int launch_reach(const ReachShape &r, int32_t blocks, const int32_t *genes, int32_t k, const ReachGraph &g, int32_t hops,
-                 int32_t nsb, int64_t tasks, int64_t *pc, int32_t *mcn, int32_t *flag, hipStream_t s)
+int launch_reach(const ReachShape &r, int32_t blocks, const int32_t *genes, int32_t k, const gapa_graph *g,
+                 int32_t hops, int32_t nsb, int64_t tasks, int64_t *pc, int32_t *mcn, int32_t *flag, hipStream_t s)
 {
     // (always the same limit: threads on other graphs launch the kernel too)
     if (r.lds > 64 * 1024)
         GAPA_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(k_six_reach<NW, kLdsGraph>),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)kReachLds));
-    hipLaunchKernelGGL((k_six_reach<NW, kLdsGraph>), dim3((unsigned)blocks), dim3(r.threads), r.lds, s, genes, k, g,
-                       hops, nsb, tasks, reinterpret_cast<unsigned long long *>(pc), mcn, flag);
+    hipLaunchKernelGGL((k_six_reach<NW, kLdsGraph>), dim3((unsigned)blocks), dim3(r.threads), r.lds, s, genes, k,
+                       neighbour_lists(g), g->n_hub, hops, nsb, tasks, reinterpret_cast<unsigned long long *>(pc), mcn, flag);
     GAPA_HIP(hipGetLastError());
     return GAPA_OK;
 }
@@ -565,11 +553,6 @@ int sixdst_eval_genes(gapa_graph *g, const int32_t *genes, int32_t P, int32_t k,
                       int32_t *mcn, int32_t *flag, hipStream_t s)
 {
     const ReachShape r = reach_shape(g);
-    const unsigned char *lists = g->d_reach;
-    const size_t off_at = (size_t)g->reach_chunks * 8, rank_at = off_at + ((size_t)g->n + 1) * 4;
-    const ReachGraph rg{reinterpret_cast<const uint16_t *>(lists + rank_at),
-                        reinterpret_cast<const int32_t *>(lists + off_at), reinterpret_cast<const uint2 *>(lists),
-                        g->n, g->n_hub};
     const int32_t nsb = (g->words + r.NW - 1) / r.NW;
     const int64_t tasks = (int64_t)P * nsb;
     // as many blocks as the chip holds at once, each with its run of tasks
@@ -578,10 +561,10 @@ int sixdst_eval_genes(gapa_graph *g, const int32_t *genes, int32_t P, int32_t k,
     hipLaunchKernelGGL(k_six_clear, dim3((std::max(P, 4) + 255) / 256), dim3(256), 0, s, pc, mcn, P, flag);
     GAPA_HIP(hipGetLastError());
     if (r.NW == 4)
-        return r.lds_graph ? launch_reach<4, true>(r, blocks, genes, k, rg, hops, nsb, tasks, pc, mcn, flag, s)
-                           : launch_reach<4, false>(r, blocks, genes, k, rg, hops, nsb, tasks, pc, mcn, flag, s);
-    return r.lds_graph ? launch_reach<2, true>(r, blocks, genes, k, rg, hops, nsb, tasks, pc, mcn, flag, s)
-                       : launch_reach<2, false>(r, blocks, genes, k, rg, hops, nsb, tasks, pc, mcn, flag, s);
+        return r.lds_graph ? launch_reach<4, true>(r, blocks, genes, k, g, hops, nsb, tasks, pc, mcn, flag, s)
+                           : launch_reach<4, false>(r, blocks, genes, k, g, hops, nsb, tasks, pc, mcn, flag, s);
+    return r.lds_graph ? launch_reach<2, true>(r, blocks, genes, k, g, hops, nsb, tasks, pc, mcn, flag, s)
+                       : launch_reach<2, false>(r, blocks, genes, k, g, hops, nsb, tasks, pc, mcn, flag, s);
 }
 
 size_t sixdst_bytes_per_individual(int32_t n)

@@ -1550,9 +1550,7 @@ int surrogate_generation(gapa_ga *ga, hipStream_t s)
     int32_t neval = L;     // children evaluated exactly (the pool, then the judge's extra sample)
     const int32_t *pool = nullptr;
     if (full) {
-        if ((rc = eval_masks(ga->graph, ga->masks.as<uint32_t>(), ga->alive.as<int32_t>(), L, F, nullptr, ga->ws,
-                             &ga->timer, s)) != GAPA_OK)
-            return rc;
+        if ((rc = ga_eval_children(ga, false, s)) != GAPA_OK) return rc;
         if ((rc = ga_rank_and_gather(ga, false, F, nullptr, 0, s)) != GAPA_OK) return rc;
     } else {
         npool = st.sp.screen;
@@ -1565,13 +1563,19 @@ int surrogate_generation(gapa_ga *ga, hipStream_t s)
                            st.crows.as<int32_t>());
         GAPA_HIP(hipGetLastError());
         gapa_graph *g = ga->graph;
-        if ((rc = launch_mask_build(st.crows.as<int32_t>(), neval, st.k, g->n, g->words, g->d_noniso, g->n_noniso,
-                                    st.cmasks.as<uint32_t>(), st.calive.as<int32_t>(), st.bflag.as<int32_t>(), s)) !=
-            GAPA_OK)
-            return rc;
-        if ((rc = eval_masks(ga->graph, st.cmasks.as<uint32_t>(), st.calive.as<int32_t>(), neval, F, nullptr, ga->ws,
-                             &ga->timer, s)) != GAPA_OK)
-            return rc;
+        if (ga->by_rows) {
+            if ((rc = eval_rows_components_ws(g, st.crows.as<int32_t>(), neval, st.k, F, nullptr,
+                                              st.bflag.as<int32_t>(), ga->ws, &ga->timer, s, kMeasurePC)) != GAPA_OK)
+                return rc;
+        } else {
+            if ((rc = launch_mask_build(st.crows.as<int32_t>(), neval, st.k, g->n, g->words, g->d_noniso, g->n_noniso,
+                                        st.cmasks.as<uint32_t>(), st.calive.as<int32_t>(), st.bflag.as<int32_t>(),
+                                        s)) != GAPA_OK)
+                return rc;
+            if ((rc = eval_masks(ga->graph, st.cmasks.as<uint32_t>(), st.calive.as<int32_t>(), neval, F, nullptr,
+                                 ga->ws, &ga->timer, s)) != GAPA_OK)
+                return rc;
+        }
         if ((rc = ga_rank_and_gather(ga, false, F, pool, npool, s)) != GAPA_OK) return rc;
     }
     double *ds = st.dstats.as<double>();

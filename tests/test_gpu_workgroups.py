@@ -1,0 +1,104 @@
+"""Fitness by one workgroup for every few individuals (graphs of at most 65,535
+nodes), through the C ABI, at the sizes where its shape changes: threads of a
+block, individuals to a block (one to eight, with four to a state byte or
+eight), the node counts at which the states leave less LDS for leftover
+nodes or none, populations that do not fill the last block; graphs without
+edges, with isolated nodes, with hubs and without, trees and paths whose
+leftover nodes outgrow LDS; rows that remove everything, nothing, or repeat a
+gene.  Every row against the library's edge-parallel union-find, a sample
+against the oracle; exact integers."""
+import numpy as np
+import pytest
+
+from oracle import cnd_oracle as O
+from paper_2412_20980_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def gp():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a HIP device"
+    from paper_2412_20980_amd import gapa
+    return gapa
+
+
+def graph_of(kind, n):
+    if kind == "path":
+        v = np.random.default_rng(n).permutation(n)
+        return inputs.csr_from_edges(n, v[:-1], v[1:])
+    if kind == "tree":
+        return inputs.barabasi_albert(n, 1, seed=n)
+    if kind == "ba":
+        return inputs.barabasi_albert(n, 2, seed=n)
+    if kind == "star":
+        return inputs.csr_from_edges(n, np.zeros(n - 1, dtype=np.int64), np.arange(1, n))
+    if kind == "empty":
+        return inputs.csr_from_edges(n, np.zeros(0, dtype=np.int64), np.zeros(0, dtype=np.int64))
+    return inputs.erdos_renyi(n, float(kind), seed=n)  # mean degree
+
+
+def rows_of(g, P, seed):
+    """P rows of n / 50 genes: hubs and others, one in ten with a repeated gene."""
+    rng = np.random.default_rng(seed)
+    k = min(g.n, max(2, g.n // 50))  # (a row has at most n genes)
+    top = np.argsort(-g.degrees(), kind="stable")[:3 * k]
+    rows = np.concatenate([rng.choice(top, size=(P, k // 2)), rng.integers(0, g.n, size=(P, k - k // 2))], axis=1)
+    rows[::10, -1] = rows[::10, 0]
+    return rows.astype(np.int32)
+
+
+@pytest.mark.parametrize("kind,n,P", [
+    ("empty", 1, 3), ("empty", 40, 9), ("1.0", 33, 100), ("ba", 512, 1025), ("2.0", 513, 512), ("ba", 4096, 513),
+    ("3.0", 4097, 257), ("ba", 4097, 1025), ("8.0", 5000, 1), ("star", 9000, 300), ("tree", 9000, 520),
+    ("path", 3000, 600), ("path", 18000, 40), ("path", 18001, 40), ("1.5", 20000, 2050), ("tree", 40000, 1030),
+    ("6.0", 40001, 1030), ("tree", 60000, 70), ("4.0", 65535, 300), ("4.0", 65536, 40)])
+def test_shapes_match_union_find_and_oracle(gp, kind, n, P):
+    g = graph_of(kind, n)
+    rows = rows_of(g, P, seed=n + P)
+    print(f"{kind} n={n} P={P}", flush=True)
+    a, b = gp.Graph.from_csr(g), gp.Graph.from_csr(g, unionfind=True)
+    F, M = a.eval(rows, want_mcn=True)
+    Fu, Mu = b.eval(rows, want_mcn=True)
+    assert np.array_equal(F, Fu) and np.array_equal(M, Mu)
+    assert np.array_equal(a.eval(rows, objective="components"), b.eval(rows, objective="components"))
+    idx = np.unique(np.linspace(0, P - 1, 6).astype(int))
+    Fo, Mo = O.eval_population(g, rows[idx], want_mcn=True)
+    assert np.array_equal(F[idx], Fo) and np.array_equal(M[idx], Mo)
+
+
+def test_everything_and_nothing_removed(gp):
+    g = inputs.erdos_renyi(300, 1.5, seed=5)  # a fifth of the nodes are isolated
+    iso = np.flatnonzero(g.degrees() == 0)
+    assert iso.size > 10
+    graph = gp.Graph.from_csr(g)
+    every = np.arange(g.n, dtype=np.int32)
+    but_one = np.where(every == iso[0], every[every != iso[0]][0], every).astype(np.int32)
+    F, M = graph.eval(np.stack([every, but_one]), want_mcn=True)
+    assert F.tolist() == [0, 0] and M.tolist() == [0, 1]  # nothing survives; one isolated node does
+    F, M = graph.eval(np.zeros((9, 0), dtype=np.int32), want_mcn=True)
+    Fo, Mo = O.pc(g, [])
+    assert (F == Fo).all() and (M == Mo).all()
+
+
+def test_noalloc_and_ga_take_the_same_way(gp):
+    """The allocation-free entry point and a GA's generations (MCN objective,
+    and a population that changes the individuals of a block) on graphs whose
+    leftover nodes outgrow LDS."""
+    import torch
+    g = graph_of("tree", 30000)
+    graph = gp.Graph.from_csr(g)
+    rows = rows_of(g, 300, seed=3)
+    d = torch.from_numpy(rows).cuda()
+    f, m = gp.gapa_eval_population_noalloc(graph.handle, d, flags=gp.GAPA_WANT_MCN)
+    F, M = gp.Graph.from_csr(g, unionfind=True).eval(rows, want_mcn=True)
+    assert np.array_equal(f.cpu().numpy(), F) and np.array_equal(m.cpu().numpy(), M)
+    small = inputs.barabasi_albert(1500, 2, seed=9)
+    ga = gp.GA(gp.Graph.from_csr(small), 20, 70, seed=4, offspring=600, objective="mcn", replay=True)
+    ref = O.OracleGA(small, 20, 70, 4, offspring=600, objective="mcn")
+    for _ in range(4):
+        ga.step(1)
+        ref.step()
+    pop, F = ga.population()
+    assert np.array_equal(pop, ref.pop) and np.array_equal(F, ref.F)
