@@ -58,7 +58,7 @@ def algorithmic_bytes_per_eval(n: int, nnz: int) -> int:
 
 # the pass's kernels, and api.hip for the graph orderings (bands, neighbour
 # order) they run on
-FITNESS_SOURCES = ("fitness_bits.hip", "fitness.hip", "device_common.h", "api.hip")
+FITNESS_SOURCES = ("fitness_bits.hip", "fitness.hip", "components.hip", "device_common.h", "api.hip")
 
 # Launch shapes of the fitness pass per workload (sweep_grid, band_scan,
 # sweeps, band_blocks): the autotuner's choice on each workload's warmed-up

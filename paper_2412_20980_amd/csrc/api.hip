@@ -474,7 +474,6 @@ int graph_build(int dev, int32_t n, int64_t nnz, const int32_t *row_ptr, const i
             const int32_t v = order[r];
             g->n_hub += row_ptr[v + 1] - row_ptr[v] > kHubDegree;
             for (int32_t e = row_ptr[v]; e < row_ptr[v + 1]; ++e) ids.push_back(rank[colD[e]]);
-            g->n_long += row_ptr[v + 1] - row_ptr[v] > 4;
             while (ids.size() % 4 != 0) ids.push_back(ids[(size_t)off[r] * 4]);
             off[r + 1] = (int32_t)(ids.size() / 4);
         }
@@ -879,14 +878,22 @@ bool params_ok(const gapa_params *p, int32_t n)
            p->reserved == 0;
 }
 
+// Whether a GA on g evaluates its rows directly (eval_rows_components).
+bool rows_fit(const gapa_graph *g)
+{
+    return g->algorithm == 0 && components_fit(g);
+}
+
 // Fills the instance table and sizes every buffer of a GA over `count`
 // instances; instance b has parameters p[b], n[b] nodes, n_noniso[b]
 // non-isolated nodes; slot_stride > 0 puts instance b's slots at
-// b * slot_stride (a batch), 0 keeps them contiguous from 0 (one GA).
+// b * slot_stride (a batch), 0 keeps them contiguous from 0 (one GA); by_rows:
+// the fitness needs no bit sets.
 int ga_allocate(gapa_ga *ga, int32_t count, const gapa_params *p, const int32_t *n, const int32_t *n_noniso,
-                int32_t slot_stride)
+                int32_t slot_stride, bool by_rows)
 {
     ga->count = count;
+    ga->by_rows = by_rows;
     ga->params = p[0];
     ga->lambda = p[0].offspring > 0 ? p[0].offspring : p[0].pop;
     ga->t_pc = bernoulli_threshold(p[0].pc);
@@ -949,7 +956,6 @@ int ga_allocate(gapa_ga *ga, int32_t count, const gapa_params *p, const int32_t 
     ga->objective_mcn = (p[0].flags & GAPA_MINIMISE_MCN) != 0;
     ga->objective_forest = (p[0].flags & GAPA_MAXIMISE_COMPONENTS) != 0;
     if (rc == GAPA_OK && ga->objective_mcn) rc = ga->child_mcn.reserve((size_t)slots * 4);
-    ga->by_rows = count == 1 && ga->graph->algorithm == 0 && components_fit(ga->graph);
     if (rc == GAPA_OK && !ga->by_rows) rc = ga->masks.reserve((size_t)mask_w * 4);
     if (rc == GAPA_OK && !ga->by_rows) rc = ga->alive.reserve((size_t)slots * 4);
     if (rc == GAPA_OK) rc = ga->src.reserve((size_t)fit_n * 4);
@@ -1152,7 +1158,7 @@ void ga_release(gapa_ga *ga)
     for (auto *b : {&ga->pop[0], &ga->pop[1], &ga->fit[0], &ga->fit[1], &ga->children, &ga->child_fit, &ga->child_mcn, &ga->masks,
                     &ga->alive, &ga->src, &ga->flag, &ga->gen_ctr, &ga->inst, &ga->noniso_buf,
                     &ga->tab_voff, &ga->tab_live_init, &ga->tab_live_gen, &ga->tab_moff, &ga->tab_node_inst,
-                    &ga->tab_tiles})
+                    &ga->tab_tiles, &ga->comp_init.insts, &ga->comp_init.tasks, &ga->comp_init.lists, &ga->comp_gen.insts, &ga->comp_gen.tasks})
         b->release();
     release_workspace(ga->ws);
 }
@@ -1201,7 +1207,7 @@ int gapa_ga_create(gapa_graph *g, const gapa_params *p, void *stream, gapa_ga **
         gapa_ga_destroy(ga);
         return code;
     };
-    int rc = ga_allocate(ga, 1, p, &g->n, &g->n_noniso, 0);
+    int rc = ga_allocate(ga, 1, p, &g->n, &g->n_noniso, 0, rows_fit(g));
     if (rc != GAPA_OK) return fail(rc);
     hipStream_t s = static_cast<hipStream_t>(stream);
     if ((rc = launch_fill_u32(ga->flag.ptr, 0u, 4, s)) != GAPA_OK) return fail(rc);
@@ -1433,7 +1439,7 @@ int gapa_ga_load(gapa_graph *g, const char *path, void *stream, gapa_ga **out)
         gapa_ga_destroy(ga);
         return code;
     };
-    int rc = ga_allocate(ga, 1, &h.params, &g->n, &g->n_noniso, 0);
+    int rc = ga_allocate(ga, 1, &h.params, &g->n, &g->n_noniso, 0, rows_fit(g));
     if (rc != GAPA_OK) return fail(rc);
     hipStream_t s = static_cast<hipStream_t>(stream);
     if ((rc = launch_fill_u32(ga->flag.ptr, 0u, 4, s)) != GAPA_OK) return fail(rc);
@@ -1749,6 +1755,7 @@ int gapa_batch_create(int32_t count, gapa_graph *const *graphs, const gapa_param
     std::vector<int32_t> ns(count), nonisos(count), voff(count + 1, 0);
     std::vector<int64_t> eoff(count + 1, 0);
     int32_t slots_needed = 1;
+    bool by_rows = true;  // every instance graph fits a workgroup
     for (int32_t b = 0; b < count; ++b) {
         const gapa_graph *g = graphs[b];
         if (!g || g->failed || g->device != graphs[0]->device) {
@@ -1766,6 +1773,7 @@ int gapa_batch_create(int32_t count, gapa_graph *const *graphs, const gapa_param
             return GAPA_E_INVALID_ARG;
         }
         slots_needed = std::max(slots_needed, std::max(p.pop, L));
+        by_rows = by_rows && (count == 1 ? rows_fit(g) : components_fit(g));
         ns[b] = g->n;
         nonisos[b] = g->n_noniso;
         if ((int64_t)voff[b] + g->n > (1 << 30) || eoff[b] + g->nnz >= (1ll << 31)) {
@@ -1794,6 +1802,17 @@ int gapa_batch_create(int32_t count, gapa_graph *const *graphs, const gapa_param
     if (count == 1) {
         ga->graph = graphs[0];
         graph_retain(ga->graph);
+    } else if (by_rows) {
+        bt->super = new (std::nothrow) gapa_graph();
+        if (!bt->super) {
+            set_error("host allocation failed");
+            return fail(GAPA_E_OOM);
+        }
+        bt->super->device = graphs[0]->device;
+        bt->super->n = voff[count];
+        bt->super->nnz = eoff[count];
+        ga->graph = bt->super;
+        graph_retain(ga->graph);
     } else {
         // the disjoint union of the instance graphs: instance b's node v is
         // node voff[b] + v
@@ -1820,9 +1839,12 @@ int gapa_batch_create(int32_t count, gapa_graph *const *graphs, const gapa_param
         ga->graph = bt->super;
         graph_retain(ga->graph);
     }
-    if ((rc = ga_allocate(ga, count, params, ns.data(), nonisos.data(), count > 1 ? bseg : 0)) != GAPA_OK)
+    if ((rc = ga_allocate(ga, count, params, ns.data(), nonisos.data(), count > 1 ? bseg : 0, by_rows)) != GAPA_OK)
         return fail(rc);
-    if (count > 1) {
+    if (count > 1 && by_rows) {
+        for (bool init : {true, false})
+            if ((rc = components_batch_plan(ga, graphs, init)) != GAPA_OK) return fail(rc);
+    } else if (count > 1) {
         // per-instance non-isolated bit sets, in local ids
         int64_t words = 0;
         for (int32_t b = 0; b < count; ++b) words += (ns[b] + 31) / 32;

@@ -28,17 +28,21 @@
 //
 // Bound by LDS: a sweep over all nodes reads four bytes at random for every
 // node that is open (about 8 clocks for a wave's 64, bank conflicts included)
-// and takes 8 us for n = 30k, of 37 (random graph of mean degree 8, three
+// and takes 8 us for n = 30k, of 34 (random graph of mean degree 8, three
 // sweeps) or 20 us (BA, m = 3, two) for the whole evaluation of one individual;
-// eight individuals in a byte cost a block 1.5 times one.  Whole calls against
+// eight individuals in a byte cost a block 1.4 times one.  Whole calls against
 // the bit-parallel pass: n = 200, P = 32: 13 against 53 us; BA n = 10k: P = 256
-// 18 against 78 us, P = 2048 30 against 133; random graph n = 30k: P = 203 39
+// 17 against 78 us, P = 2048 30 against 133; random graph n = 30k: P = 203 35
 // us against 2.5 ms (few individuals leave that pass a large union-find around
-// the roots), P = 2048 56 against 138 us; power law n = 65k: P = 256 50 against
-// 114 us, P = 2048 120 against 179.  Bits instead of bytes for the states: 1.5
-// times slower sweeps (ten more instructions a neighbour).  One individual a
-// block whatever the population: n = 30k, P = 2048 336 us.
+// the roots), P = 2048 46 against 138 us; power law n = 65k: P = 256 50 against
+// 114 us, P = 2048 118 against 179; 32 graphs of 1000 to 50,000 nodes, 128
+// individuals each: 98 against 200 us, bound by the largest graphs' blocks.
+// Bits instead of bytes for the states: 1.5 times slower sweeps (ten more
+// instructions a neighbour).  One individual a block whatever the population:
+// n = 30k, P = 2048 336 us.  Pushing on from hubs, too: BA n = 10k 26 instead of
+// 20 us.
 #include <algorithm>
+#include <vector>
 
 #include "device_common.h"
 #include "internal.h"
@@ -51,7 +55,7 @@ constexpr int32_t kSweepNodes = 4;     // nodes a thread has in flight in one
 constexpr int32_t kSweeps = 8;         // sweeps over the list of open nodes, at most
 constexpr int32_t kLaterChunks = 32;   // chunks of neighbours an open node reads in one
 constexpr int32_t kWaveChunks = 8;     // longer lists are united by a whole wave
-constexpr int32_t kPushLanes = 16;     // lanes that push one newly reached node
+constexpr int32_t kPushLanes = 4;      // lanes that push one newly reached node
 constexpr int32_t kPushLevels = 4;     // levels pushed after the root's neighbours, at most
 
 // Union-find parents of the open nodes: in LDS, or in global memory.
@@ -200,6 +204,14 @@ private:
     }
 };
 
+// One instance of a batch (device table).
+struct CompInst {
+    int64_t lists_off;  // first byte of its neighbour lists
+    int64_t child_off;  // of its rows in the children
+    int32_t slot_off;   // of its slots in the fitness values
+    int32_t n, chunks, n_hub, k, n1, cap, bits;
+};
+
 // LDS: the states; of the n1 nodes with an edge, the listed ones (a bit each)
 // and their number before each word [ceil(n1 / 32) each]; parents [cap] and
 // the list [cap].
@@ -222,14 +234,14 @@ struct CompSums {
     int32_t root[kGroup], removed[kGroup], outside[kGroup], big[kGroup];
     unsigned long long sum[kGroup];
     int32_t added[3], seen[3];  // of a sweep, three in turn: the next one's is cleared while unused
-    int32_t queued;
+    int32_t queued, hub;        // nodes pushed on from; whether one is a hub
     int32_t wave[16];
 };
 
 // Lists the nodes open in some individual, in rank order, as many as fit;
 // returns how many there are.  Whole block.
 template <int kBits>
-__device__ int32_t list_open(const CompLds<kBits> &l, CompSums &sm, int32_t n1, int32_t cap)
+__device__ __forceinline__ int32_t list_open(const CompLds<kBits> &l, CompSums &sm, int32_t n1, int32_t cap)
 {
     const int32_t W1 = (n1 + 31) / 32, T = blockDim.x, tid = threadIdx.x;
     const int lane = tid & 63, wv = tid >> 6;
@@ -435,7 +447,7 @@ __device__ __forceinline__ int32_t sweep_heads(const CompView &a, const CompLds<
 // Fitness of the individuals [z0, z0 + members) of a view, members <= kBits.
 // Whole block; ends with a barrier.
 template <int kBits>
-__device__ void eval_group(const CompView &a, const CompLds<kBits> &l, CompSums &sm, int32_t z0, int32_t members)
+__device__ __forceinline__ void eval_group(const CompView &a, const CompLds<kBits> &l, CompSums &sm, int32_t z0, int32_t members)
 {
     constexpr uint32_t kAll = States<kBits>::kAll;
     const int32_t n = a.g.n, n1 = a.n1;
@@ -445,7 +457,7 @@ __device__ void eval_group(const CompView &a, const CompLds<kBits> &l, CompSums 
     // members past the last count as removing every node
     l.st.clear(n, kAll & ~((1u << members) - 1u));
     if (tid < 3) sm.added[tid] = sm.seen[tid] = 0;
-    if (tid == 0) sm.queued = 0;
+    if (tid == 0) sm.queued = sm.hub = 0;
     if (tid < kGroup) {
         sm.root[tid] = n1;
         sm.removed[tid] = a.k;
@@ -484,13 +496,15 @@ __device__ void eval_group(const CompView &a, const CompLds<kBits> &l, CompSums 
         }
     }
     __syncthreads();
-    // The roots' surviving neighbours are reached, and queued; while few nodes
-    // are, their neighbours in turn (without hubs, a sweep that starts from a
-    // handful of reached nodes gets little further).
+    // The roots' surviving neighbours are reached, and queued; while they are
+    // few and no hub among them, their neighbours in turn (without hubs, a
+    // sweep that starts from a handful of reached nodes gets little further;
+    // with one, it gets most of the way, and pushing the hub's list is slow).
     auto push = [&](int32_t u, uint32_t bits) {
         const uint32_t alive = bits & ~l.st.removed(u);
         if (!alive) return;
         if (alive & ~l.st.or_reached(u, alive)) {
+            if (u < a.g.n_hub) sm.hub = 1;
             const int32_t at = atomicAdd(&sm.queued, 1);
             if (at < a.cap) l.list[at] = (uint16_t)u;
         }
@@ -519,13 +533,14 @@ __device__ void eval_group(const CompView &a, const CompLds<kBits> &l, CompSums 
             for (int e = 0; e < 4; ++e)
                 if (!((l.st.removed(u[e]) >> i) & 1u)) l.st.or_reached(u[e], 1u << i);
         }
-        if (many && lane == 0) atomicAdd(&sm.queued, T);
+        if (many && lane == 0) sm.hub = 1;
     }
     __syncthreads();
     for (int32_t level = 0, q0 = 0; level < kPushLevels; ++level) {
         const int32_t q1 = min(sm.queued, a.cap);
+        const bool hub = sm.hub;
         __syncthreads();  // everyone has read it before it grows again
-        if (q1 == q0 || q1 - q0 > T / 8) break;
+        if (q1 == q0 || q1 - q0 > T || hub) break;
         for (int32_t q = q0 + tid / kPushLanes; q < q1; q += T / kPushLanes) {
             const int32_t v = l.list[q];
             const uint32_t bits = l.st.get(v).x;
@@ -535,8 +550,10 @@ __device__ void eval_group(const CompView &a, const CompLds<kBits> &l, CompSums 
         q0 = q1;
         __syncthreads();
     }
-    // Sweeps over all nodes, while the last one reached an eighth of the open
-    // pairs, or half as many as had been reached before.
+    // Sweeps over all nodes, until a round or two of the list hold the rest,
+    // while the last one reached an eighth of the open pairs, or half as many
+    // as had been reached before.
+    const int32_t few = min(2 * T, max(T, n1 / 6));
     int32_t open = 0, found = 0;
     for (int32_t i = 0; i < members; ++i) open += n1 - sm.removed[i];
     for (int32_t s = 0; s < kFullSweeps; ++s) {
@@ -546,7 +563,7 @@ __device__ void eval_group(const CompView &a, const CompLds<kBits> &l, CompSums 
         __syncthreads();
         const int32_t now = sm.added[s % 3];
         open -= now;
-        if (open <= T || now == 0 || (now < open / 8 && now < found / 2)) break;
+        if (open <= few || now == 0 || (now < open / 8 && now < found / 2)) break;
         found += now;
     }
     // Sweeps over the list of the nodes still open (those that fit it).  A
@@ -646,6 +663,33 @@ __global__ __launch_bounds__(1024) void k_components(CompView a, int32_t P, int3
     for (int32_t z = blockIdx.x * group; z < P; z += gridDim.x * group) eval_group(a, l, sm, z, min(group, P - z));
 }
 
+// Tasks (instance, first individual, individuals, 0) of many instances, the
+// largest graphs first.  A block takes one of every gridDim.x, forwards and
+// backwards in turn, so that large tasks meet small ones.
+__global__ __launch_bounds__(1024) void k_components_batch(const CompInst *__restrict__ insts,
+                                                           const int4 *__restrict__ tasks, int32_t ntasks,
+                                                           const unsigned char *__restrict__ lists,
+                                                           const int32_t *__restrict__ children,
+                                                           int64_t *__restrict__ fitness, int32_t *__restrict__ mcn,
+                                                           int32_t forest, int32_t *__restrict__ flag,
+                                                           int32_t *__restrict__ spill, int32_t spill_stride)
+{
+    extern __shared__ __align__(16) uint8_t comp_lds[];
+    __shared__ CompSums sm;
+    const int32_t B = gridDim.x;
+    for (int32_t r = 0; r * B < ntasks; ++r) {
+        const int32_t t = r * B + ((r & 1) ? B - 1 - (int32_t)blockIdx.x : (int32_t)blockIdx.x);
+        if (t >= ntasks) continue;
+        const int4 task = tasks[t];
+        const CompInst &I = insts[task.x];
+        const CompView a{children + I.child_off, I.k, neighbour_lists(lists + I.lists_off, I.n, I.chunks, I.n_hub),
+                         I.n1, I.cap, spill + (int64_t)blockIdx.x * spill_stride, fitness + I.slot_off,
+                         mcn ? mcn + I.slot_off : nullptr, forest, flag};
+        if (I.bits == 4) eval_group(a, comp_carve<4>(comp_lds, a), sm, task.y, task.z);
+        else eval_group(a, comp_carve<8>(comp_lds, a), sm, task.y, task.z);
+    }
+}
+
 // Launch shape for P individuals: threads enough for a few rounds over the
 // nodes; a workgroup a compute unit (small ones: two or four) before a
 // workgroup takes more than one individual; four individuals a workgroup at
@@ -659,18 +703,42 @@ struct CompShape {
 constexpr size_t kCompLds = 156 * 1024;
 constexpr int32_t kWideNodes = 40000;
 
+int32_t comp_threads(int32_t n)
+{
+    return n <= 512 ? 256 : n <= 4096 ? 512 : 1024;
+}
+
+// Individuals of a workgroup, to fill `room` workgroups with P.
+int32_t comp_group(int32_t n, int64_t P, int32_t room)
+{
+    return (int32_t)std::min<int64_t>(n <= kWideNodes ? kGroup : 4, (P + room - 1) / room);
+}
+
+// LDS entries for leftover nodes (all a graph of n1 nodes with an edge can
+// have, as far as `lds` bytes go), and the LDS bytes with them.
+int32_t comp_cap(int32_t bits, int32_t n, int32_t n1, size_t lds, size_t *used)
+{
+    const size_t fixed = bits == 4 ? comp_lds_fixed<4>(n, n1) : comp_lds_fixed<8>(n, n1);
+    const int32_t cap = (int32_t)std::min<size_t>((size_t)n1 + 1, (lds - fixed) / 6);
+    *used = fixed + (size_t)cap * 6;
+    return cap;
+}
+
+int32_t comp_per_cu(int32_t threads, size_t lds)
+{
+    return (int32_t)std::min<size_t>(2048 / threads, (160 * 1024) / (lds + 1024));
+}
+
 CompShape comp_shape(const gapa_graph *g, int32_t P, size_t spill_bytes)
 {
     CompShape c{};
-    c.threads = g->n <= 512 ? 256 : g->n <= 4096 ? 512 : 1024;
-    const int32_t per_cu = 1024 / c.threads, room = 256 * per_cu;
-    c.group = std::min(g->n <= kWideNodes ? 8 : 4, (P + room - 1) / room);
+    c.threads = comp_threads(g->n);
+    const int32_t per_cu = 1024 / c.threads;
+    c.group = comp_group(g->n, P, 256 * per_cu);
     c.bits = c.group <= 4 ? 4 : 8;
-    const size_t fixed = c.bits == 4 ? comp_lds_fixed<4>(g->n, g->n_noniso) : comp_lds_fixed<8>(g->n, g->n_noniso);
-    c.cap = (int32_t)std::min<size_t>((size_t)g->n_noniso + 1, (kCompLds / per_cu - fixed) / 6);
-    c.lds = fixed + (size_t)c.cap * 6;
+    c.cap = comp_cap(c.bits, g->n, g->n_noniso, kCompLds / per_cu, &c.lds);
     const int32_t groups = (P + c.group - 1) / c.group;
-    c.blocks = std::min(groups, 256 * (int32_t)std::min<size_t>(2048 / c.threads, (160 * 1024) / (c.lds + 1024)));
+    c.blocks = std::min(groups, 256 * comp_per_cu(c.threads, c.lds));
     if (c.cap <= g->n_noniso)
         c.blocks = (int32_t)std::min<size_t>((size_t)c.blocks, spill_bytes / (((size_t)g->n_noniso + 1) * 4));
     return c;
@@ -727,6 +795,89 @@ int eval_rows_components_ws(gapa_graph *g, const int32_t *genes, int32_t P, int3
     const int rc = ws.spill.reserve(spill);
     if (rc != GAPA_OK) return rc;
     return eval_rows_components(g, genes, P, k, fitness, mcn, flag, ws.spill.ptr, spill, timer, s, measure);
+}
+
+// Instance table and tasks of a batch: `init` for the initial population, else
+// for a generation's children.
+int components_batch_plan(gapa_ga *ga, gapa_graph *const *graphs, bool init)
+{
+    CompBatch &cb = init ? ga->comp_init : ga->comp_gen;
+    const int32_t count = ga->count;
+    int32_t n_max = 0;
+    int64_t total = 0;
+    for (const GaInst &I : ga->hinst) {
+        n_max = std::max(n_max, I.n);
+        total += init ? I.P : I.L;
+    }
+    cb.threads = comp_threads(n_max);
+    const int32_t per_cu = 1024 / cb.threads;
+    std::vector<CompInst> insts((size_t)count);
+    std::vector<int4> tasks;
+    std::vector<int32_t> by_size((size_t)count);
+    for (int32_t b = 0; b < count; ++b) by_size[b] = b;
+    std::sort(by_size.begin(), by_size.end(), [&](int32_t x, int32_t y) {
+        return ga->hinst[x].n != ga->hinst[y].n ? ga->hinst[x].n > ga->hinst[y].n : x < y;
+    });
+    cb.lds = 0;
+    cb.spill_stride = 0;
+    int64_t lists_bytes = 0;
+    for (int32_t b = 0; b < count; ++b) {
+        insts[b].lists_off = lists_bytes;
+        lists_bytes += (int64_t)((neighbour_lists_bytes(graphs[b]->n, graphs[b]->list_chunks) + 255) & ~(size_t)255);
+    }
+    for (int32_t b : by_size) {
+        const GaInst &I = ga->hinst[b];
+        CompInst &c = insts[b];
+        const int32_t group = comp_group(I.n, total, 256 * per_cu), live = init ? I.P : I.L;
+        c.n = I.n;
+        c.chunks = graphs[b]->list_chunks;
+        c.n_hub = graphs[b]->n_hub;
+        c.k = I.k;
+        c.n1 = I.n_noniso;
+        c.bits = group <= 4 ? 4 : 8;
+        size_t used = 0;
+        c.cap = comp_cap(c.bits, I.n, c.n1, kCompLds / per_cu, &used);
+        c.child_off = I.child_off;
+        c.slot_off = I.slot_off;
+        cb.lds = std::max(cb.lds, used);
+        if (c.cap <= c.n1) cb.spill_stride = std::max(cb.spill_stride, c.n1 + 1);
+        for (int32_t z = 0; z < live; z += group) tasks.push_back(make_int4(b, z, std::min(group, live - z), 0));
+    }
+    cb.ntasks = (int32_t)tasks.size();
+    cb.blocks = std::min(cb.ntasks, 256 * comp_per_cu(cb.threads, cb.lds));
+    int rc;
+    if ((rc = cb.insts.reserve(insts.size() * sizeof(CompInst))) != GAPA_OK) return rc;
+    if ((rc = cb.tasks.reserve(tasks.size() * sizeof(int4))) != GAPA_OK) return rc;
+    if ((rc = ga->ws.spill.reserve((size_t)cb.blocks * cb.spill_stride * 4)) != GAPA_OK) return rc;
+    DevBuf &lists = ga->comp_init.lists;
+    if (!lists.ptr) {
+        if ((rc = lists.reserve((size_t)lists_bytes)) != GAPA_OK) return rc;
+        for (int32_t b = 0; b < count; ++b)
+            GAPA_HIP(hipMemcpyAsync(lists.as<unsigned char>() + insts[b].lists_off, graphs[b]->d_lists,
+                                    neighbour_lists_bytes(graphs[b]->n, graphs[b]->list_chunks),
+                                    hipMemcpyDeviceToDevice, nullptr));
+        GAPA_HIP(hipStreamSynchronize(nullptr));
+    }
+    GAPA_HIP(hipMemcpy(cb.insts.ptr, insts.data(), insts.size() * sizeof(CompInst), hipMemcpyHostToDevice));
+    GAPA_HIP(hipMemcpy(cb.tasks.ptr, tasks.data(), tasks.size() * sizeof(int4), hipMemcpyHostToDevice));
+    return GAPA_OK;
+}
+
+int eval_rows_components_batch(gapa_ga *ga, bool init, int32_t *mcn, hipStream_t s, Measure measure)
+{
+    const CompBatch &cb = init ? ga->comp_init : ga->comp_gen;
+    if (cb.lds > 60 * 1024)
+        GAPA_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(k_components_batch),
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)kCompLds));
+    TimedScope pass(&ga->timer, "fitness_pass", s, 1);
+    TimedScope ts(&ga->timer, "k_components", s);
+    hipLaunchKernelGGL(k_components_batch, dim3((unsigned)cb.blocks), dim3(cb.threads), cb.lds, s,
+                       cb.insts.as<CompInst>(), cb.tasks.as<int4>(), cb.ntasks,
+                       ga->comp_init.lists.as<unsigned char>(), ga->children.as<int32_t>(),
+                       ga->child_fit.as<int64_t>(), mcn, (int32_t)measure, ga->flag.as<int32_t>() + 3,
+                       ga->ws.spill.as<int32_t>(), cb.spill_stride);
+    GAPA_HIP(hipGetLastError());
+    return GAPA_OK;
 }
 
 }  // namespace gapa

@@ -763,7 +763,9 @@ int ga_eval_children(gapa_ga *ga, bool init, hipStream_t s)
     int32_t *mcn = ga->objective_mcn ? ga->child_mcn.as<int32_t>() : nullptr;
     const Measure measure = ga->objective_forest ? kMeasureForest : kMeasurePC;
     int rc;
-    if (ga->by_rows)
+    if (ga->by_rows && ga->count > 1)
+        rc = eval_rows_components_batch(ga, init, mcn, s, measure);
+    else if (ga->by_rows)
         rc = eval_rows_components_ws(ga->graph, ga->children.as<int32_t>(), init ? ga->params.pop : ga->lambda,
                                      ga->params.k, ga->child_fit.as<int64_t>(), mcn, ga->flag.as<int32_t>() + 3,
                                      ga->ws, &ga->timer, s, measure);

@@ -157,7 +157,6 @@ struct gapa_graph {
     // [n + 1] first chunk of each node, the uint16 [n] new number of each node
     unsigned char *d_lists = nullptr;
     int32_t list_chunks = 0;
-    int32_t n_long = 0;         // nodes of more than four neighbours
     int32_t n_hub = 0;          // nodes of more than kHubDegree neighbours
     int32_t algorithm = 0;      // 0: bit-parallel sweeps, 1: edge-parallel union-find
     gapa::Tuning tune;
@@ -252,18 +251,30 @@ struct NeighbourLists {
     const uint2 *ids;      // [off[n]]
     const uint2 *head;     // [n]
     int32_t n;
-    int32_t n_long;        // nodes of more than one chunk: the first n_long
+    int32_t n_hub;         // nodes of more than kHubDegree neighbours: the first n_hub
 };
 constexpr int32_t kListsMaxN = 65535;
+constexpr int32_t kHubDegree = 24;
+
+// The lists laid out from `base` on (in the order of gapa_graph::d_lists).
+__host__ __device__ inline NeighbourLists neighbour_lists(const unsigned char *base, int32_t n, int32_t chunks,
+                                                          int32_t n_hub)
+{
+    const size_t ids_at = (size_t)n * 8, off_at = ids_at + (size_t)chunks * 8, rank_at = off_at + ((size_t)n + 1) * 4;
+    return NeighbourLists{reinterpret_cast<const uint16_t *>(base + rank_at),
+                          reinterpret_cast<const int32_t *>(base + off_at),
+                          reinterpret_cast<const uint2 *>(base + ids_at), reinterpret_cast<const uint2 *>(base), n,
+                          n_hub};
+}
+
+inline size_t neighbour_lists_bytes(int32_t n, int32_t chunks)
+{
+    return (size_t)n * 8 + (size_t)chunks * 8 + ((size_t)n + 1) * 4 + (size_t)n * 2;
+}
 
 inline NeighbourLists neighbour_lists(const gapa_graph *g)
 {
-    const size_t ids_at = (size_t)g->n * 8, off_at = ids_at + (size_t)g->list_chunks * 8;
-    const size_t rank_at = off_at + ((size_t)g->n + 1) * 4;
-    return NeighbourLists{reinterpret_cast<const uint16_t *>(g->d_lists + rank_at),
-                          reinterpret_cast<const int32_t *>(g->d_lists + off_at),
-                          reinterpret_cast<const uint2 *>(g->d_lists + ids_at),
-                          reinterpret_cast<const uint2 *>(g->d_lists), g->n, g->n_long};
+    return neighbour_lists(g->d_lists, g->n, g->list_chunks, g->n_hub);
 }
 
 // Fitness of P gene rows (device, [P][k]) by one workgroup each
@@ -279,9 +290,17 @@ int eval_rows_components(gapa_graph *g, const int32_t *genes, int32_t P, int32_t
 int eval_rows_components_ws(gapa_graph *g, const int32_t *genes, int32_t P, int32_t k, int64_t *fitness, int32_t *mcn,
                             int32_t *flag, FitnessWorkspace &ws, KernelTimer *timer, hipStream_t s, Measure measure);
 
-// Dense reachability fitness (sixdst.hip).  kHubDegree: nodes above it are
-// pulled by several lanes each.
-constexpr int32_t kHubDegree = 24;
+// The same for the instances of a batch, in one launch (plans made at creation,
+// one for the initial population and one for a generation's children).
+struct CompBatch {
+    DevBuf insts, tasks, lists;  // (lists: of the graphs, once for both plans)
+    int32_t ntasks = 0, threads = 0, blocks = 0, spill_stride = 0;
+    size_t lds = 0;
+};
+int components_batch_plan(gapa_ga *ga, gapa_graph *const *graphs, bool init);
+int eval_rows_components_batch(gapa_ga *ga, bool init, int32_t *mcn, hipStream_t s, Measure measure);
+
+// Dense reachability fitness (sixdst.hip).
 bool sixdst_sparse(const gapa_graph *g, int32_t hops);
 int sixdst_eval_genes(gapa_graph *g, const int32_t *genes, int32_t P, int32_t k, int32_t hops, int64_t *pc,
                       int32_t *mcn, int32_t *flag, hipStream_t s);
@@ -383,7 +402,8 @@ struct gapa_ga {
     int32_t slots = 0;
     bool objective_mcn = false;
     bool objective_forest = false;  // GAPA_MAXIMISE_COMPONENTS: fitness = |V minus S| - components
-    bool by_rows = false;         // fitness by eval_rows_components: no bit sets are made
+    bool by_rows = false;         // fitness by eval_rows_components(_batch): no bit sets are made
+    gapa::CompBatch comp_init, comp_gen;  // a batch evaluated that way
     gapa::DevBuf masks;           // uint32 removed-node bit sets of the children
     gapa::DevBuf alive;           // int32 slots: surviving non-isolated nodes
     gapa::DevBuf src;             // int32 [sum P] elitism: source tag of each kept row
@@ -416,5 +436,8 @@ struct gapa_ga {
 
 struct gapa_batch {
     gapa_ga *ga = nullptr;
-    gapa_graph *super = nullptr;  // owned
+    // owned: the disjoint union of the instance graphs, or, where workgroups
+    // evaluate the individuals on the graphs' neighbour lists, only its device,
+    // sizes and tuning
+    gapa_graph *super = nullptr;
 };

@@ -330,7 +330,7 @@ constexpr unsigned long long kTaskDone = 1ull << kSumBits;
 
 template <int NW, bool kLdsGraph>
 __global__ __launch_bounds__(1024) void k_six_reach(const int32_t *__restrict__ genes, int32_t k, const NeighbourLists g,
-                                                    int32_t n_hub, int32_t hops, int32_t nsb, int64_t tasks,
+                                                    int32_t hops, int32_t nsb, int64_t tasks,
                                                     unsigned long long *__restrict__ pc, int32_t *__restrict__ mcn,
                                                     int32_t *__restrict__ flag)
 {
@@ -404,7 +404,7 @@ __global__ __launch_bounds__(1024) void k_six_reach(const int32_t *__restrict__ 
 
         for (int32_t h = 2; h <= hops; ++h) {
             bool changed = false;
-            for (int32_t v = tid / kHubLanes; v < n_hub; v += T / kHubLanes) {
+            for (int32_t v = tid / kHubLanes; v < g.n_hub; v += T / kHubLanes) {
                 Bits<NW> acc = ld_bits<NW>(cur + v * NW);
                 const Bits<NW> mine = acc;
                 if (!removed(dead, v) && !covers<NW>(mine, full)) {
@@ -417,7 +417,7 @@ __global__ __launch_bounds__(1024) void k_six_reach(const int32_t *__restrict__ 
                 }
                 if (sub == 0) st_bits<NW>(nxt + v * NW, acc);
             }
-            for (int32_t v = n_hub + tid; v < n; v += T) {
+            for (int32_t v = g.n_hub + tid; v < n; v += T) {
                 Bits<NW> acc = ld_bits<NW>(cur + v * NW);
                 const Bits<NW> mine = acc;
                 if (!removed(dead, v) && !covers<NW>(mine, full)) {
@@ -517,7 +517,7 @@ int launch_reach(const ReachShape &r, int32_t blocks, const int32_t *genes, int3
         GAPA_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(k_six_reach<NW, kLdsGraph>),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)kReachLds));
     hipLaunchKernelGGL((k_six_reach<NW, kLdsGraph>), dim3((unsigned)blocks), dim3(r.threads), r.lds, s, genes, k,
-                       neighbour_lists(g), g->n_hub, hops, nsb, tasks, reinterpret_cast<unsigned long long *>(pc), mcn, flag);
+                       neighbour_lists(g), hops, nsb, tasks, reinterpret_cast<unsigned long long *>(pc), mcn, flag);
     GAPA_HIP(hipGetLastError());
     return GAPA_OK;
 }

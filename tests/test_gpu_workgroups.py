@@ -102,3 +102,26 @@ def test_noalloc_and_ga_take_the_same_way(gp):
         ref.step()
     pop, F = ga.population()
     assert np.array_equal(pop, ref.pop) and np.array_equal(F, ref.F)
+
+
+@pytest.mark.parametrize("kinds", [
+    [("tree", 30000, 40), ("ba", 400, 100), ("2.0", 41000, 33), ("empty", 5, 7), ("3.0", 3000, 128)],
+    [("ba", 300, 9), ("star", 500, 70)],
+    [("4.0", 65536, 20), ("ba", 900, 50)]])  # one graph too large: the bit-parallel pass takes the batch
+def test_batches_follow_single_gas(gp, kinds):
+    graphs = [graph_of(kind, n) for kind, n, _ in kinds]
+    params = [dict(k=max(1, g.n // 60), pop=P, seed=5 + b, offspring=P + 10 * b)
+              for b, (g, (_, _, P)) in enumerate(zip(graphs, kinds))]
+    handles = [gp.Graph.from_csr(g) for g in graphs]
+    print(kinds, flush=True)
+    bt = gp.Batch(handles, params)
+    gas = [gp.GA(h, **p) for h, p in zip(handles, params)]
+    for h in handles:
+        h.close()  # the batch and the GAs keep what they need
+    bt.step(5)
+    for b, ga in enumerate(gas):
+        ga.step(5)
+        (rows, F), (rows1, F1) = bt.population(b), ga.population()
+        assert np.array_equal(F, F1) and np.array_equal(rows, rows1), b
+        Fo = O.eval_population(graphs[b], rows[:4])
+        assert np.array_equal(F[:4], Fo), b
