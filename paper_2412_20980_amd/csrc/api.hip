@@ -958,7 +958,6 @@ int ga_allocate(gapa_ga *ga, int32_t count, const gapa_params *p, const int32_t 
     if (rc == GAPA_OK && ga->objective_mcn) rc = ga->child_mcn.reserve((size_t)slots * 4);
     if (rc == GAPA_OK && !ga->by_rows) rc = ga->masks.reserve((size_t)mask_w * 4);
     if (rc == GAPA_OK && !ga->by_rows) rc = ga->alive.reserve((size_t)slots * 4);
-    if (rc == GAPA_OK) rc = ga->src.reserve((size_t)fit_n * 4);
     if (rc == GAPA_OK) rc = ga->flag.reserve(16);
     if (rc == GAPA_OK) rc = ga->gen_ctr.reserve(16);
     if (rc == GAPA_OK) rc = ga->inst.reserve(sizeof(GaInst) * count);
@@ -1156,7 +1155,7 @@ void ga_release(gapa_ga *ga)
     if (ga->cap_stream) (void)hipStreamDestroy(ga->cap_stream);
     ga->cap_stream = nullptr;
     for (auto *b : {&ga->pop[0], &ga->pop[1], &ga->fit[0], &ga->fit[1], &ga->children, &ga->child_fit, &ga->child_mcn, &ga->masks,
-                    &ga->alive, &ga->src, &ga->flag, &ga->gen_ctr, &ga->inst, &ga->noniso_buf,
+                    &ga->alive, &ga->flag, &ga->gen_ctr, &ga->inst, &ga->noniso_buf,
                     &ga->tab_voff, &ga->tab_live_init, &ga->tab_live_gen, &ga->tab_moff, &ga->tab_node_inst,
                     &ga->tab_tiles, &ga->comp_init.insts, &ga->comp_init.tasks, &ga->comp_init.lists, &ga->comp_gen.insts, &ga->comp_gen.tasks})
         b->release();

@@ -550,12 +550,12 @@ __global__ void k_mcn_objective(const int32_t *__restrict__ mcn, int64_t *__rest
 // A block takes kRankKeys keys.  Each of its waves holds a 64-entry slice of
 // the pool, one entry per lane, and compares it with one key at a time: a
 // ballot and a bit count give the slice's entries below the key.  The waves'
-// counts meet in LDS, and the block places its keys in the same launch.  At
-// P = lambda = 1024 elitism (ranks and the row gather) takes 13.9 us per
-// generation with 8 keys a block, against 15.1 with 16 and 20.0 with 64
-// (the keys' loop is a chain of LDS reads; more blocks share it), and 22 us
-// for a tile-by-tile count into atomic counters plus a second launch placing
-// the keys.
+// counts meet in LDS, and the block places its keys and copies their rows in
+// the same launch, kRowLanes threads a row.  At P = lambda = 1024, k = 2000 the
+// ranks take 5.7 us with 8 keys a block (6.9 with 16, 11.8 with 64: the keys'
+// loop is a chain of LDS reads; more blocks share it); the row copies in a
+// launch of their own took 5.2 us more, and at n = 200 (P = 32, k = 10) 3.9 us
+// after 4.6.
 // Slower: counting the parents by ballot too, and the comparison loop
 // written without branches, eight keys a batch.
 struct RankArgs {
@@ -565,8 +565,11 @@ struct RankArgs {
     const int32_t *pool;    // NULL, or [npool] offspring of each pooled entry (one instance)
     int32_t npool;          // with pool
     int32_t init;           // generation 0: no parents
-    int32_t *src;           // [P] source tag of each kept row (instance base fit_off)
     int64_t *f_out;         // next fitness (instance base fit_off)
+    const int32_t *parents;   // rows of the current population (instance base pop_off)
+    const int32_t *children;  // rows of the offspring (instance base child_off)
+    int32_t *rows_out;        // rows of the next population (instance base pop_off)
+    uint32_t *gen_ctr;        // [1] advanced after generation 0
 };
 
 struct RankView {
@@ -587,15 +590,19 @@ __device__ __forceinline__ RankView rank_view(const RankArgs &a, int32_t b)
 
 constexpr int kRankKeys = 8;    // keys per block
 constexpr int kRankWaves = 16;  // waves per block
+constexpr int kRowLanes = 64 * kRankWaves / kRankKeys;
 
-__global__ __launch_bounds__(64 * kRankWaves) void k_rank_place(RankArgs a)
+__global__ __launch_bounds__(64 * kRankWaves) void k_rank_rows(RankArgs a)
 {
     __shared__ int64_t kf[kRankKeys];
     __shared__ int32_t kt[kRankKeys], kc[kRankKeys];
+    __shared__ int32_t s_to[kRankKeys], s_tag[kRankKeys];  // position (or P and beyond: dropped) and source of each key
     const GaInst &I = a.inst[blockIdx.y];
     const RankView r = rank_view(a, blockIdx.y);
     const int32_t total = r.npar + r.npool;
     const int32_t k0 = blockIdx.x * kRankKeys;
+    // (every reader of the counter in this generation has finished: stream order)
+    if (!a.init && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) a.gen_ctr[0] += 1u;
     if (k0 >= total) return;  // uniform over the block
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     if (threadIdx.x < kRankKeys) {
@@ -627,47 +634,42 @@ __global__ __launch_bounds__(64 * kRankWaves) void k_rank_place(RankArgs a)
     }
     if (mine) atomicAdd(&kc[lane], mine);
     __syncthreads();
-    const int32_t t = k0 + threadIdx.x;
-    if (threadIdx.x >= kRankKeys || t >= total) return;
-    const int64_t f = kf[threadIdx.x];
-    int32_t p = kc[threadIdx.x], tag;
-    if (t < r.npar) {
-        p += t;
-        tag = t;
-    } else {
-        int32_t lo = 0, hi = r.npar;
-        while (lo < hi) {
-            const int32_t mid = (lo + hi) >> 1;
-            if (r.f_par[mid] <= f) lo = mid + 1;
-            else hi = mid;
+    if (threadIdx.x < kRankKeys) {
+        const int32_t t = k0 + threadIdx.x;
+        int32_t p = INT_MAX, tag = 0;
+        if (t < total) {
+            const int64_t f = kf[threadIdx.x];
+            p = kc[threadIdx.x];
+            if (t < r.npar) {
+                p += t;
+                tag = t;
+            } else {
+                int32_t lo = 0, hi = r.npar;
+                while (lo < hi) {
+                    const int32_t mid = (lo + hi) >> 1;
+                    if (r.f_par[mid] <= f) lo = mid + 1;
+                    else hi = mid;
+                }
+                p += lo;
+                tag = r.npar + kt[threadIdx.x];
+            }
+            if (p < I.P) a.f_out[I.fit_off + p] = f;
         }
-        p += lo;
-        tag = r.npar + kt[threadIdx.x];
+        s_to[threadIdx.x] = p;
+        s_tag[threadIdx.x] = tag;
     }
-    if (p < I.P) {
-        a.src[I.fit_off + p] = tag;
-        a.f_out[I.fit_off + p] = f;
+    __syncthreads();
+    const int32_t q = threadIdx.x / kRowLanes, p = s_to[q], tag = s_tag[q], k = I.k;
+    if (p >= I.P) return;
+    const int32_t *s = tag < r.npar ? a.parents + I.pop_off + (int64_t)tag * k
+                                    : a.children + I.child_off + (int64_t)(tag - r.npar) * k;
+    int32_t *d = a.rows_out + I.pop_off + (int64_t)p * k;
+    if (((reinterpret_cast<uintptr_t>(s) | reinterpret_cast<uintptr_t>(d) | (uintptr_t)k * 4) & 15) == 0) {
+        for (int32_t j = threadIdx.x % kRowLanes; j < k / 4; j += kRowLanes)
+            reinterpret_cast<int4 *>(d)[j] = reinterpret_cast<const int4 *>(s)[j];
+    } else {
+        for (int32_t j = threadIdx.x % kRowLanes; j < k; j += kRowLanes) d[j] = s[j];
     }
-}
-
-// Row r of the next population from its source tag; after generation 0 the
-// first block also advances the device generation counter (every reader of
-// it in this generation has finished: stream order).
-__global__ void k_gather_rows(const GaInst *__restrict__ inst, const int32_t *__restrict__ src, int32_t init,
-                              const int32_t *__restrict__ parents, const int32_t *__restrict__ children,
-                              int32_t *__restrict__ out, uint32_t *__restrict__ gen_ctr)
-{
-    const GaInst &I = inst[blockIdx.y];
-    const int32_t r = blockIdx.x;
-    if (!init && r == 0 && blockIdx.y == 0 && threadIdx.x == 0) gen_ctr[0] += 1u;
-    if (r >= I.P) return;
-    const int32_t npar = init ? 0 : I.P;
-    const int32_t tag = src[I.fit_off + r];
-    const int32_t k = I.k;
-    const int32_t *s = tag < npar ? parents + I.pop_off + (int64_t)tag * k
-                                  : children + I.child_off + (int64_t)(tag - npar) * k;
-    int32_t *d = out + I.pop_off + (int64_t)r * k;
-    for (int32_t j = threadIdx.x; j < k; j += blockDim.x) d[j] = s[j];
 }
 
 OpArgs make_args(gapa_ga *ga, const int32_t *pop, const int64_t *fit)
@@ -700,22 +702,16 @@ int ga_rank_and_gather(gapa_ga *ga, bool init, const int64_t *f_pool, const int3
     a.pool = pool;
     a.npool = npool;
     a.init = init ? 1 : 0;
-    a.src = ga->src.as<int32_t>();
     a.f_out = ga->fit[nxt].as<int64_t>();
+    a.parents = ga->pop[ga->cur].as<int32_t>();
+    a.children = ga->children.as<int32_t>();
+    a.rows_out = ga->pop[nxt].as<int32_t>();
+    a.gen_ctr = ga->gen_ctr.as<uint32_t>();
     // launch extents: the largest instance
     const int32_t max_total = init ? ga->max_pop : (pool ? ga->max_pop + npool : ga->max_pop_lambda);
     TimedScope pass(&ga->timer, "elitism", s, 1);
-    {
-        TimedScope ts(&ga->timer, "elitism_rank", s);
-        hipLaunchKernelGGL(k_rank_place, dim3((max_total + kRankKeys - 1) / kRankKeys, count), dim3(64 * kRankWaves),
-                           0, s, a);
-    }
-    {
-        TimedScope ts(&ga->timer, "gather_rows", s);
-        hipLaunchKernelGGL(k_gather_rows, dim3(ga->max_pop, count), dim3(256), 0, s, ga->inst.as<GaInst>(),
-                           ga->src.as<int32_t>(), a.init, ga->pop[ga->cur].as<int32_t>(), ga->children.as<int32_t>(),
-                           ga->pop[nxt].as<int32_t>(), ga->gen_ctr.as<uint32_t>());
-    }
+    hipLaunchKernelGGL(k_rank_rows, dim3((max_total + kRankKeys - 1) / kRankKeys, count), dim3(64 * kRankWaves), 0, s,
+                       a);
     GAPA_HIP(hipGetLastError());
     ga->cur = nxt;
     return GAPA_OK;

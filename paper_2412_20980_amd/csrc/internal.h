@@ -327,7 +327,7 @@ struct GaInst {
     int64_t pop_off;    // first element of its rows in pop[*] (row stride k)
     int64_t child_off;  // first element of its rows in children (row stride k)
     int64_t mask_off;   // first word of its child masks (row stride W)
-    int32_t fit_off;    // first entry in fit[*] and src
+    int32_t fit_off;    // first entry in fit[*]
     int32_t slot_off;   // first entry in child_fit and alive
     int32_t noniso_off; // first word of its non-isolated node bit set
     uint64_t seed, t_pc, t_pm;
@@ -406,7 +406,6 @@ struct gapa_ga {
     gapa::CompBatch comp_init, comp_gen;  // a batch evaluated that way
     gapa::DevBuf masks;           // uint32 removed-node bit sets of the children
     gapa::DevBuf alive;           // int32 slots: surviving non-isolated nodes
-    gapa::DevBuf src;             // int32 [sum P] elitism: source tag of each kept row
     gapa::DevBuf flag;            // int32 [4] device error flags
     gapa::DevBuf gen_ctr;         // uint32 [1] generations completed (read by the operator kernel)
     uint32_t *noniso = nullptr;   // batch: per-instance non-isolated bit sets (else the graph's)
