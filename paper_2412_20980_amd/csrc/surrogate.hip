@@ -460,8 +460,9 @@ struct AdamArgs {
 
 __device__ __forceinline__ float adam(float &theta, float &m, float &v, float g, const AdamArgs &o)
 {
-    m = o.b1 * m + (1.f - o.b1) * g;
-    v = o.b2 * v + (1.f - o.b2) * g * g;
+    // (the fused operations written out, so that every kernel rounds alike)
+    m = __builtin_fmaf(1.f - o.b1, g, o.b1 * m);
+    v = __builtin_fmaf((1.f - o.b2) * g, g, o.b2 * v);
     theta -= o.lr * (m / o.c1) / (sqrtf(v / o.c2) + o.eps);
     return theta;
 }
@@ -579,15 +580,24 @@ __global__ __launch_bounds__(64) void k_mlp_wgrad(WgradArgs a)
 
 // Embeddings.  dE = M^T dx, M the batch's sample x node membership matrix:
 // for the hub nodes that sit in most sets of a converged population this is
-// a dense contraction over the batch, so it runs on the matrix cores.  The B
-// operand (dx of the whole batch, bf16, dimension-major) is staged once per
-// block in LDS, rows padded by 8 elements so that the 16 rows a k-step reads
-// fall in different banks; each wave then walks tiles of 16 nodes: the A
-// operand is the tile's membership bits (node-major rows, one 32-bit word
-// per 32 samples) expanded to bf16 0/1, K = the batch; k-steps whose word is
+// a dense contraction over the batch, so it runs on the matrix cores.  dx of
+// the whole batch (bf16, dimension-major) is staged once per block in LDS, rows
+// padded by 8 elements so that the 16 rows a k-step reads fall in different
+// banks; each wave then walks tiles of 16 nodes, K = the batch: one operand is
+// 16 dimensions of dx, the other the tile's membership bits (node-major rows,
+// one 32-bit word per 32 samples) expanded to bf16 0/1; k-steps whose word is
 // zero for the whole tile are skipped.  Adam is lazy on E: a node in some
 // sample steps with the global step count, straight from the accumulators;
 // the others keep weights and moments.
+//
+// Bound by memory: weights, both moments and the bf16 copy of nearly every row
+// read and written, 377 MB a step at n = 200k.  The nodes are the columns of
+// the product, so a lane holds four dimensions in a row of one node and moves
+// them 16 bytes at a time, and a tile's weights and moments are loaded before
+// its contraction.  n = 200k: 103 us a launch, of which the contraction alone
+// takes 55 and the memory traffic at a copy's rate 74; n = 20,011: 24 us.  (With
+// the nodes as rows, 4 bytes at a time and loaded after the contraction: 117 and
+// 33.)
 __global__ __launch_bounds__(1024) void k_grad_adam_E(const uint32_t *__restrict__ bits, int32_t Wb,
                                                      const uint16_t *__restrict__ dxT, int32_t B,
                                                      float *__restrict__ E, float *__restrict__ m,
@@ -604,78 +614,81 @@ __global__ __launch_bounds__(1024) void k_grad_adam_E(const uint32_t *__restrict
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, nw = blockDim.x >> 6;
     const int lr = lane & 15, lg = lane >> 4;
     const int64_t tiles = (n + 15) / 16;
-    for (int64_t tile = (int64_t)blockIdx.x * nw + wv; tile < tiles; tile += (int64_t)gridDim.x * nw) {
-        const int64_t v0 = tile * 16;
-        const int64_t row = v0 + lr;
-        // every lane (lr, lg) holds all Wb <= 32 words of node v0 + lr's row
-        // (the four lanes of a node read the same 128 bytes), so a k-step
-        // needs no exchange between lanes
-        uint32_t w32[32];
+    const f32x4 zero = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int64_t tile = (int64_t)wv * gridDim.x + blockIdx.x; tile < tiles; tile += (int64_t)gridDim.x * nw) {
+        const int64_t node = tile * 16 + lr;  // this lane's node
+        // byte lg of every word of the node's row (1, 2 or a multiple of 4
+        // words, at most 32), four to a register: the samples this lane's
+        // operands hold
+        uint32_t by[8], rowany = 0u;
+        uint4 row[8];
 #pragma unroll
-        for (int ks = 0; ks < 32; ++ks) w32[ks] = (row < n && ks < Wb) ? bits[row * Wb + ks] : 0u;
-        uint32_t rowany = 0u;
-#pragma unroll
-        for (int ks = 0; ks < 32; ++ks) rowany |= w32[ks];
-        if (__ballot(rowany != 0u) == 0) {
-            if (keep)
-                for (int q = lane; q < 16 * kD; q += 64)
-                    if (v0 + q / kD < n) keep[v0 * kD + q] = 0.f;
-            continue;
+        for (int q = 0; q < 8; ++q) {
+            row[q] = uint4{0u, 0u, 0u, 0u};
+            if (node < n) {
+                if (4 * q + 3 < Wb) row[q] = *reinterpret_cast<const uint4 *>(bits + node * Wb + 4 * q);
+                else if (q == 0) row[q] = uint4{bits[node * Wb], Wb > 1 ? bits[node * Wb + 1] : 0u, 0u, 0u};
+            }
         }
-        f32x4 acc[4];
 #pragma unroll
-        for (int t = 0; t < 4; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int ks = 0; ks < 32; ++ks) {
-            const uint32_t word = w32[ks];
-            if (__ballot(word != 0u) == 0) continue;
-            const uint32_t byte = (word >> (8 * lg)) & 0xFFu;
-            uint4 q;
-            q.x = ((byte & 1u) ? 0x3F80u : 0u) | ((byte & 2u) ? 0x3F800000u : 0u);
-            q.y = ((byte & 4u) ? 0x3F80u : 0u) | ((byte & 8u) ? 0x3F800000u : 0u);
-            q.z = ((byte & 16u) ? 0x3F80u : 0u) | ((byte & 32u) ? 0x3F800000u : 0u);
-            q.w = ((byte & 64u) ? 0x3F80u : 0u) | ((byte & 128u) ? 0x3F800000u : 0u);
-            const bf16x8 A = __builtin_bit_cast(bf16x8, q);
-#pragma unroll
-            for (int t = 0; t < 4; ++t) acc[t] = mfma(A, ld8(sB + (t * 16 + lr) * SB + ks * 32 + lg * 8), acc[t]);
+        for (int q = 0; q < 8; ++q) {
+            rowany |= row[q].x | row[q].y | row[q].z | row[q].w;
+            by[q] = ((row[q].x >> (8 * lg)) & 0xFFu) | (((row[q].y >> (8 * lg)) & 0xFFu) << 8) |
+                    (((row[q].z >> (8 * lg)) & 0xFFu) << 16) | ((row[q].w >> (8 * lg)) << 24);
         }
-        // lane (lr, lg) holds dE[v0 + 4 lg + r][16 t + lr]; node v0 + i's
-        // membership flag sits in lane i.  The weights and moments of all
-        // sixteen entries are loaded before any is updated, so the loads are
-        // in flight together.
-        bool tch[4];
-        float th[4][4], mm[4][4], vv[4][4];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int64_t node = v0 + 4 * lg + r;
-            const bool touched = __shfl((int)rowany, 4 * lg + r, 64) != 0;
-            tch[r] = touched && node < n;
+        const bool touched = rowany != 0u;  // (false past the last node)
+        const int64_t base = node * kD + 4 * lg;
+        if (__ballot(touched) == 0) {
             if (keep && node < n)
 #pragma unroll
-                for (int t = 0; t < 4; ++t) keep[node * kD + t * 16 + lr] = touched ? acc[t][r] : 0.f;
+                for (int t = 0; t < 4; ++t) *reinterpret_cast<f32x4 *>(keep + base + 16 * t) = zero;
+            continue;
+        }
+        // weights and moments of dimensions 16 t + 4 lg .. + 3
+        f32x4 th[4], mm[4], vv[4], acc[4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            th[t] = touched ? *reinterpret_cast<const f32x4 *>(E + base + 16 * t) : zero;
+            mm[t] = touched ? *reinterpret_cast<const f32x4 *>(m + base + 16 * t) : zero;
+            vv[t] = touched ? *reinterpret_cast<const f32x4 *>(v + base + 16 * t) : zero;
+            acc[t] = zero;
         }
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int64_t base = (v0 + 4 * lg + r) * kD + lr;
+        for (int ks = 0; ks < 32; ++ks) {
+            const uint32_t byte = (by[ks >> 2] >> (8 * (ks & 3))) & 0xFFu;
+            if (__ballot(byte != 0u) == 0) continue;
+            // bits 2 q and 2 q + 1 to the two halves of a word, times bf16 1.0
+            const uint32_t pair = byte | (byte << 15);
+            uint4 q;
+            q.x = __umul24(pair & 0x10001u, 0x3F80u);
+            q.y = __umul24((pair >> 2) & 0x10001u, 0x3F80u);
+            q.z = __umul24((pair >> 4) & 0x10001u, 0x3F80u);
+            q.w = __umul24((pair >> 6) & 0x10001u, 0x3F80u);
+            const bf16x8 M = __builtin_bit_cast(bf16x8, q);
 #pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                th[r][t] = tch[r] ? E[base + t * 16] : 0.f;
-                mm[r][t] = tch[r] ? m[base + t * 16] : 0.f;
-                vv[r][t] = tch[r] ? v[base + t * 16] : 0.f;
-            }
+            for (int t = 0; t < 4; ++t) acc[t] = mfma(ld8(sB + (t * 16 + lr) * SB + ks * 32 + lg * 8), M, acc[t]);
         }
+        if (keep && node < n)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            if (!tch[r]) continue;
-            const int64_t base = (v0 + 4 * lg + r) * kD + lr;
+            for (int t = 0; t < 4; ++t) *reinterpret_cast<f32x4 *>(keep + base + 16 * t) = touched ? acc[t] : zero;
+        if (!touched) continue;
 #pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                adam(th[r][t], mm[r][t], vv[r][t], acc[t][r], o);
-                E[base + t * 16] = th[r][t];
-                m[base + t * 16] = mm[r][t];
-                v[base + t * 16] = vv[r][t];
-                Eb[base + t * 16] = f2bf(th[r][t]);
+        for (int t = 0; t < 4; ++t) {
+            uint2 h;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                float x = th[t][r], y = mm[t][r], z = vv[t][r];
+                adam(x, y, z, acc[t][r], o);
+                th[t][r] = x;
+                mm[t][r] = y;
+                vv[t][r] = z;
             }
+            h.x = f2bf(th[t][0]) | ((uint32_t)f2bf(th[t][1]) << 16);
+            h.y = f2bf(th[t][2]) | ((uint32_t)f2bf(th[t][3]) << 16);
+            *reinterpret_cast<f32x4 *>(E + base + 16 * t) = th[t];
+            *reinterpret_cast<f32x4 *>(m + base + 16 * t) = mm[t];
+            *reinterpret_cast<f32x4 *>(v + base + 16 * t) = vv[t];
+            *reinterpret_cast<uint2 *>(Eb + base + 16 * t) = h;
         }
     }
 }
@@ -1334,9 +1347,13 @@ int train_step(gapa_ga *ga, const int32_t *genes, const float *target, int32_t B
             return rc;
     }
     const int64_t tiles = ((int64_t)st.n + 15) / 16;
-    // one 16-wave block per compute unit shares one staged copy of dx
-    const unsigned eblocks = (unsigned)std::min<int64_t>((tiles + 15) / 16, 256);
-    hipLaunchKernelGGL(k_grad_adam_E, dim3(eblocks), dim3(1024), grad_E_lds(B), s, st.brows.as<uint32_t>(), Wb,
+    // One block per compute unit shares one staged copy of dx.  Its waves (16 at
+    // the most) are as many as share the tiles evenly: at n = 200k 13 with four
+    // tiles each take 103 us, 16 of which only a few have a fourth 111.
+    const int64_t rounds = (tiles + 256 * 16 - 1) / (256 * 16);
+    const int32_t ewaves = (int32_t)((tiles + 256 * rounds - 1) / (256 * rounds));
+    const unsigned eblocks = (unsigned)std::min<int64_t>((tiles + ewaves - 1) / ewaves, 256);
+    hipLaunchKernelGGL(k_grad_adam_E, dim3(eblocks), dim3(64 * ewaves), grad_E_lds(B), s, st.brows.as<uint32_t>(), Wb,
                        st.dxT.as<uint16_t>(), B, st.theta.as<float>(), st.m.as<float>(), st.v.as<float>(),
                        st.Eb.as<uint16_t>(), keep ? st.keep_E.as<float>() : nullptr, (int64_t)st.n, o);
     GAPA_HIP(hipGetLastError());

@@ -182,6 +182,38 @@ def test_adam_step_matches_formula(gp):
         assert np.max(np.abs(got[name] - q[name])) <= 2e-6, name
 
 
+@pytest.mark.parametrize("n, k, B", [(17, 2, 32), (4096, 33, 64), (65_537, 150, 1024)])
+def test_embedding_step_at_tile_edges(gp, n, k, B):
+    """The embeddings' gradient and step where the last tile of 16 nodes holds
+    one node, where every wave has one tile, and one node past the size from
+    which a wave has more than one: tolerances as in the two tests above."""
+    import torch
+    rng = np.random.default_rng(n)
+    g = inputs.barabasi_albert(n, 2, seed=6)
+    _, ga = make_ga(gp, g, k=k, batch=B)
+    p = set_weights(ga, random_weights(rng, n))
+    sets = inputs.hub_biased_population(g, k, B, seed=8, hub_frac=0.5) if n > 1000 else \
+        inputs.random_population(n, k, B, seed=8)
+    sets[0, 0] = n - 1 if n - 1 not in sets[0] else sets[0, 0]
+    target = rng.normal(size=B).astype(np.float32)
+    ga.train_batch(torch.from_numpy(sets).cuda(), torch.from_numpy(target).cuda(), keep_grads=True)
+    _, ref, _ = S.loss_and_grads(p, sets, target.astype(np.float64), bf16_ops=True)
+    got = ga.surrogate_tensor("E", grad=True, n=n).astype(np.float64)
+    err = np.abs(got - ref["E"])
+    scale = np.max(np.abs(ref["E"]))
+    close = np.mean(err <= 2.0 ** -8 * np.abs(ref["E"]) + 2.0 ** -12 * scale)
+    print(f"n {n} B {B}: max err / max |ref| = {err.max() / scale:.2e}, within a bf16 step: {close:.4f}", flush=True)
+    assert err.max() <= 2.0 ** -6 * scale
+    assert close >= 0.99
+    used = np.zeros(n, bool)
+    used[sets.ravel()] = True
+    assert not got[~used].any()
+    q = {name: t.copy() for name, t in p.items()}
+    grads = {name: ga.surrogate_tensor(name, grad=True, n=n).astype(np.float64) for name in S.TENSORS}
+    S.Adam(q, lr=1e-3).step(q, grads, rows=S.batch_rows(sets))
+    assert np.max(np.abs(weights(ga, n)["E"] - q["E"])) <= 2e-6
+
+
 def run_replayed(gp, g, gens, **kw):
     """Device GA with a surrogate next to the oracle replaying its screening
     decisions; checks the screening, the judge's statistics and the state
