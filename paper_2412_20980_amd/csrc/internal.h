@@ -317,7 +317,11 @@ int launch_mask_build(const int32_t *genes, int32_t P, int32_t k, int32_t n, int
 
 // Dynamic LDS of the operator kernels for n nodes and budget k, and the
 // function attributes they need when it exceeds the default 64 KiB.
+// LDS an operator block needs at least for n and k, at most kOpLdsMax; and the
+// LDS it takes, with the quads of its member counts.
+constexpr size_t kOpLdsMax = 160 * 1024;
 size_t ga_op_lds_bytes(int32_t n, int32_t k);
+size_t ga_op_lds_layout(int32_t n, int32_t k, int32_t *log_q);
 int ga_prepare_kernels(size_t lds);
 
 // Device table entry of one GA instance: where its rows live in the shared
@@ -332,6 +336,7 @@ struct GaInst {
     int32_t noniso_off; // first word of its non-isolated node bit set
     uint64_t seed, t_pc, t_pm;
     int32_t P, L, k, n, W, KW, T, n_noniso;
+    int32_t log_q;      // words of a quad in the operators' LDS, as a power of two
 };
 
 int ga_init_population(gapa_ga *ga, hipStream_t s);

@@ -71,6 +71,17 @@ def test_small_config_trajectories(gp, n, k, P, T, pc, pm, lam, seed):
     lockstep(gp, g, k, P, seed, pc, pm, T, lam, 6)
 
 
+@pytest.mark.parametrize("n,k,P,T,pc,pm,lam", [
+    (127, 63, 3, 2, 0.5, 0.5, 0),          # one quad of the member counts, half full
+    (129, 4, 6, 64, 0.5, 0.5, 9),          # a second quad of one word; a contestant a lane
+    (65_537, 2055, 4, 2, 0.5, 0.1, 0),     # more slots than 256 threads hold in registers
+    (70_000, 4100, 3, 3, 0.6, 0.3, 2),     # and more than 512
+    (1_305_000, 3, 4, 2, 0.7, 0.5, 0),     # LDS nearly full of the set: long quads
+])
+def test_operator_block_edges(gp, n, k, P, T, pc, pm, lam):
+    lockstep(gp, inputs.erdos_renyi(n, 1.5, seed=n), k, P, 11, pc, pm, T, lam, 3)
+
+
 def test_no_variation_fixed_point(gp, ba200):
     graph = gp.Graph.from_csr(ba200)
     ga = gp.GA(graph, 10, 32, 0, pc=0.0, pm=0.0)
