@@ -193,21 +193,6 @@ __global__ __launch_bounds__(64 * kRankWaves) void k_rank_rows(RankArgs a)
     }
 }
 
-OpArgs make_args(gapa_ga *ga, const int32_t *pop)
-{
-    OpArgs a;
-    a.inst = ga->inst.as<GaInst>();
-    a.pop = pop;
-    a.noniso = ga->noniso ? ga->noniso : ga->graph->d_noniso;
-    a.children = ga->children.as<int32_t>();
-    a.masks = ga->masks.as<uint32_t>();
-    a.alive = ga->alive.as<int32_t>();
-    a.flag = ga->flag.as<int32_t>();
-    a.gen_ctr = ga->gen_ctr.as<uint32_t>();
-    a.rows_only = ga->by_rows ? 1 : 0;
-    return a;
-}
-
 }  // namespace
 
 int ga_rank_and_gather(gapa_ga *ga, bool init, const int64_t *f_pool, const int32_t *pool, int32_t npool,
@@ -277,7 +262,7 @@ int ga_prepare_kernels(size_t lds)
 
 int ga_launch_init(gapa_ga *ga, hipStream_t s)
 {
-    OpArgs a = make_args(ga, nullptr);
+    OpArgs a = op_args(ga, nullptr);
     TimedScope ts(&ga->timer, "ga_init", s, 1);
     hipLaunchKernelGGL(k_init, dim3(ga->max_pop, ga->count),
                        dim3(op_threads(ga->params.k, (int64_t)ga->max_pop * ga->count)), ga->op_lds_bytes, s, a);
@@ -287,7 +272,7 @@ int ga_launch_init(gapa_ga *ga, hipStream_t s)
 
 int ga_launch_offspring(gapa_ga *ga, hipStream_t s, bool rows_only)
 {
-    OpArgs a = make_args(ga, ga->pop[ga->cur].as<int32_t>());
+    OpArgs a = op_args(ga, ga->pop[ga->cur].as<int32_t>());
     a.rows_only |= rows_only ? 1 : 0;
     TimedScope ts(&ga->timer, "ga_offspring", s, 1);
     hipLaunchKernelGGL(k_offspring, dim3(ga->max_lambda, ga->count),
@@ -296,12 +281,14 @@ int ga_launch_offspring(gapa_ga *ga, hipStream_t s, bool rows_only)
     return GAPA_OK;
 }
 
-int ga_eval_children(gapa_ga *ga, bool init, hipStream_t s)
+static int ga_eval(gapa_ga *ga, bool init, bool breed, hipStream_t s)
 {
     int32_t *mcn = ga->objective_mcn ? ga->child_mcn.as<int32_t>() : nullptr;
     const Measure measure = ga->objective_forest ? kMeasureForest : kMeasurePC;
     int rc;
-    if (ga->by_rows && ga->count > 1)
+    if (breed)
+        rc = breed_rows_components(ga, mcn, s, measure);
+    else if (ga->by_rows && ga->count > 1)
         rc = eval_rows_components_batch(ga, init, mcn, s, measure);
     else if (ga->by_rows)
         rc = eval_rows_components_ws(ga->graph, ga->children.as<int32_t>(), init ? ga->params.pop : ga->lambda,
@@ -322,6 +309,8 @@ int ga_eval_children(gapa_ga *ga, bool init, hipStream_t s)
     return GAPA_OK;
 }
 
+int ga_eval_children(gapa_ga *ga, bool init, hipStream_t s) { return ga_eval(ga, init, false, s); }
+
 int ga_init_population(gapa_ga *ga, hipStream_t s)
 {
     int rc = launch_fill_u32(ga->gen_ctr.ptr, 0u, 1, s);
@@ -333,8 +322,10 @@ int ga_init_population(gapa_ga *ga, hipStream_t s)
 
 int ga_generation(gapa_ga *ga, hipStream_t s)
 {
-    int rc = ga_launch_offspring(ga, s);
-    if (rc == GAPA_OK) rc = ga_eval_children(ga, false, s);
+    // (with timing on, breeding and evaluation are launches of their own)
+    const bool breed = ga->by_rows && ga->count == 1 && !ga->timer.level && components_breed(ga);
+    int rc = breed ? GAPA_OK : ga_launch_offspring(ga, s);
+    if (rc == GAPA_OK) rc = ga_eval(ga, false, breed, s);
     if (rc == GAPA_OK) rc = ga_rank_and_gather(ga, false, ga->child_fit.as<int64_t>(), nullptr, 0, s);
     if (rc != GAPA_OK) return rc;
     ga->generation += 1;

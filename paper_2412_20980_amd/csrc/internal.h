@@ -298,6 +298,8 @@ struct CompBatch {
     size_t lds = 0;
 };
 int components_batch_plan(gapa_ga *ga, gapa_graph *const *graphs, bool init);
+bool components_breed(const gapa_ga *ga);
+int breed_rows_components(gapa_ga *ga, int32_t *mcn, hipStream_t s, Measure measure);
 int eval_rows_components_batch(gapa_ga *ga, bool init, int32_t *mcn, hipStream_t s, Measure measure);
 
 // Dense reachability fitness (sixdst.hip).

@@ -496,5 +496,21 @@ __device__ __forceinline__ void make_child(const OpLds &l, const Op &a, OpSums &
     emit(l, a, sm, o);
 }
 
+// Arguments of a launch for every instance of ga, breeding from the rows in pop.
+inline OpArgs op_args(gapa_ga *ga, const int32_t *pop)
+{
+    OpArgs a;
+    a.inst = ga->inst.as<GaInst>();
+    a.pop = pop;
+    a.noniso = ga->noniso ? ga->noniso : ga->graph->d_noniso;
+    a.children = ga->children.as<int32_t>();
+    a.masks = ga->masks.as<uint32_t>();
+    a.alive = ga->alive.as<int32_t>();
+    a.flag = ga->flag.as<int32_t>();
+    a.gen_ctr = ga->gen_ctr.as<uint32_t>();
+    a.rows_only = ga->by_rows ? 1 : 0;
+    return a;
+}
+
 }  // namespace
 }  // namespace gapa

@@ -104,6 +104,29 @@ def test_noalloc_and_ga_take_the_same_way(gp):
     assert np.array_equal(pop, ref.pop) and np.array_equal(F, ref.F)
 
 
+@pytest.mark.parametrize("kind,n,k,P,lam,objective", [
+    ("ba", 1000, 60, 20, 256, "mcn"),          # as many children as workgroups
+    ("ba", 5000, 60, 20, 257, "components"),   # one more: workgroups of several, bred apart
+    ("path", 45000, 700, 6, 0, "components"),  # a graph the bit-parallel pass keeps
+    ("tree", 30000, 900, 9, 12, "pc"),
+    ("3.0", 48500, 24000, 3, 0, "pc"),         # the operators need more LDS than the evaluation
+])
+def test_children_bred_in_place_follow_the_oracle(gp, kind, n, k, P, lam, objective):
+    g = graph_of(kind, n)
+    print(f"{kind} n={n} k={k} P={P} lambda={lam} {objective}", flush=True)
+    graph = gp.Graph.from_csr(g)
+    ga = gp.GA(graph, k, P, 21, 0.6, 0.1, 3, lam, objective=objective)
+    timed = gp.GA(graph, k, P, 21, 0.6, 0.1, 3, lam, objective=objective)
+    timed.set_timing(True)
+    oga = O.OracleGA(g, k, P, 21, 0.6, 0.1, 3, lam, objective=objective)
+    for gen in range(4):
+        for x in (ga, timed):
+            pop, F = x.population()
+            assert np.array_equal(F, oga.F) and np.array_equal(pop, oga.pop), gen
+            x.step(1)
+        oga.step()
+
+
 @pytest.mark.parametrize("kinds", [
     [("tree", 30000, 40), ("ba", 400, 100), ("2.0", 41000, 33), ("empty", 5, 7), ("3.0", 3000, 128)],
     [("ba", 300, 9), ("star", 500, 70)],
