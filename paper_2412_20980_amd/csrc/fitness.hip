@@ -252,6 +252,37 @@ int launch_fill_u32(void *p, uint32_t value, int64_t count, hipStream_t s)
     return GAPA_OK;
 }
 
+namespace {
+
+struct MailWords {
+    const uint32_t *src[3];
+    int64_t end[3];  // words up to and with each array
+};
+
+__global__ void k_mail(MailWords m, uint32_t *__restrict__ to)
+{
+    for (int64_t w = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; w < m.end[2]; w += (int64_t)gridDim.x * blockDim.x)
+        to[w] = w < m.end[0] ? m.src[0][w] : w < m.end[1] ? m.src[1][w - m.end[0]] : m.src[2][w - m.end[1]];
+}
+
+}  // namespace
+
+int mail_collect(const Mailbox &mail, MailItem a, MailItem b, MailItem c, hipStream_t s)
+{
+    MailWords m;
+    m.src[0] = static_cast<const uint32_t *>(a.src);
+    m.src[1] = static_cast<const uint32_t *>(b.src);
+    m.src[2] = static_cast<const uint32_t *>(c.src);
+    m.end[0] = (int64_t)(a.bytes / 4);
+    m.end[1] = m.end[0] + (int64_t)(b.bytes / 4);
+    m.end[2] = m.end[1] + (int64_t)(c.bytes / 4);
+    const int64_t blocks = std::min<int64_t>((m.end[2] + 255) / 256, 64);
+    hipLaunchKernelGGL(k_mail, dim3((unsigned)blocks), dim3(256), 0, s, m, reinterpret_cast<uint32_t *>(mail.dev));
+    GAPA_HIP(hipGetLastError());
+    GAPA_HIP(hipStreamSynchronize(s));
+    return GAPA_OK;
+}
+
 int launch_mask_build(const int32_t *genes, int32_t P, int32_t k, int32_t n, int32_t W, const uint32_t *noniso,
                       int32_t n_noniso, uint32_t *masks, int32_t *alive, int32_t *flag, hipStream_t s)
 {

@@ -1175,9 +1175,11 @@ int eval_genes_bits_scratch(gapa_graph *g, const int32_t *genes, int32_t P, int3
         // one workgroup an individual; the scratch past the flag takes the
         // leftover nodes that do not fit LDS
         int32_t *flag = static_cast<int32_t *>(scratch);
-        *flag_out = flag;
-        const int rc = launch_fill_u32(flag, 0u, 4, s);
-        if (rc != GAPA_OK) return rc;
+        if (flag_out) {
+            *flag_out = flag;
+            const int rc = launch_fill_u32(flag, 0u, 4, s);
+            if (rc != GAPA_OK) return rc;
+        }
         return eval_rows_components(g, genes, P, k, fitness, mcn, flag, static_cast<char *>(scratch) + 256,
                                     bytes - 256, nullptr, s, measure);
     }
@@ -1206,7 +1208,7 @@ int eval_genes_bits_scratch(gapa_graph *g, const int32_t *genes, int32_t P, int3
     ws.pflag_clear = false;  // cleared by reserve_pass below: the scratch keeps the last call's flags
     ws.small.borrow(b + l.small, l.total - l.small);
     int32_t *flag = reinterpret_cast<int32_t *>(b + l.flag);
-    *flag_out = flag;
+    if (flag_out) *flag_out = flag;
     PassShape sh{};
     sh.Wd = Wd;
     sh.log_wd = 0;
@@ -1216,7 +1218,7 @@ int eval_genes_bits_scratch(gapa_graph *g, const int32_t *genes, int32_t P, int3
     int rc;
     // the scratch keeps whatever the last call left: the gene flag and the
     // leftover union-find's set sizes must start at zero
-    if ((rc = launch_fill_u32(flag, 0u, 4, s)) != GAPA_OK) return rc;
+    if (flag_out && (rc = launch_fill_u32(flag, 0u, 4, s)) != GAPA_OK) return rc;
     if ((rc = launch_fill_u32(ws.ucount.ptr, 0u, (int64_t)sh.B * g->n, s)) != GAPA_OK) return rc;
     if ((rc = reserve_pass(g, ws, sh, s)) != GAPA_OK) return rc;
     for (int32_t c0 = 0; c0 < P; c0 += sh.B) {
