@@ -148,3 +148,19 @@ def test_batches_follow_single_gas(gp, kinds):
         assert np.array_equal(F, F1) and np.array_equal(rows, rows1), b
         Fo = O.eval_population(graphs[b], rows[:4])
         assert np.array_equal(F[:4], Fo), b
+
+
+@pytest.mark.parametrize("arcs", [[], [(0, 1)], [(0, 1), (1, 2), (2, 0)]])
+def test_repeated_arcs_of_a_trusted_graph(gp, arcs):
+    """Arcs that a trusted CSR holds twice one way only (one list has no room
+    for it; every list has, but with other ids) change no component."""
+    g = inputs.barabasi_albert(2500, 3, seed=2)
+    g = inputs.csr_from_edges(g.n, np.concatenate([np.repeat(np.arange(g.n), g.degrees()), [0, 1, 2]]),
+                              np.concatenate([g.col_idx, [1, 2, 0]]))
+    lists = [list(g.col_idx[g.row_ptr[v]:g.row_ptr[v + 1]]) for v in range(g.n)]
+    for u, v in arcs:
+        lists[u] = sorted(lists[u] + [v])
+    rp = np.concatenate([[0], np.cumsum([len(x) for x in lists])]).astype(np.int32)
+    graph = gp.Graph(g.n, rp, np.concatenate(lists).astype(np.int32), trust=True)
+    rows = inputs.random_population(g.n, 200, 40, seed=9)
+    assert np.array_equal(graph.eval(rows), O.eval_population(g, rows))
