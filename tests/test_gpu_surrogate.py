@@ -84,6 +84,24 @@ def test_forward_matches_oracle(gp, P):
     assert np.max(np.abs(y - ref)) <= 3e-2 * scale
 
 
+@pytest.mark.parametrize("k", [1, 16, 135, 2049, 2200])
+def test_forward_at_row_length_edges(gp, k):
+    """Rows of one gene, of one gene a lane group, of a remainder after the
+    unrolled loads, and of more genes than one staged chunk; tolerances as
+    above."""
+    import torch
+    g = inputs.barabasi_albert(4500, 2, seed=4)
+    _, ga = make_ga(gp, g, k=k, pop=4, lam=32)
+    p = random_weights(np.random.default_rng(k), g.n)
+    p["E"] *= np.sqrt(20 / k)
+    p = set_weights(ga, p)
+    sets = inputs.random_population(g.n, k, 33, seed=k)
+    y = ga.predict(torch.from_numpy(sets).cuda()).cpu().numpy().astype(np.float64)
+    ref_b = S.forward(p, sets, bf16_ops=True)["yhat"]
+    scale = 1.0 + np.max(np.abs(ref_b))
+    assert np.max(np.abs(y - ref_b)) <= 2e-3 * scale
+
+
 def test_gradients_match_oracle(gp):
     """Element by element.  A bfloat16 operand that rounds differently on the
     two sides (their float32 and float64 sums differ in the last bits and
