@@ -467,10 +467,13 @@ __device__ __forceinline__ PullOut pull_node_rt(const int4 r, int Wd, int w, uin
 // pull, 1 while the node has bits pending; read (read_flags) so that settled
 // nodes are skipped without loading their rows (a node's reach row changes
 // only by its own pull, so a settled node stays settled).
+// pending (with kCount): nodes this thread's group left pending (its first lane's
+// count).
+template <bool kCount>
 __device__ __forceinline__ bool pull_sweep_rt(const int4 *__restrict__ recs, int32_t count, int32_t Wd,
                                               const int32_t *__restrict__ colD, const uint32_t *__restrict__ dead,
                                               uint32_t *__restrict__ reach, int32_t max_scan,
-                                              uint8_t *__restrict__ pflag, bool read_flags)
+                                              uint8_t *__restrict__ pflag, bool read_flags, int32_t &pending)
 {
     const int lane = threadIdx.x & 63;
     const int w = lane & (Wd - 1);
@@ -484,6 +487,7 @@ __device__ __forceinline__ bool pull_sweep_rt(const int4 *__restrict__ recs, int
             const int4 r = recs[idx];
             if (pflag && read_flags && !pflag[idx]) continue;
             const PullOut o = pull_node_rt(r, Wd, w, gmask, colD, dead, reach, max_scan);
+            if constexpr (kCount) pending += w == 0 && o.pending;
             any_gain |= o.gained;
             if (pflag && w == 0) pflag[idx] = o.pending ? 1 : 0;
         }
@@ -599,21 +603,102 @@ __global__ __launch_bounds__(kBlk) void k_collect_pending(const uint8_t *__restr
 }
 
 // Further sweeps over the worklist; sweep s runs only if sweep s - 1 changed
-// something (changed[s - 1] != 0; changed[0] is set by the caller).
+// something (changed[s - 1] != 0; changed[0] is set by the caller).  With
+// kCount, one block in kPendingSample adds the nodes it leaves pending to sample.
+constexpr int kPendingSample = 16;
+
+template <bool kCount>
 __global__ void k_pull_worklist(const int4 *__restrict__ worklist, const int32_t *__restrict__ wl_count,
                                 int32_t Wd, const int32_t *__restrict__ colD, const uint32_t *__restrict__ dead,
                                 uint32_t *__restrict__ reach, int32_t *__restrict__ changed, int32_t s,
-                                uint8_t *__restrict__ pflag)
+                                uint8_t *__restrict__ pflag, int32_t *__restrict__ sample)
 {
     if (ld_relaxed(changed + s - 1) == 0) return;
     const int32_t count = ld_relaxed(wl_count);
+    int32_t pending = 0;
     // with flags (pflag not NULL) the first sweep writes every worklist
     // position's flag, later ones skip the nodes it (or they) left settled
-    const bool any_gain = pull_sweep_rt(worklist, count, Wd, colD, dead, reach, INT_MAX, pflag, s > 1);
+    const bool any_gain = pull_sweep_rt<kCount>(worklist, count, Wd, colD, dead, reach, INT_MAX, pflag, s > 1, pending);
+    if constexpr (kCount) {
+        if (blockIdx.x % kPendingSample == 0) {
+            pending = wave_sum(pending);
+            if ((threadIdx.x & 63) == 0 && pending) atomicAdd(sample, pending);
+        }
+    }
     // one flag for the whole grid: set it with a plain store, and only if no
     // other wave has (same-address atomics from every wave would serialise)
     if (any_gain && (threadIdx.x & 63) == 0 && ld_relaxed(changed + s) == 0)
         __hip_atomic_store(changed + s, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// On graphs without hubs (gapa_graph::far) the sweeps end while the roots' sets
+// still grow, and each pair they leave costs the union-find as much as a
+// hundred bits of a sweep.  Further rounds over the worklist, in one launch: a
+// block pulls its nodes again and again, reading what the others have reached
+// so far, and stops when none of its nodes is pending or when few nodes of the
+// whole worklist (one in 512, after the first rounds) gained a bit since its
+// last look; no block waits for another.
+//
+// Random graphs, n = 200k, a pass without and with the rounds: mean degree 8,
+// 32 individuals 7.6 and 0.26 ms, 203 1.4 and 0.27, 2048 0.34 both ways (the
+// sweeps leave nothing there; the sampled count of pending nodes ends the launch
+// at once, where running it for whatever the last sweep changed took 10 us);
+// mean degree 4, 203 individuals 10.6 and 0.54, 1024 25.7 and 0.61.  Small world
+// of 100k nodes 2.4 and 0.35 (32 individuals; 1.7 when one gain in 128 nodes was
+// asked of a round).  Lattices and paths stop after a few rounds.
+constexpr int kRoundBlocks = 2048;  // all resident at once
+constexpr int kRounds = 256, kFirstRounds = 3;
+constexpr int kGainSlot = 40;       // of the pass's counters: nodes that gained a bit, over all blocks and rounds
+constexpr int kPendingSlot = 41;    // and: nodes the last sweep's sampled blocks left pending
+
+__global__ __launch_bounds__(kBlk) void k_pull_rounds(const int4 *__restrict__ worklist,
+                                                      const int32_t *__restrict__ wl_count, int32_t Wd,
+                                                      const int32_t *__restrict__ colD,
+                                                      const uint32_t *__restrict__ dead, uint32_t *__restrict__ reach,
+                                                      const int32_t *__restrict__ pending, int32_t *__restrict__ gains,
+                                                      uint8_t *__restrict__ pflag)
+{
+    __shared__ int32_t s_gain, s_open, s_go;
+    const int32_t count = ld_relaxed(wl_count);
+    // (the last sweep's sampled blocks found few nodes pending)
+    if (ld_relaxed(pending) < count / (128 * kPendingSample)) return;
+    const int lane = threadIdx.x & 63;
+    const int w = lane & (Wd - 1);
+    const uint64_t gmask = group_mask(Wd);
+    const int64_t group = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / Wd;
+    const int64_t ngroups = (int64_t)gridDim.x * blockDim.x / Wd;
+    if (threadIdx.x == 0) s_gain = s_open = 0;
+    int32_t seen = 0;
+    __syncthreads();
+    for (int32_t round = 0; round < kRounds; ++round) {
+        int32_t gained = 0;
+        bool open = false;
+        for (int64_t idx = group; idx < count; idx += ngroups) {
+            if (!pflag[idx]) continue;
+            const PullOut o = pull_node_rt(worklist[idx], Wd, w, gmask, colD, dead, reach, INT_MAX);
+            open |= o.pending;
+            if (w == 0) {
+                gained += o.gained;
+                pflag[idx] = o.pending ? 1 : 0;
+            }
+        }
+        const uint64_t any_open = __ballot(open);
+        gained = wave_sum(gained);
+        if (lane == 0) {
+            if (any_open) s_open = 1;
+            if (gained) atomicAdd(&s_gain, gained);
+        }
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            if (s_gain) atomicAdd(gains, s_gain);
+            const int32_t now = ld_relaxed(gains), more = now - seen;
+            s_go = s_open && (round == 0 || more >= (round < kFirstRounds ? 1 : max(count >> 9, 1)));
+            seen = now;
+            s_gain = s_open = 0;
+        }
+        __syncthreads();
+        if (!s_go) break;
+    }
 }
 
 // Pending (individual, node) pairs.  Every pending node is counted for its
@@ -1081,9 +1166,20 @@ int run_pass(gapa_graph *g, FitnessWorkspace &ws, const PassShape &sh, const Ins
         const bool settled_flags = tu.sweeps >= 3;
         {
             TimedScope ts(timer, "k_pull_worklist", s);
-            for (int32_t sw = 1; sw <= tu.sweeps; ++sw)
-                hipLaunchKernelGGL(k_pull_worklist, dim3(grid), dim3(kBlk), 0, s, worklist, wl_count, Wd, g->d_colD,
-                                   dead, reach, changed, sw, settled_flags ? ws.pflag.as<uint8_t>() : nullptr);
+            uint8_t *flags = settled_flags ? ws.pflag.as<uint8_t>() : nullptr;
+            const bool rounds = g->far && settled_flags;
+            for (int32_t sw = 1; sw <= tu.sweeps; ++sw) {
+                if (rounds && sw == tu.sweeps)
+                    hipLaunchKernelGGL(k_pull_worklist<true>, dim3(grid), dim3(kBlk), 0, s, worklist, wl_count, Wd,
+                                       g->d_colD, dead, reach, changed, sw, flags, ctr + kPendingSlot);
+                else
+                    hipLaunchKernelGGL(k_pull_worklist<false>, dim3(grid), dim3(kBlk), 0, s, worklist, wl_count, Wd,
+                                       g->d_colD, dead, reach, changed, sw, flags, nullptr);
+            }
+            if (rounds)
+                hipLaunchKernelGGL(k_pull_rounds, dim3(kRoundBlocks), dim3(kBlk), 0, s, worklist, wl_count, Wd,
+                                   g->d_colD, dead, reach, ctr + kPendingSlot, ctr + kGainSlot,
+                                   ws.pflag.as<uint8_t>());
         }
         {
             TimedScope ts(timer, "k_collect_pairs", s);
