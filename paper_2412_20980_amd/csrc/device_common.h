@@ -23,6 +23,14 @@ struct Words4 {
     uint32_t w0, w1, w2, w3;
 };
 
+// a ^ b ^ c in one instruction (the truth table of its three-input bit operation;
+// the compiler makes two of it).  Breeding 4096 children of 2000 genes is bound
+// by its draws: 93.6 us to 90.4 (n = 200k), 1024 33.1 to 32.3.
+__device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c)
+{
+    return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);
+}
+
 // Philox4x32-10 (Salmon, Moraes, Dror, Shaw, SC'11): ten rounds, each two
 // 32x32 -> 64-bit products of counter words 0 and 2 whose halves are swapped
 // and xored with the other counter words and the round key; the key advances
@@ -37,8 +45,8 @@ __device__ __forceinline__ Words4 philox4x32_10(uint32_t c0, uint32_t c1, uint32
         const uint64_t p1 = (uint64_t)0xCD9E8D57u * c2;
         const uint32_t lo0 = (uint32_t)p0, hi0 = (uint32_t)(p0 >> 32);
         const uint32_t lo1 = (uint32_t)p1, hi1 = (uint32_t)(p1 >> 32);
-        const uint32_t n0 = hi1 ^ c1 ^ k0;
-        const uint32_t n2 = hi0 ^ c3 ^ k1;
+        const uint32_t n0 = xor3(hi1, c1, k0);
+        const uint32_t n2 = xor3(hi0, c3, k1);
         c0 = n0;
         c1 = lo1;
         c2 = n2;
