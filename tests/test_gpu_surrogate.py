@@ -200,11 +200,14 @@ def test_adam_step_matches_formula(gp):
         assert np.max(np.abs(got[name] - q[name])) <= 2e-6, name
 
 
-@pytest.mark.parametrize("n, k, B", [(17, 2, 32), (4096, 33, 64), (65_537, 150, 1024)])
+@pytest.mark.parametrize("n, k, B", [(17, 2, 32), (4096, 33, 64), (65_537, 150, 1024),
+                                     (262_144, 2100, 32), (262_145, 30, 64)])
 def test_embedding_step_at_tile_edges(gp, n, k, B):
     """The embeddings' gradient and step where the last tile of 16 nodes holds
-    one node, where every wave has one tile, and one node past the size from
-    which a wave has more than one: tolerances as in the two tests above."""
+    one node, where every wave has one tile, one node past the size from which
+    a wave has more than one, and on both sides of the size at which the
+    batch's bit sets are no longer built beside the embedding sums: tolerances
+    as in the two tests above."""
     import torch
     rng = np.random.default_rng(n)
     g = inputs.barabasi_albert(n, 2, seed=6)
