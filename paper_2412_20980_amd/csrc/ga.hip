@@ -42,7 +42,7 @@ __global__ __launch_bounds__(kOpBlock) void k_init(OpArgs args)
     emit(l, a, sm, i);
 }
 
-__global__ __launch_bounds__(kOpBlock) void k_offspring(OpArgs args)
+__global__ __launch_bounds__(kOpBlock, 8) void k_offspring(OpArgs args)
 {
     extern __shared__ __align__(16) uint32_t smem[];
     __shared__ OpSums sm;
@@ -222,11 +222,17 @@ int ga_rank_and_gather(gapa_ga *ga, bool init, const int64_t *f_pool, const int3
     return GAPA_OK;
 }
 
-// Threads of an operator block: more for long rows while there are few of them
-// (k = 3000, n = 200k: 300 children 33 us with 512 threads against 44 with 256;
-// 1024 of k = 2000, a block for every place on the chip, 41 against 35; k = 100:
-// 11.4 against 11.0).
-static int32_t op_threads(int32_t k, int64_t rows) { return k > 256 && rows <= 512 ? kOpBlock : kOpBlock / 2; }
+// Threads of an operator block: 256 for short rows (k = 100: 11.0 us against 11.4
+// with 512; 32 GAs of k = 10 to 500 together 27.4 against 38), 512 for long ones
+// (n = 200k, k = 2000: 1024 children 31.8 us against 32.2, 4096 87.2 against 90.9;
+// 300 of k = 3000 33 against 44).  That takes the registers down to 64, for eight
+// waves a SIMD; with more, 37.5 and 98.2.
+static int32_t op_threads(const gapa_ga *ga)
+{
+    int32_t k = INT_MAX;
+    for (const GaInst &I : ga->hinst) k = std::min(k, I.k);
+    return k > 1024 ? kOpBlock : kOpBlock / 2;
+}
 
 size_t ga_op_lds_bytes(int32_t n, int32_t k)
 {
@@ -265,7 +271,7 @@ int ga_launch_init(gapa_ga *ga, hipStream_t s)
     OpArgs a = op_args(ga, nullptr);
     TimedScope ts(&ga->timer, "ga_init", s, 1);
     hipLaunchKernelGGL(k_init, dim3(ga->max_pop, ga->count),
-                       dim3(op_threads(ga->params.k, (int64_t)ga->max_pop * ga->count)), ga->op_lds_bytes, s, a);
+                       dim3(op_threads(ga)), ga->op_lds_bytes, s, a);
     GAPA_HIP(hipGetLastError());
     return GAPA_OK;
 }
@@ -276,7 +282,7 @@ int ga_launch_offspring(gapa_ga *ga, hipStream_t s, bool rows_only)
     a.rows_only |= rows_only ? 1 : 0;
     TimedScope ts(&ga->timer, "ga_offspring", s, 1);
     hipLaunchKernelGGL(k_offspring, dim3(ga->max_lambda, ga->count),
-                       dim3(op_threads(ga->params.k, (int64_t)ga->max_lambda * ga->count)), ga->op_lds_bytes, s, a);
+                       dim3(op_threads(ga)), ga->op_lds_bytes, s, a);
     GAPA_HIP(hipGetLastError());
     return GAPA_OK;
 }
