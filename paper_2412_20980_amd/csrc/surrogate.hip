@@ -730,28 +730,19 @@ __device__ __forceinline__ uint32_t random_key(uint64_t seed, uint32_t gen, uint
     return draw(seed, i, ind, gen, kStreamSurrRandom, 0).w0;
 }
 
-__device__ __forceinline__ bool bit_of(const uint32_t *bits, int32_t i)
-{
-    return (bits[i >> 5] >> (i & 31)) & 1u;
-}
-
-// Exclusive prefix sum over the block (blockDim.x a multiple of 64, <= 1024);
-// also returns the block total.  Every thread must call it.
-__device__ int32_t block_scan(int32_t x, int32_t *total)
+// Exclusive prefix sum over the 1024 threads of a block; also returns the total.
+// Every thread must call it.
+__device__ __forceinline__ int32_t block_scan(int32_t x, int32_t *total)
 {
     __shared__ int32_t s_wave[16];
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    int32_t incl = x;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const int32_t y = __shfl_up(incl, off, 64);
-        if (lane >= off) incl += y;
-    }
+    const int32_t incl = wave_scan(x);
     if (lane == 63) s_wave[wv] = incl;
     __syncthreads();
     int32_t before = 0, sum = 0;
-    for (int q = 0; q < (int)(blockDim.x >> 6); ++q) {
-        if (q < wv) before += s_wave[q];
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+        before += q < wv ? s_wave[q] : 0;
         sum += s_wave[q];
     }
     __syncthreads();
@@ -759,49 +750,53 @@ __device__ int32_t block_scan(int32_t x, int32_t *total)
     return before + incl - x;
 }
 
-// Sets in sel (a bit set over [0, L), cleared by the caller) the `want`
-// entries with the smallest (key[i], i) among those not in excl (NULL: none
-// excluded); want must not exceed the entries left.  Radix selection on the
-// key, eight bits a pass: each pass counts the candidates' next digit and
-// keeps the digit that holds the want-th smallest; the keys equal to the
-// final value are then taken in index order.  Whole block.
-__device__ void block_select(const uint32_t *key, const uint32_t *excl, int32_t L, int32_t want, uint32_t *sel)
+// Thread t of 1024 holds the keys of the entries [t per, (t + 1) per), u-th in
+// key[u]; those with bit u of `open` are candidates.  Writes the `want` candidates
+// with the smallest (key, entry) to out, ascending by entry, and returns which
+// of the thread's entries they are; want must not exceed the candidates.
+//
+// Radix selection, 11 bits of the key a pass: each pass counts the candidates'
+// next digit (two counters a thread) and keeps the digit that holds the
+// want-th smallest; the keys equal to the final value are then taken in order.
+// (Predictions of one generation share their leading digits: a wave whose
+// digits are all equal adds its count at once.)
+constexpr int kKeysPerThread = kMaxLambda / 1024;
+
+__device__ __forceinline__ uint32_t block_select(const uint32_t (&key)[kKeysPerThread], uint32_t open, int32_t per,
+                                                 int32_t want, int32_t *__restrict__ out)
 {
-    __shared__ int32_t hist[256];
+    __shared__ int32_t hist[2048];
     __shared__ uint32_t s_val;
     __shared__ int32_t s_need;
-    if (want <= 0) return;
-    uint32_t val = 0;  // digits fixed so far
+    uint32_t val = 0;  // the digits fixed so far
     int32_t need = want;
-    for (int shift = 24; shift >= 0; shift -= 8) {
-        for (int32_t i = threadIdx.x; i < 256; i += blockDim.x) hist[i] = 0;
-        __syncthreads();
-        const uint32_t hi_mask = shift == 24 ? 0u : ~0u << (shift + 8);
-        for (int32_t i = threadIdx.x; i < L; i += blockDim.x)
-            if (!(excl && bit_of(excl, i)) && (key[i] & hi_mask) == (val & hi_mask))
-                atomicAdd(&hist[(key[i] >> shift) & 255u], 1);
-        __syncthreads();
-        if (threadIdx.x < 64) {
-            // lane l holds digits 4l .. 4l + 3
-            const int l = threadIdx.x;
-            const int32_t c0 = hist[4 * l], c1 = hist[4 * l + 1], c2 = hist[4 * l + 2], c3 = hist[4 * l + 3];
-            int32_t incl = c0 + c1 + c2 + c3;
 #pragma unroll
-            for (int off = 1; off < 64; off <<= 1) {
-                const int32_t y = __shfl_up(incl, off, 64);
-                if (l >= off) incl += y;
-            }
-            int32_t before = incl - (c0 + c1 + c2 + c3);
-            // the digit whose cumulative count first reaches need
-            const int32_t cs[4] = {c0, c1, c2, c3};
+    for (int pass = 0; pass < 3; ++pass) {
+        const int shift = pass == 0 ? 21 : pass == 1 ? 10 : 0;
+        const uint32_t digits = pass == 2 ? 1023u : 2047u;
+        const uint32_t fixed = pass == 0 ? 0u : pass == 1 ? 0xFFE00000u : 0xFFFFFC00u;
+        hist[threadIdx.x] = hist[threadIdx.x + 1024] = 0;
+        __syncthreads();
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                if (before < need && before + cs[e] >= need) {
-                    s_val = val | ((uint32_t)(4 * l + e) << shift);
-                    s_need = need - before;
-                }
-                before += cs[e];
+        for (int u = 0; u < kKeysPerThread; ++u) {
+            if (!((open >> u) & 1u) || (key[u] & fixed) != val) continue;
+            const uint32_t d = (key[u] >> shift) & digits;
+            const uint64_t here = __ballot(1);
+            if (__ballot(d == (uint32_t)__builtin_amdgcn_readfirstlane((int)d)) == here) {
+                if ((threadIdx.x & 63) == __ffsll((unsigned long long)here) - 1) atomicAdd(&hist[d], __popcll(here));
+            } else {
+                atomicAdd(&hist[d], 1);
             }
+        }
+        __syncthreads();
+        const int32_t c0 = hist[2 * threadIdx.x], c1 = hist[2 * threadIdx.x + 1];
+        int32_t total = 0;
+        const int32_t before = block_scan(c0 + c1, &total);
+        // the digit whose cumulative count first reaches need
+        if (before < need && before + c0 + c1 >= need) {
+            const bool second = before + c0 < need;
+            s_val = val | ((2 * threadIdx.x + (second ? 1u : 0u)) << shift);
+            s_need = need - before - (second ? c0 : 0);
         }
         __syncthreads();
         val = s_val;
@@ -809,36 +804,20 @@ __device__ void block_select(const uint32_t *key, const uint32_t *excl, int32_t 
         __syncthreads();
     }
     // keys below val are taken; of the keys equal to val, the first `need`
-    // in index order.  Thread t owns the index range [t per, (t + 1) per).
-    const int32_t per = (L + blockDim.x - 1) / blockDim.x;
-    const int32_t i0 = min(L, (int32_t)threadIdx.x * per), i1 = min(L, i0 + per);
-    int32_t eq = 0;
-    for (int32_t i = i0; i < i1; ++i) eq += !(excl && bit_of(excl, i)) && key[i] == val;
-    int32_t total = 0;
-    int32_t rank = block_scan(eq, &total);
-    for (int32_t i = i0; i < i1; ++i) {
-        if (excl && bit_of(excl, i)) continue;
-        bool take = key[i] < val;
-        if (key[i] == val) take = rank++ < need;
-        if (take) atomicOr(&sel[i >> 5], 1u << (i & 31));
+    uint32_t less = 0, equal = 0;
+#pragma unroll
+    for (int u = 0; u < kKeysPerThread; ++u) {
+        if (!((open >> u) & 1u)) continue;
+        less |= (key[u] < val ? 1u : 0u) << u;
+        equal |= (key[u] == val ? 1u : 0u) << u;
     }
-    __syncthreads();
-}
-
-// Indices whose bit is set in bits[0, ceil(lambda / 32)), ascending, to
-// out[]; whole block (blockDim.x <= 1024).
-__device__ void block_compact(const uint32_t *bits, int32_t lambda, int32_t *out)
-{
-    const int32_t words = (lambda + 31) / 32;
-    const int32_t per = (words + blockDim.x - 1) / blockDim.x;
-    const int32_t w0 = min(words, (int32_t)threadIdx.x * per), w1 = min(words, w0 + per);
-    int32_t cnt = 0;
-    for (int32_t w = w0; w < w1; ++w) cnt += __popc(bits[w]);
     int32_t total = 0;
-    int32_t off = block_scan(cnt, &total);
-    for (int32_t w = w0; w < w1; ++w)
-        for (uint32_t x = bits[w]; x; x &= x - 1) out[off++] = w * 32 + __ffs(x) - 1;
-    __syncthreads();
+    for (int32_t left = need - block_scan(__popc(equal), &total); __popc(equal) > max(left, 0);)
+        equal &= ~(1u << (31 - __clz((int)equal)));
+    const uint32_t taken = less | equal;
+    int32_t at = block_scan(__popc(taken), &total);
+    for (uint32_t x = taken; x; x &= x - 1) out[at++] = (int32_t)threadIdx.x * per + __ffs(x) - 1;
+    return taken;
 }
 
 // Screening.  pool[0, m): the m children with the smallest (prediction,
@@ -846,24 +825,27 @@ __device__ void block_compact(const uint32_t *bits, int32_t lambda, int32_t *out
 // draw(seed, o, 0, gen, stream 7), o); ascending.  pool[m, m + extra): the
 // judge's unbiased sample, the `extra` other children with the smallest
 // (first word of draw(seed, o, 1, gen, stream 7), o); ascending.  One block
-// of 1024 threads, keys in LDS, lambda <= 8192.
+// of 1024 threads, keys in registers, lambda <= 8192.  4096 children: 15.8 us (30.5 with eight bits
+// a pass, the keys in LDS and the choice kept as a bit set).
 __global__ __launch_bounds__(1024) void k_screen(const float *__restrict__ yhat, int32_t lambda, int32_t m,
                                                  int32_t extra, uint64_t seed, uint32_t gen,
                                                  int32_t *__restrict__ pool)
 {
-    __shared__ uint32_t key[kMaxLambda];
-    __shared__ uint32_t chosen[kMaxLambda / 32], judged[kMaxLambda / 32];
-    for (int32_t i = threadIdx.x; i < lambda; i += blockDim.x)
-        key[i] = yhat ? pred_key(yhat[i]) : random_key(seed, gen, 0, i);
-    for (int32_t i = threadIdx.x; i < kMaxLambda / 32; i += blockDim.x) chosen[i] = judged[i] = 0u;
-    __syncthreads();
-    block_select(key, nullptr, lambda, m, chosen);
-    block_compact(chosen, lambda, pool);
+    const int32_t per = (lambda + 1023) / 1024, i0 = (int32_t)threadIdx.x * per;
+    uint32_t key[kKeysPerThread], open = 0;
+#pragma unroll
+    for (int u = 0; u < kKeysPerThread; ++u) {
+        const bool in = u < per && i0 + u < lambda;
+        key[u] = !in ? 0u : yhat ? pred_key(yhat[i0 + u]) : random_key(seed, gen, 0, i0 + u);
+        open |= (in ? 1u : 0u) << u;
+    }
+    const uint32_t chosen = block_select(key, open, per, m, pool);
     if (extra <= 0) return;
-    for (int32_t i = threadIdx.x; i < lambda; i += blockDim.x) key[i] = random_key(seed, gen, 1, i);
-    __syncthreads();
-    block_select(key, chosen, lambda, extra, judged);
-    block_compact(judged, lambda, pool + m);
+    open &= ~chosen;
+#pragma unroll
+    for (int u = 0; u < kKeysPerThread; ++u)
+        if ((open >> u) & 1u) key[u] = random_key(seed, gen, 1, i0 + u);
+    block_select(key, open, per, extra, pool + m);
 }
 
 __global__ void k_iota(int32_t *__restrict__ out, int32_t count)

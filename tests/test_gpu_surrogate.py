@@ -323,6 +323,16 @@ def test_screened_trajectory_replays_exactly(gp):
         assert abs(dev - r) <= 0.05 * r + 1e-4
 
 
+@pytest.mark.parametrize("n,k,lam,screen", [(40, 1, 700, 300), (40, 1, 8192, 4000), (1500, 12, 1025, 1024),
+                                            (1500, 12, 2049, 1), (60, 2, 1024, 1024)])
+def test_screening_at_selection_edges(gp, n, k, lam, screen):
+    """Screening with many equal predictions (a few dozen distinct children), at
+    one entry a thread and more, for one child and for all."""
+    g = inputs.barabasi_albert(n, 1, seed=5)
+    _, _, screened, _ = run_replayed(gp, g, 4, k=k, lam=lam, screen=screen, fallback_gens=0)
+    assert screened == 2
+
+
 def test_full_size_screened_generations_replay_exactly(gp, cl200k):
     """The surrogate workload at its size: 200k nodes, k = 2000, population
     1024, 4096 children per generation, 512 screened for exact evaluation
