@@ -954,7 +954,7 @@ int gapa_sixdst_eval(gapa_graph *g, const int32_t *genes, int32_t P, int32_t k, 
             (rc = w.six_tot.reserve((size_t)chunk * 8)) != GAPA_OK)
             return rc;
         if ((rc = launch_fill_u32(w.flag.ptr, 0u, 4, s)) != GAPA_OK) return fail_handle(&g->failed, rc);
-        if ((rc = launch_mask_build(d_genes, P, k, g->n, g->words, g->d_noniso, g->n_noniso, w.masks.as<uint32_t>(),
+        if ((rc = launch_mask_build(d_genes, nullptr, P, k, g->n, g->words, g->d_noniso, g->n_noniso, w.masks.as<uint32_t>(),
                                     w.alive.as<int32_t>(), w.flag.as<int32_t>(), s)) != GAPA_OK)
             return fail_handle(&g->failed, rc);
         if ((rc = sixdst_eval_masks(g, w.masks.as<uint32_t>(), P, hops, chunk, w.six_mats.as<uint8_t>(),

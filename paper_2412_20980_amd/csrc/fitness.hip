@@ -58,9 +58,11 @@ __device__ __forceinline__ void unite(int32_t *parent, int32_t a, int32_t b)
     }
 }
 
-// Removed-node bit set of each row of genes, built in LDS and written out,
-// plus the row's count of surviving non-isolated nodes.  One block per row.
-__global__ void k_mask_build_lds(const int32_t *__restrict__ genes, int32_t k, int32_t n, int32_t W,
+// Removed-node bit set of each row of genes (of row rows[i] as the i-th, if rows
+// is given), built in LDS and written out, plus the row's count of surviving
+// non-isolated nodes.  One block per row.
+__global__ void k_mask_build_lds(const int32_t *__restrict__ genes, const int32_t *__restrict__ rows, int32_t k,
+                                 int32_t n, int32_t W,
                                  const uint32_t *__restrict__ noniso, int32_t n_noniso, uint32_t *__restrict__ masks,
                                  int32_t *__restrict__ alive, int32_t *__restrict__ flag)
 {
@@ -70,7 +72,7 @@ __global__ void k_mask_build_lds(const int32_t *__restrict__ genes, int32_t k, i
     for (int32_t w = threadIdx.x; w < W; w += blockDim.x) U[w] = 0u;
     __syncthreads();
     // eight genes a thread at a time, their loads in flight together
-    const int32_t *row = genes + (int64_t)i * k;
+    const int32_t *row = genes + (int64_t)(rows ? rows[i] : i) * k;
     for (int32_t j0 = threadIdx.x; j0 < k; j0 += 8 * blockDim.x) {
         int32_t v[8];
 #pragma unroll
@@ -119,14 +121,15 @@ __global__ void k_mask_build_lds(const int32_t *__restrict__ genes, int32_t k, i
 }
 
 // Same with the bit set built in global memory (bit sets too large for LDS).
-__global__ void k_mask_build(const int32_t *__restrict__ genes, int32_t k, int32_t n, int32_t W,
+__global__ void k_mask_build(const int32_t *__restrict__ genes, const int32_t *__restrict__ rows, int32_t k,
+                             int32_t n, int32_t W,
                              uint32_t *__restrict__ masks, int32_t *__restrict__ flag)
 {
     const int32_t i = blockIdx.x;
     uint32_t *m = masks + (int64_t)i * W;
     for (int32_t w = threadIdx.x; w < W; w += blockDim.x) m[w] = 0u;
     __syncthreads();
-    const int32_t *row = genes + (int64_t)i * k;
+    const int32_t *row = genes + (int64_t)(rows ? rows[i] : i) * k;
     for (int32_t j = threadIdx.x; j < k; j += blockDim.x) {
         const int32_t v = row[j];
         if (v < 0 || v >= n) {
@@ -283,16 +286,16 @@ int mail_collect(const Mailbox &mail, MailItem a, MailItem b, MailItem c, hipStr
     return GAPA_OK;
 }
 
-int launch_mask_build(const int32_t *genes, int32_t P, int32_t k, int32_t n, int32_t W, const uint32_t *noniso,
+int launch_mask_build(const int32_t *genes, const int32_t *rows, int32_t P, int32_t k, int32_t n, int32_t W, const uint32_t *noniso,
                       int32_t n_noniso, uint32_t *masks, int32_t *alive, int32_t *flag, hipStream_t s)
 {
     if (P <= 0) return GAPA_OK;
     const size_t lds = (size_t)W * 4;
     if (lds <= 64 * 1024) {
-        hipLaunchKernelGGL(k_mask_build_lds, dim3(P), dim3(kBlock), lds, s, genes, k, n, W, noniso, n_noniso, masks,
+        hipLaunchKernelGGL(k_mask_build_lds, dim3(P), dim3(kBlock), lds, s, genes, rows, k, n, W, noniso, n_noniso, masks,
                            alive, flag);
     } else {
-        hipLaunchKernelGGL(k_mask_build, dim3(P), dim3(kBlock), 0, s, genes, k, n, W, masks, flag);
+        hipLaunchKernelGGL(k_mask_build, dim3(P), dim3(kBlock), 0, s, genes, rows, k, n, W, masks, flag);
         hipLaunchKernelGGL(k_mask_alive, dim3(P), dim3(kBlock), 0, s, masks, W, noniso, n_noniso, alive);
     }
     GAPA_HIP(hipGetLastError());
@@ -322,7 +325,7 @@ int eval_genes(gapa_graph *g, const int32_t *genes, int32_t P, int32_t k, int64_
     if ((rc = ws.alive.reserve((size_t)P * 4)) != GAPA_OK) return rc;
     {
         TimedScope ts(timer, "mask_build", s);
-        if ((rc = launch_mask_build(genes, P, k, g->n, g->words, g->d_noniso, g->n_noniso, ws.masks.as<uint32_t>(),
+        if ((rc = launch_mask_build(genes, nullptr, P, k, g->n, g->words, g->d_noniso, g->n_noniso, ws.masks.as<uint32_t>(),
                                     ws.alive.as<int32_t>(), flag, s)) != GAPA_OK)
             return rc;
     }

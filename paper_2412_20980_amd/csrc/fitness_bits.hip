@@ -1319,7 +1319,7 @@ int eval_genes_bits_scratch(gapa_graph *g, const int32_t *genes, int32_t P, int3
     if ((rc = reserve_pass(g, ws, sh, s)) != GAPA_OK) return rc;
     for (int32_t c0 = 0; c0 < P; c0 += sh.B) {
         const int32_t rows = std::min(sh.B, P - c0);
-        if ((rc = launch_mask_build(genes ? genes + (int64_t)c0 * k : nullptr, rows, k, g->n, g->words, g->d_noniso,
+        if ((rc = launch_mask_build(genes ? genes + (int64_t)c0 * k : nullptr, nullptr, rows, k, g->n, g->words, g->d_noniso,
                                     g->n_noniso, ws.masks.as<uint32_t>(), ws.alive.as<int32_t>(), flag, s)) != GAPA_OK)
             return rc;
         if ((rc = run_pass(g, ws, sh, nullptr, ws.masks.as<uint32_t>(), ws.alive.as<int32_t>(), rows, 0, fitness + c0,

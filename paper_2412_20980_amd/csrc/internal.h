@@ -342,10 +342,10 @@ size_t sixdst_bytes_per_individual(int32_t n);
 int sixdst_eval_masks(gapa_graph *g, const uint32_t *masks, int32_t P, int32_t hops, int32_t chunk, uint8_t *mats,
                       unsigned long long *tot, int64_t *pc, int32_t *mcn, hipStream_t s);
 
-// genes[P][k] (device) -> masks[P][W] and alive[P]; out-of-range genes
-// raise flag[0].
-int launch_mask_build(const int32_t *genes, int32_t P, int32_t k, int32_t n, int32_t W, const uint32_t *noniso,
-                      int32_t n_noniso, uint32_t *masks, int32_t *alive, int32_t *flag, hipStream_t s);
+// P rows of genes[.][k] (device; rows[0 .. P), or the first P when rows is NULL)
+// -> masks[P][W] and alive[P]; out-of-range genes raise flag[0].
+int launch_mask_build(const int32_t *genes, const int32_t *rows, int32_t P, int32_t k, int32_t n, int32_t W,
+                      const uint32_t *noniso, int32_t n_noniso, uint32_t *masks, int32_t *alive, int32_t *flag, hipStream_t s);
 
 // ------------------------------------------------------------------- GA -----
 

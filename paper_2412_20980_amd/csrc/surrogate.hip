@@ -825,8 +825,8 @@ __device__ __forceinline__ uint32_t block_select(const uint32_t (&key)[kKeysPerT
 // draw(seed, o, 0, gen, stream 7), o); ascending.  pool[m, m + extra): the
 // judge's unbiased sample, the `extra` other children with the smallest
 // (first word of draw(seed, o, 1, gen, stream 7), o); ascending.  One block
-// of 1024 threads, keys in registers, lambda <= 8192.  4096 children: 15.8 us (30.5 with eight bits
-// a pass, the keys in LDS and the choice kept as a bit set).
+// of 1024 threads, keys in registers, lambda <= 8192.  4096 children: 15.8 us
+// (30.5 with eight bits a pass, the keys in LDS and the choice kept as a bit set).
 __global__ __launch_bounds__(1024) void k_screen(const float *__restrict__ yhat, int32_t lambda, int32_t m,
                                                  int32_t extra, uint64_t seed, uint32_t gen,
                                                  int32_t *__restrict__ pool)
@@ -1348,7 +1348,7 @@ int train_step(gapa_ga *ga, const int32_t *genes, const float *target, int32_t B
         hipLaunchKernelGGL(k_batch_bits, dim3(nchunks), dim3(256), (size_t)kBitChunk * Wb * 4, s, genes, st.k, B, pos,
                            nchunks, st.n, st.brows.as<uint32_t>());
     } else {
-        if (!masked) rc = launch_mask_build(genes, B, st.k, g->n, g->words, g->d_noniso, g->n_noniso,
+        if (!masked) rc = launch_mask_build(genes, nullptr, B, st.k, g->n, g->words, g->d_noniso, g->n_noniso,
                                             st.bmasks.as<uint32_t>(), st.balive.as<int32_t>(), st.tflag.as<int32_t>(), s);
         if (rc != GAPA_OK) return rc;
         if ((rc = launch_bits_transpose(st.bmasks.as<uint32_t>(), B, g->words, g->n, st.brows.as<uint32_t>(), s)) !=
@@ -1475,7 +1475,7 @@ int surrogate_attach(gapa_ga *ga, const gapa_surrogate_params *sp, hipStream_t s
     res(st->buf_genes, (size_t)sp->buffer * st->k * 4);
     res(st->buf_y, (size_t)sp->buffer * 8);
     res(st->pool, (size_t)L * 4);
-    res(st->crows, (size_t)(sp->screen + kJudgeExtra) * st->k * 4);
+    if (ga->by_rows) res(st->crows, (size_t)(sp->screen + kJudgeExtra) * st->k * 4);
     res(st->cmasks, (size_t)(sp->screen + kJudgeExtra) * st->W * 4);
     res(st->calive, (size_t)(sp->screen + kJudgeExtra) * 4);
     res(st->dstats, 64);
@@ -1585,17 +1585,18 @@ int surrogate_generation(gapa_ga *ga, hipStream_t s)
         pool = st.pool.as<int32_t>();
         hipLaunchKernelGGL(k_screen, dim3(1), dim3(1024), 0, s, random ? nullptr : yhat, L, npool, extra,
                            st.seed, gen, st.pool.as<int32_t>());
-        hipLaunchKernelGGL(k_gather_pool_rows, dim3(neval), dim3(256), 0, s, pool, ga->children.as<int32_t>(), st.k,
-                           st.crows.as<int32_t>());
         GAPA_HIP(hipGetLastError());
         gapa_graph *g = ga->graph;
         if (ga->by_rows) {
+            hipLaunchKernelGGL(k_gather_pool_rows, dim3(neval), dim3(256), 0, s, pool, ga->children.as<int32_t>(), st.k,
+                               st.crows.as<int32_t>());
+            GAPA_HIP(hipGetLastError());
             if ((rc = eval_rows_components_ws(g, st.crows.as<int32_t>(), neval, st.k, F, nullptr,
                                               st.bflag.as<int32_t>(), ga->ws, &ga->timer, s, kMeasurePC)) != GAPA_OK)
                 return rc;
         } else {
-            if ((rc = launch_mask_build(st.crows.as<int32_t>(), neval, st.k, g->n, g->words, g->d_noniso, g->n_noniso,
-                                        st.cmasks.as<uint32_t>(), st.calive.as<int32_t>(), st.bflag.as<int32_t>(),
+            if ((rc = launch_mask_build(ga->children.as<int32_t>(), pool, neval, st.k, g->n, g->words, g->d_noniso,
+                                        g->n_noniso, st.cmasks.as<uint32_t>(), st.calive.as<int32_t>(), st.bflag.as<int32_t>(),
                                         s)) != GAPA_OK)
                 return rc;
             if ((rc = eval_masks(ga->graph, st.cmasks.as<uint32_t>(), st.calive.as<int32_t>(), neval, F, nullptr,
