@@ -1097,6 +1097,10 @@ int ga_allocate(gapa_ga *ga, int32_t count, const gapa_params *p, const int32_t 
     }
     if (rc == GAPA_OK) rc = ga->children.reserve((size_t)child_el * 4);
     if (rc == GAPA_OK) rc = ga->child_fit.reserve((size_t)slots * 8);
+    if (by_rows && count == 1 && ga->max_pop_lambda <= kMergeKeys) {
+        if (rc == GAPA_OK) rc = ga->children_prev.reserve((size_t)child_el * 4);
+        if (rc == GAPA_OK) rc = ga->child_fit_prev.reserve((size_t)slots * 8);
+    }
     ga->slots = slots;
     ga->objective_mcn = (p[0].flags & GAPA_MINIMISE_MCN) != 0;
     ga->objective_forest = (p[0].flags & GAPA_MAXIMISE_COMPONENTS) != 0;
@@ -1191,6 +1195,7 @@ int ga_run(gapa_ga *ga, int32_t n_generations, hipStream_t s)
             ++i;
             continue;
         }
+        if (n_generations - i >= 2 && ga_merges(ga)) return ga_generations(ga, n_generations - i, s);
         if (!(ga->use_graph && ga->warm && ga->timer.level == 0)) {
             const int rc = ga_generation(ga, s);
             if (rc != GAPA_OK) return rc;
@@ -1305,7 +1310,7 @@ void ga_release(gapa_ga *ga)
     ga->surr = nullptr;
     if (ga->cap_stream) (void)hipStreamDestroy(ga->cap_stream);
     ga->cap_stream = nullptr;
-    for (auto *b : {&ga->pop[0], &ga->pop[1], &ga->fit[0], &ga->fit[1], &ga->children, &ga->child_fit, &ga->child_mcn, &ga->masks,
+    for (auto *b : {&ga->pop[0], &ga->pop[1], &ga->fit[0], &ga->fit[1], &ga->children, &ga->child_fit, &ga->children_prev, &ga->child_fit_prev, &ga->child_mcn, &ga->masks,
                     &ga->alive, &ga->flag, &ga->gen_ctr, &ga->inst, &ga->noniso_buf,
                     &ga->tab_voff, &ga->tab_live_init, &ga->tab_live_gen, &ga->tab_moff, &ga->tab_node_inst,
                     &ga->tab_tiles, &ga->comp_init.insts, &ga->comp_init.tasks, &ga->comp_init.lists, &ga->comp_gen.insts, &ga->comp_gen.tasks})

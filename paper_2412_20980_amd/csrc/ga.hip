@@ -49,7 +49,7 @@ __global__ __launch_bounds__(kOpBlock, 8) void k_offspring(OpArgs args)
     const Op a = resolve(args);
     const int32_t o = blockIdx.x;
     if (o >= a.L) return;
-    make_child(carve(smem, a), a, sm, o, *args.gen_ctr + 1u);
+    make_child(carve(smem, a), a, sm, o, *args.gen_ctr + 1u, [&](int32_t p) { return a.pop + (int64_t)p * a.k; });
 }
 
 // Fitness of every slot from the pass's MCN (GAPA_MINIMISE_MCN).
@@ -90,7 +90,8 @@ struct RankArgs {
     const int32_t *parents;   // rows of the current population (instance base pop_off)
     const int32_t *children;  // rows of the offspring (instance base child_off)
     int32_t *rows_out;        // rows of the next population (instance base pop_off)
-    uint32_t *gen_ctr;        // [1] advanced after generation 0
+    uint32_t *gen_ctr;        // [1] advanced by gens after generation 0
+    uint32_t gens;
 };
 
 struct RankView {
@@ -123,7 +124,7 @@ __global__ __launch_bounds__(64 * kRankWaves) void k_rank_rows(RankArgs a)
     const int32_t total = r.npar + r.npool;
     const int32_t k0 = blockIdx.x * kRankKeys;
     // (every reader of the counter in this generation has finished: stream order)
-    if (!a.init && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) a.gen_ctr[0] += 1u;
+    if (!a.init && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) a.gen_ctr[0] += a.gens;
     if (k0 >= total) return;  // uniform over the block
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     if (threadIdx.x < kRankKeys) {
@@ -196,7 +197,7 @@ __global__ __launch_bounds__(64 * kRankWaves) void k_rank_rows(RankArgs a)
 }  // namespace
 
 int ga_rank_and_gather(gapa_ga *ga, bool init, const int64_t *f_pool, const int32_t *pool, int32_t npool,
-                       hipStream_t s)
+                       hipStream_t s, int32_t gens)
 {
     const int nxt = init ? ga->cur : 1 - ga->cur;
     const int32_t count = ga->count;
@@ -212,6 +213,7 @@ int ga_rank_and_gather(gapa_ga *ga, bool init, const int64_t *f_pool, const int3
     a.children = ga->children.as<int32_t>();
     a.rows_out = ga->pop[nxt].as<int32_t>();
     a.gen_ctr = ga->gen_ctr.as<uint32_t>();
+    a.gens = (uint32_t)gens;
     // launch extents: the largest instance
     const int32_t max_total = init ? ga->max_pop : (pool ? ga->max_pop + npool : ga->max_pop_lambda);
     TimedScope pass(&ga->timer, "elitism", s, 1);
@@ -336,6 +338,16 @@ int ga_generation(gapa_ga *ga, hipStream_t s)
     if (rc != GAPA_OK) return rc;
     ga->generation += 1;
     return GAPA_OK;
+}
+
+int ga_generations(gapa_ga *ga, int32_t n, hipStream_t s)
+{
+    const Measure measure = ga->objective_forest ? kMeasureForest : kMeasurePC;
+    int rc = GAPA_OK;
+    for (int32_t i = 0; i < n && rc == GAPA_OK; ++i) rc = breed_rows_components(ga, nullptr, s, measure, i);
+    if (rc == GAPA_OK) rc = ga_rank_and_gather(ga, false, ga->child_fit.as<int64_t>(), nullptr, 0, s, n);
+    if (rc == GAPA_OK) ga->generation += n;
+    return rc;
 }
 
 }  // namespace gapa

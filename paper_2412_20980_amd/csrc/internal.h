@@ -331,7 +331,8 @@ struct CompBatch {
 };
 int components_batch_plan(gapa_ga *ga, gapa_graph *const *graphs, bool init);
 bool components_breed(const gapa_ga *ga);
-int breed_rows_components(gapa_ga *ga, int32_t *mcn, hipStream_t s, Measure measure);
+// (ahead > 0: the ahead-th generation since the last elitism, merged in first)
+int breed_rows_components(gapa_ga *ga, int32_t *mcn, hipStream_t s, Measure measure, int32_t ahead = 0);
 int eval_rows_components_batch(gapa_ga *ga, bool init, int32_t *mcn, hipStream_t s, Measure measure);
 
 // Dense reachability fitness (sixdst.hip).
@@ -377,6 +378,11 @@ int ga_init_population(gapa_ga *ga, hipStream_t s);
 // One generation of every instance; the generation number is read on the
 // device, so the launches can be captured into a graph and replayed.
 int ga_generation(gapa_ga *ga, hipStream_t s);
+// n >= 2 generations at a launch each, one elitism at the end; for GAs that
+// ga_merges allows.
+constexpr int32_t kMergeKeys = 256;  // parents and children together, at most
+bool ga_merges(const gapa_ga *ga);
+int ga_generations(gapa_ga *ga, int32_t n, hipStream_t s);
 int ga_launch_init(gapa_ga *ga, hipStream_t s);
 // rows_only: the children's rows only; their bit sets and alive counts are
 // left for the caller to build (for the few it evaluates).
@@ -387,7 +393,7 @@ int ga_launch_offspring(gapa_ga *ga, hipStream_t s, bool rows_only = false);
 // writes the next population buffer and, after generation 0, advances the
 // device generation counter.
 int ga_rank_and_gather(gapa_ga *ga, bool init, const int64_t *f_pool, const int32_t *pool, int32_t npool,
-                       hipStream_t s);
+                       hipStream_t s, int32_t gens = 1);
 // Exact fitness of the children currently held (the initial population at
 // generation 0) into child_fit.
 int ga_eval_children(gapa_ga *ga, bool init, hipStream_t s);
@@ -437,6 +443,7 @@ struct gapa_ga {
     gapa::DevBuf fit[2];          // int64 [sum P]
     gapa::DevBuf children;        // int32 rows
     gapa::DevBuf child_fit;       // int64 slots
+    gapa::DevBuf children_prev, child_fit_prev;  // of the generation before, when generations run at a launch each
     gapa::DevBuf child_mcn;       // int32 slots (GAPA_MINIMISE_MCN: the pass's MCN, copied into child_fit)
     int32_t slots = 0;
     bool objective_mcn = false;

@@ -365,7 +365,10 @@ constexpr int kOpSlots = 8;
 //   eq. 9   each mutated slot, ascending, swaps its gene for a uniform
 //           non-member (MUTATE draws).
 //   sort    the row ascending.
-__device__ __forceinline__ void make_child(const OpLds &l, const Op &a, OpSums &sm, int32_t o, uint32_t gen)
+// row(p) points at the row at position p of the population.
+template <class Row>
+__device__ __forceinline__ void make_child(const OpLds &l, const Op &a, OpSums &sm, int32_t o, uint32_t gen,
+                                           const Row &row)
 {
     const int32_t T = blockDim.x;
     if (threadIdx.x < 64) {
@@ -384,8 +387,8 @@ __device__ __forceinline__ void make_child(const OpLds &l, const Op &a, OpSums &
     clear_lds(l, a);
     __syncthreads();
 
-    const int32_t *base = a.pop + (int64_t)(o % a.P) * a.k;
-    const int32_t *donor = a.pop + (int64_t)sm.donor * a.k;
+    const int32_t *base = row(o % a.P);
+    const int32_t *donor = row(sm.donor);
     const bool regs = a.k <= T * kOpSlots;
     int32_t bv[kOpSlots], dv[kOpSlots];
     uint32_t takes = 0u;  // bit i: slot threadIdx.x + T i takes the donor gene

@@ -15,8 +15,9 @@ WRITE_SIZE counters in KiB per dispatch) and writes
     counter runs of the same command, the HBM traffic of one pass: FETCH_SIZE
     and WRITE_SIZE summed over the pass's kernels, each scaled by bytes /
     counter measured on a plain copy of known size.
-A pass is the dispatches of the fitness kernels from one k_dead_transpose up
-to the next dispatch of any other kernel.
+A pass is the dispatches of the fitness kernels from one k_dead_transpose (or
+k_components_batch, a pass of its own) up to the next dispatch of any other
+kernel.
 """
 from __future__ import annotations
 
@@ -28,10 +29,11 @@ import re
 import sqlite3
 import sys
 
-# kernels of one batched-fitness pass (bit-parallel path)
+# kernels of one batched-fitness pass (bit-parallel path; workgroups of their own)
 FITNESS_KERNELS = ("k_dead_transpose", "k_seed", "k_pull_band", "k_collect_pending", "k_pull_worklist",
-                   "k_collect_pairs", "k_pairs_hook", "k_pairs_count", "k_pairs_reduce")
-PASS_MARKER = "k_dead_transpose"  # launched first in every pass, once
+                   "k_pull_rounds", "k_collect_pairs", "k_pairs_hook", "k_pairs_count", "k_pairs_reduce",
+                   "k_components_batch")
+PASS_MARKERS = ("k_dead_transpose", "k_components_batch")  # launched first in every pass, once
 
 
 def short(name: str) -> str:
@@ -83,16 +85,16 @@ def kernel_table(db: str) -> str:
 
 def last_passes(seq, K: int):
     """Indices of the dispatches of the last K passes in a sequence of
-    (kernel name, ...) items: a pass starts at PASS_MARKER and runs while the
+    (kernel name, ...) items: a pass starts at one of PASS_MARKERS and runs while the
     kernels are fitness kernels."""
-    starts = [i for i, it in enumerate(seq) if it[0] == PASS_MARKER]
+    starts = [i for i, it in enumerate(seq) if it[0] in PASS_MARKERS]
     if len(starts) < K:
         raise SystemExit(f"only {len(starts)} passes in the run, {K} asked for")
     out = []
     for s in starts[-K:]:
         i = s
         idx = []
-        while i < len(seq) and seq[i][0] in FITNESS_KERNELS and (i == s or seq[i][0] != PASS_MARKER):
+        while i < len(seq) and seq[i][0] in FITNESS_KERNELS and (i == s or seq[i][0] not in PASS_MARKERS):
             idx.append(i)
             i += 1
         out.append(idx)

@@ -127,6 +127,34 @@ def test_children_bred_in_place_follow_the_oracle(gp, kind, n, k, P, lam, object
         oga.step()
 
 
+@pytest.mark.parametrize("kind,n,k,P,lam,objective", [
+    ("ba", 200, 10, 32, 0, "pc"),
+    ("2.0", 60, 1, 1, 255, "pc"),            # one parent; as many keys as threads
+    ("2.0", 60, 2, 200, 56, "components"),   # more rows to copy than blocks; many equal keys
+    ("empty", 40, 3, 9, 12, "components"),   # all keys equal
+    ("3.0", 900, 30, 128, 128, "pc"),
+    ("3.0", 900, 30, 128, 129, "pc"),        # one key too many: elitism launched by itself
+    ("tree", 30000, 900, 9, 12, "pc"),
+    ("1.5", 2500, 700, 40, 20, "mcn"),       # an objective of its own launch
+])
+def test_generations_of_one_call_follow_the_oracle(gp, kind, n, k, P, lam, objective):
+    """Calls of one, two and more generations, in every parity, the children's
+    buffers swapped in between; timing on for one call."""
+    g = graph_of(kind, n)
+    print(f"{kind} n={n} k={k} P={P} lambda={lam} {objective}", flush=True)
+    ga = gp.GA(gp.Graph.from_csr(g), k, P, 22, 0.6, 0.1, 2, lam, objective=objective)
+    oga = O.OracleGA(g, k, P, 22, 0.6, 0.1, 2, lam, objective=objective)
+    for steps, timing in ((2, 0), (1, 0), (3, 0), (5, 0), (2, 1), (4, 0)):
+        ga.set_timing(timing)
+        ga.step(steps)
+        for _ in range(steps):
+            oga.step()
+        pop, F = ga.population()
+        assert np.array_equal(F, oga.F) and np.array_equal(pop, oga.pop), steps
+        genes, f, gens = ga.best()
+        assert gens == oga.generation and f == oga.F[0] and np.array_equal(genes, oga.pop[0])
+
+
 @pytest.mark.parametrize("kinds", [
     [("tree", 30000, 40), ("ba", 400, 100), ("2.0", 41000, 33), ("empty", 5, 7), ("3.0", 3000, 128)],
     [("ba", 300, 9), ("star", 500, 70)],
