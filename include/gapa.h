@@ -77,7 +77,10 @@ enum {
                                    launches as a HIP graph once and replay it
                                    (same results; fewer launch gaps).  Kernel
                                    timing, when enabled, runs generations
-                                   eagerly instead.                             */
+                                   eagerly instead; so does a GA whose
+                                   generation is a launch or two (on small
+                                   graphs), but for calls gapa_ga_record has
+                                   recorded as a whole.                         */
     GAPA_MINIMISE_MCN = 1u << 5, /* gapa_params.flags: the GA minimises the
                                    largest surviving component (MCN, the CND
                                    fitness of Section III-D) instead of PC: the

@@ -1147,7 +1147,9 @@ int capture_generations(gapa_ga *ga, int c, int32_t gens)
     const int64_t gen = ga->generation;
     GAPA_HIP(hipStreamBeginCapture(ga->cap_stream, hipStreamCaptureModeRelaxed));
     int rc = GAPA_OK;
-    for (int32_t i = 0; i < gens && rc == GAPA_OK; ++i) rc = ga_generation(ga, ga->cap_stream);
+    if (gens >= 2 && ga_merges(ga)) rc = ga_generations(ga, gens, ga->cap_stream);
+    else
+        for (int32_t i = 0; i < gens && rc == GAPA_OK; ++i) rc = ga_generation(ga, ga->cap_stream);
     hipGraph_t graph = nullptr;
     const hipError_t e = hipStreamEndCapture(ga->cap_stream, &graph);
     ga->cur = c;
@@ -1195,17 +1197,26 @@ int ga_run(gapa_ga *ga, int32_t n_generations, hipStream_t s)
             ++i;
             continue;
         }
-        if (n_generations - i >= 2 && ga_merges(ga)) return ga_generations(ga, n_generations - i, s);
-        if (!(ga->use_graph && ga->warm && ga->timer.level == 0)) {
+        const int c = ga->cur;
+        const bool replays = ga->use_graph && ga->warm && ga->timer.level == 0;
+        // a recording of all remaining generations (made by gapa_ga_record), else one
+        // generation; a GA whose generation is a launch or two makes those instead
+        // (n = 200, P = 32: 14.0 us a generation against 20.0, n = 10k, P = 256: 27.7
+        // and 32.2: a graph costs the host more than they do)
+        gapa_ga::Replay *r = replays ? find_replay(ga, c, n_generations - i) : nullptr;
+        const bool direct = ga->by_rows && ga->count == 1 && components_breed(ga);
+        if (!r && n_generations - i >= 2 && ga_merges(ga)) {
+            const int rc = ga_generations(ga, n_generations - i, s);
+            ga->warm = ga->warm || rc == GAPA_OK;
+            return rc;
+        }
+        if (!r && (!replays || direct)) {
             const int rc = ga_generation(ga, s);
             if (rc != GAPA_OK) return rc;
             ga->warm = true;  // every buffer of a generation has its final size
             ++i;
             continue;
         }
-        const int c = ga->cur;
-        // a recording of all remaining generations (made by gapa_ga_record), else one generation
-        gapa_ga::Replay *r = find_replay(ga, c, n_generations - i);
         if (!r) {
             r = find_replay(ga, c, 1);
             if (!r) {

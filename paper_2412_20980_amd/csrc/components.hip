@@ -919,7 +919,7 @@ bool components_breed(const gapa_ga *ga)
 // = 128 (64) 21.7 and 22.3.
 bool ga_merges(const gapa_ga *ga)
 {
-    if (!ga->by_rows || ga->count != 1 || ga->surr || ga->objective_mcn || ga->use_graph || ga->timer.level ||
+    if (!ga->by_rows || ga->count != 1 || ga->surr || ga->objective_mcn || ga->timer.level ||
         ga->max_pop_lambda > kMergeKeys || ga->op_lds_bytes > kCompLds / 2)
         return false;
     const int32_t parts = comp_threads(ga->graph->n, ga->lambda) / ga->max_pop_lambda;
@@ -948,8 +948,7 @@ int breed_rows_components(gapa_ga *ga, int32_t *mcn, hipStream_t s, Measure meas
     MergeArgs m{};
     size_t lds = c.lds;
     if (ahead > 0) {
-        std::swap(ga->children, ga->children_prev);
-        std::swap(ga->child_fit, ga->child_fit_prev);
+        ga->swap_children();
         m.f_par = ga->fit[ga->cur].as<int64_t>();
         m.f_child = ga->child_fit_prev.as<int64_t>();
         m.children = ga->children_prev.as<int32_t>();

@@ -344,6 +344,8 @@ int ga_generations(gapa_ga *ga, int32_t n, hipStream_t s)
 {
     const Measure measure = ga->objective_forest ? kMeasureForest : kMeasurePC;
     int rc = GAPA_OK;
+    // (an even number of swaps: the last children are where recordings, too, put theirs)
+    if ((n & 1) == 0) ga->swap_children();
     for (int32_t i = 0; i < n && rc == GAPA_OK; ++i) rc = breed_rows_components(ga, nullptr, s, measure, i);
     if (rc == GAPA_OK) rc = ga_rank_and_gather(ga, false, ga->child_fit.as<int64_t>(), nullptr, 0, s, n);
     if (rc == GAPA_OK) ga->generation += n;

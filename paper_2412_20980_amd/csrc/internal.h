@@ -8,6 +8,7 @@
 #include <atomic>
 #include <map>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "gapa.h"
@@ -444,6 +445,11 @@ struct gapa_ga {
     gapa::DevBuf children;        // int32 rows
     gapa::DevBuf child_fit;       // int64 slots
     gapa::DevBuf children_prev, child_fit_prev;  // of the generation before, when generations run at a launch each
+    void swap_children()
+    {
+        std::swap(children, children_prev);
+        std::swap(child_fit, child_fit_prev);
+    }
     gapa::DevBuf child_mcn;       // int32 slots (GAPA_MINIMISE_MCN: the pass's MCN, copied into child_fit)
     int32_t slots = 0;
     bool objective_mcn = false;

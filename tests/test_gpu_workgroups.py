@@ -139,20 +139,24 @@ def test_children_bred_in_place_follow_the_oracle(gp, kind, n, k, P, lam, object
 ])
 def test_generations_of_one_call_follow_the_oracle(gp, kind, n, k, P, lam, objective):
     """Calls of one, two and more generations, in every parity, the children's
-    buffers swapped in between; timing on for one call."""
+    buffers swapped in between; timing on for one call, some recorded."""
     g = graph_of(kind, n)
     print(f"{kind} n={n} k={k} P={P} lambda={lam} {objective}", flush=True)
-    ga = gp.GA(gp.Graph.from_csr(g), k, P, 22, 0.6, 0.1, 2, lam, objective=objective)
+    graph = gp.Graph.from_csr(g)
+    ga, replayed = (gp.GA(graph, k, P, 22, 0.6, 0.1, 2, lam, replay=r, objective=objective) for r in (False, True))
     oga = O.OracleGA(g, k, P, 22, 0.6, 0.1, 2, lam, objective=objective)
-    for steps, timing in ((2, 0), (1, 0), (3, 0), (5, 0), (2, 1), (4, 0)):
-        ga.set_timing(timing)
-        ga.step(steps)
+    for steps, timing in ((2, 0), (1, 0), (3, 0), (5, 0), (2, 1), (4, 0), (5, 0), (5, 0)):
+        if steps == 5:
+            replayed.record(5)
         for _ in range(steps):
             oga.step()
-        pop, F = ga.population()
-        assert np.array_equal(F, oga.F) and np.array_equal(pop, oga.pop), steps
-        genes, f, gens = ga.best()
-        assert gens == oga.generation and f == oga.F[0] and np.array_equal(genes, oga.pop[0])
+        for x in (ga, replayed):
+            x.set_timing(timing)
+            x.step(steps)
+            pop, F = x.population()
+            assert np.array_equal(F, oga.F) and np.array_equal(pop, oga.pop), steps
+            genes, f, gens = x.best()
+            assert gens == oga.generation and f == oga.F[0] and np.array_equal(genes, oga.pop[0])
 
 
 @pytest.mark.parametrize("kinds", [
