@@ -697,8 +697,12 @@ static int copy_back(gapa_graph *g, const int32_t *flag, int32_t hflag[4], const
 {
     const size_t nf = fitness ? (size_t)P * 8 : 0, nm = mcn ? (size_t)P * 4 : 0;
     if (16 + nf + nm <= Mailbox::kBytes && g->mail.open()) {
-        const int rc = mail_collect(g->mail, {flag, 16}, {d_fit, nf}, {d_mcn, nm}, s);
+        // (the graph's own flag is left clear for the next call)
+        const bool own = flag == g->ws.flag.ptr;
+        const int rc = mail_collect(g->mail, {flag, 16}, {d_fit, nf}, {d_mcn, nm}, s,
+                                    own ? g->ws.flag.as<uint32_t>() : nullptr);
         if (rc != GAPA_OK) return rc;
+        if (own) g->flag_clear = true;
         std::memcpy(hflag, g->mail.host, 16);
         if (nf) std::memcpy(fitness, g->mail.host + 16, nf);
         if (nm) std::memcpy(mcn, g->mail.host + 16 + nf, nm);
@@ -778,9 +782,12 @@ int gapa_eval_population(gapa_graph *g, const int32_t *genes, int32_t P, int32_t
         d_mcn = want_mcn ? w.mcn.as<int32_t>() : nullptr;
     }
     // (nobody reads the gene flag of trusted device rows: without the launch that
-    // clears it, n = 200, P = 32 takes 9.5 us a call instead of 13.0)
+    // clears it, n = 200, P = 32 takes 9.5 us a call instead of 13.0; other calls
+    // find it clear, or clear it, and may leave it set until it is read)
     const bool check = !(dev_ptrs && trust);
-    if (check && (rc = launch_fill_u32(w.flag.ptr, 0u, 4, s)) != GAPA_OK) return fail_handle(&g->failed, rc);
+    if (check && !g->flag_clear && (rc = launch_fill_u32(w.flag.ptr, 0u, 4, s)) != GAPA_OK)
+        return fail_handle(&g->failed, rc);
+    g->flag_clear = false;
     if ((rc = eval_genes(g, d_genes, P, k, d_fit, d_mcn, w.flag.as<int32_t>(), w, &g->timer, s, measure)) !=
         GAPA_OK)
         return fail_handle(&g->failed, rc);
@@ -941,6 +948,7 @@ int gapa_sixdst_eval(gapa_graph *g, const int32_t *genes, int32_t P, int32_t k, 
         d_pc = w.fitness.as<int64_t>();
         d_mcn = w.mcn.as<int32_t>();
     }
+    g->flag_clear = false;
     if (sparse) {
         if ((rc = sixdst_eval_genes(g, d_genes, P, k, hops, d_pc, d_mcn, w.flag.as<int32_t>(), s)) != GAPA_OK)
             return fail_handle(&g->failed, rc);

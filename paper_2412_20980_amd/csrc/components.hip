@@ -31,12 +31,12 @@
 // and takes 8 us for n = 30k, of 34 (random graph of mean degree 8, three
 // sweeps) or 20 us (BA, m = 3, two) for the whole evaluation of one individual;
 // eight individuals in a byte cost a block 1.4 times one.  Whole calls against
-// the bit-parallel pass: n = 200, P = 32: 13 against 53 us; BA n = 10k: P = 256
-// 17 against 78 us, P = 2048 30 against 133; random graph n = 30k: P = 203 35
-// us against 2.5 ms (few individuals leave that pass a large union-find around
-// the roots), P = 2048 46 against 138 us; power law n = 65k: P = 256 50 against
-// 114 us, P = 2048 118 against 179; 32 graphs of 1000 to 50,000 nodes, 128
-// individuals each: 98 against 200 us, bound by the largest graphs' blocks.
+// the bit-parallel pass: n = 200, P = 32: 9.7 against 53 us; BA n = 10k: P = 256
+// 16 against 78 us, P = 2048 28 against 133; random graph n = 30k: P = 203 34
+// us against 2.4 ms (few individuals left that pass a large union-find around
+// the roots), P = 2048 44 against 136 us; power law n = 65k: P = 256 48 against
+// 115 us, P = 2048 116 against 179; 32 graphs of 1000 to 50,000 nodes, 128
+// individuals each: 82 against 200 us, bound by the largest graphs' blocks.
 // Bits instead of bytes for the states: 1.5 times slower sweeps (ten more
 // instructions a neighbour).  One individual a block whatever the population:
 // n = 30k, P = 2048 336 us.  Pushing on from hubs, too: BA n = 10k 26 instead of

@@ -259,20 +259,25 @@ namespace {
 
 struct MailWords {
     const uint32_t *src[3];
-    int64_t end[3];  // words up to and with each array
+    int64_t end[3];   // words up to and with each array
+    uint32_t *clear;  // NULL, or the first array, to be cleared once copied
 };
 
 __global__ void k_mail(MailWords m, uint32_t *__restrict__ to)
 {
     for (int64_t w = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; w < m.end[2]; w += (int64_t)gridDim.x * blockDim.x)
+    {
         to[w] = w < m.end[0] ? m.src[0][w] : w < m.end[1] ? m.src[1][w - m.end[0]] : m.src[2][w - m.end[1]];
+        if (m.clear && w < m.end[0]) m.clear[w] = 0u;
+    }
 }
 
 }  // namespace
 
-int mail_collect(const Mailbox &mail, MailItem a, MailItem b, MailItem c, hipStream_t s)
+int mail_collect(const Mailbox &mail, MailItem a, MailItem b, MailItem c, hipStream_t s, uint32_t *clear)
 {
     MailWords m;
+    m.clear = clear;
     m.src[0] = static_cast<const uint32_t *>(a.src);
     m.src[1] = static_cast<const uint32_t *>(b.src);
     m.src[2] = static_cast<const uint32_t *>(c.src);

@@ -51,7 +51,7 @@ struct DevBuf {
 // kernels read its inputs and write its results in place, so that a call with
 // host arrays waits once, for its stream, instead of once a copy (a copy from or
 // to ordinary memory is one of 12 to 17 us, whatever its size).  100 rows of 20
-// genes, n = 2018: 34 us a call against 66 by copies; a GA's best individual 14
+// genes, n = 2018: 32 us a call against 66 by copies; a GA's best individual 14
 // against 45, its population of 1000 genes 14 against 46, of 77,000 29 against 56.
 // From 1 MiB on the copies' own staging takes over.
 //
@@ -68,12 +68,13 @@ struct Mailbox {
 };
 
 // Up to three device arrays (bytes a multiple of 4) to the front of the mailbox,
-// one after the other, and waits for them (and all else on the stream).
+// one after the other, and waits for them (and all else on the stream).  clear: the
+// first array again, to be cleared once copied, or NULL.
 struct MailItem {
     const void *src;
     size_t bytes;
 };
-int mail_collect(const Mailbox &m, MailItem a, MailItem b, MailItem c, hipStream_t s);
+int mail_collect(const Mailbox &m, MailItem a, MailItem b, MailItem c, hipStream_t s, uint32_t *clear = nullptr);
 
 // ---------------------------------------------------------------- timing ----
 
@@ -196,6 +197,7 @@ struct gapa_graph {
     gapa::FitnessWorkspace ws;
     gapa::KernelTimer timer;
     gapa::Mailbox mail;
+    bool flag_clear = false;    // ws.flag holds zeros
     bool failed = false;
 };
 
