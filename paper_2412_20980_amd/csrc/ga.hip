@@ -8,8 +8,8 @@
 // (seed, generation, individual, slot), so the result is a pure function of
 // the seed and does not depend on the launch geometry.  The parts that are
 // sequential by definition (rejection draws that depend on the current
-// membership, in ascending slot order) run on one lane over LDS only; their
-// first-attempt draws are computed by the whole block beforehand.
+// membership, in ascending slot order) are resolved by one wave over LDS only;
+// repairs' first-attempt draws are computed by the whole block beforehand.
 //
 // A launch serves one GA or a batch of independent GAs (one per instance
 // graph): blockIdx.y selects the instance, whose sizes, seed and buffer
@@ -24,7 +24,7 @@
 namespace gapa {
 namespace {
 
-constexpr int kOpBlock = 512;
+constexpr int kOpBlock = 512;  // threads of an operator block, at most
 
 // Initial individual i (eq. 2): slot j takes the first INIT draw that is not
 // already in the row; the row is then sorted.
