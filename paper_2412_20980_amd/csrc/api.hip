@@ -70,30 +70,22 @@ void DevBuf::release()
 
 namespace {
 
+// Mailboxes of destroyed handles (trivially destroyed: handles may outlive it).
 struct SpareMail {
     std::mutex mu;
-    std::vector<unsigned char *> boxes;
+    unsigned char *boxes[Mailbox::kSpare];
+    size_t count;
 };
-
-// (never destroyed: handles may outlive the statics)
-SpareMail &spare_mail()
-{
-    static SpareMail *s = new SpareMail;
-    return *s;
-}
+SpareMail g_spare_mail;
 
 }  // namespace
 
 bool Mailbox::open()
 {
     if (!host) {
-        SpareMail &spare = spare_mail();
         {
-            std::lock_guard<std::mutex> lock(spare.mu);
-            if (!spare.boxes.empty()) {
-                host = spare.boxes.back();
-                spare.boxes.pop_back();
-            }
+            std::lock_guard<std::mutex> lock(g_spare_mail.mu);
+            if (g_spare_mail.count > 0) host = g_spare_mail.boxes[--g_spare_mail.count];
         }
         if (!host && hipHostMalloc(reinterpret_cast<void **>(&host), kBytes,
                                    hipHostMallocMapped | hipHostMallocPortable | hipHostMallocCoherent) != hipSuccess) {
@@ -115,12 +107,9 @@ void Mailbox::close()
     if (!host) return;
     bool kept = false;
     {
-        SpareMail &spare = spare_mail();
-        std::lock_guard<std::mutex> lock(spare.mu);
-        if (spare.boxes.size() < kSpare) {
-            spare.boxes.push_back(host);
-            kept = true;
-        }
+        std::lock_guard<std::mutex> lock(g_spare_mail.mu);
+        kept = g_spare_mail.count < kSpare;
+        if (kept) g_spare_mail.boxes[g_spare_mail.count++] = host;
     }
     if (!kept) (void)hipHostFree(host);
     host = dev = nullptr;
