@@ -640,13 +640,19 @@ __global__ void k_pull_worklist(const int4 *__restrict__ worklist, const int32_t
 // last look; no block waits for another.
 //
 // Random graphs, n = 200k, a pass without and with the rounds: mean degree 8,
-// 32 individuals 7.6 and 0.26 ms, 203 1.4 and 0.27, 2048 0.34 both ways (the
+// 32 individuals 7.6 and 0.17 ms, 203 1.4 and 0.22, 2048 0.34 both ways (the
 // sweeps leave nothing there; the sampled count of pending nodes ends the launch
 // at once, where running it for whatever the last sweep changed took 10 us);
-// mean degree 4, 203 individuals 10.6 and 0.54, 1024 25.7 and 0.61.  Small world
-// of 100k nodes 2.4 and 0.35 (32 individuals; 1.7 when one gain in 128 nodes was
-// asked of a round).  Lattices and paths stop after a few rounds.
-constexpr int kRoundBlocks = 2048;  // all resident at once
+// mean degree 4, 203 individuals 10.2 and 0.36, 1024 24 and 0.59.  Small world
+// of 100k nodes, 256 individuals 7.5 and 0.39.  Lattices and paths stop after
+// rounds that cost what they save, or a little less.
+//
+// A quarter of the chip's waves, and an eighth for one or two words a node: nodes
+// that follow one another in a wave pass bits on within a round, which nodes
+// pulled at the same time do not (mean degree 4: 203 individuals 0.56 ms with all
+// waves, 0.36 with a quarter, 0.41 with an eighth; mean degree 8, 32 individuals
+// 0.25, 0.20 and 0.17).
+constexpr int kRoundBlocks = 512;
 constexpr int kRounds = 256, kFirstRounds = 3;
 constexpr int kGainSlot = 40;       // of the pass's counters: nodes that gained a bit, over all blocks and rounds
 constexpr int kPendingSlot = 41;    // and: nodes the last sweep's sampled blocks left pending
@@ -1177,9 +1183,9 @@ int run_pass(gapa_graph *g, FitnessWorkspace &ws, const PassShape &sh, const Ins
                                        g->d_colD, dead, reach, changed, sw, flags, nullptr);
             }
             if (rounds)
-                hipLaunchKernelGGL(k_pull_rounds, dim3(kRoundBlocks), dim3(kBlk), 0, s, worklist, wl_count, Wd,
-                                   g->d_colD, dead, reach, ctr + kPendingSlot, ctr + kGainSlot,
-                                   ws.pflag.as<uint8_t>());
+                hipLaunchKernelGGL(k_pull_rounds, dim3(Wd <= 2 ? kRoundBlocks / 2 : kRoundBlocks), dim3(kBlk), 0, s,
+                                   worklist, wl_count, Wd, g->d_colD, dead, reach, ctr + kPendingSlot,
+                                   ctr + kGainSlot, flags);
         }
         {
             TimedScope ts(timer, "k_collect_pairs", s);
