@@ -470,7 +470,7 @@ GAPA_API int gapa_ga_fitness_stats(gapa_ga *ga, int64_t out[4]);
  *   band_scan    neighbours a node reads in the ordered sweep, >= 1
  *   sweeps       follow-up sweeps over the nodes still pending, 0..32
  *   band_blocks  block cap of one band launch, 1..65535
- * Defaults 4096, 32, 3, 8192.  A change also applies to GAs and batches on
+ * Defaults 2048, 32, 3, 2048.  A change also applies to GAs and batches on
  * the graph (recorded generations are re-recorded). */
 typedef struct gapa_tuning {
     int32_t sweep_grid;

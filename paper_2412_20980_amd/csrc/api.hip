@@ -325,9 +325,11 @@ constexpr int kSources = 64;
 constexpr int kMaxBands = 24;
 constexpr int kMinBand = 16384;  // at n = 200k the 8.9k nodes of BFS levels 3+ join level 2's band: 2 % faster
 
-// Nine nodes in ten within three hops of the sources: graphs with hubs (power laws
-// of mean degree 6 and 10, BA with m = 2: 85 to 99 % at n = 100k and 200k); not:
-// random graphs of mean degree 4 to 8 (8 to 69 %), lattices.
+// Nine nodes in ten within three hops of the sources: graphs with hubs (at n = 100k
+// and 200k power laws of mean degree 6 to 10 and BA with m = 2 to 4: 93 to 100 %);
+// not: random graphs of mean degree 4 to 8 (8 to 69 %), lattices.  On BA with m = 2
+// the rounds would take 32 individuals from 0.96 to 0.15 ms (n = 100k, the hubs
+// removed), but 1024 from 0.20 to 0.27.
 constexpr int kFarLevel = 4;
 
 // Also returns each source's index among its instance's sources (the t-th
@@ -390,7 +392,7 @@ void graph_orderings(int32_t n, const int32_t *rp, const int32_t *ci, const std:
     for (int32_t v = 0; v < n; ++v)
         if (deg[v] > 0) ++lev_count[level[v]];
     for (int32_t l = 0; l < nlev; ++l) lev_first[l + 1] = lev_first[l] + lev_count[l];
-    far = nlev > kFarLevel && lev_first[kFarLevel] < 9 * (int64_t)lev_first[nlev] / 10;
+    far = nlev > kFarLevel && 10 * (int64_t)lev_first[kFarLevel] < 9 * (int64_t)lev_first[nlev];
     band_v.resize(lev_first[nlev]);
     for (int32_t v = 0; v < n; ++v)
         if (deg[v] > 0) band_v[lev_first[level[v]]++] = v;

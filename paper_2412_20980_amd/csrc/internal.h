@@ -154,11 +154,16 @@ struct FitnessWorkspace {
 
 // Launch shapes of the bit-parallel fitness pass (results do not depend on
 // them; only speed does).
+// (The defaults against a grid of 4096 and bands of 8192 blocks: power law n =
+// 200k, P = 1024, uniform rows 148 us a pass against 175, hub rows 191 and 202; P =
+// 32 86 and 92; BA m = 3 165 and 186; random graph of mean degree 8 222 and 240; two
+// sweeps or 16 neighbours are up to 5 % faster on these and ten times slower
+// without hubs, or 20 % on BA with m = 2.)
 struct Tuning {
-    int32_t sweep_grid = 4096;   // blocks of the worklist, pair and union-find kernels
+    int32_t sweep_grid = 2048;   // blocks of the worklist, pair and union-find kernels
     int32_t band_scan = 32;      // neighbours read per node in the ordered sweep
     int32_t sweeps = 3;          // follow-up sweeps over the pending nodes
-    int32_t band_blocks = 8192;  // block cap of one band launch
+    int32_t band_blocks = 2048;  // block cap of one band launch
 };
 
 }  // namespace gapa

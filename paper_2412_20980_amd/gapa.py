@@ -334,7 +334,7 @@ class Graph:
         _check(lib().gapa_graph_get_tuning(self.handle, C.byref(t)))
         return {f: getattr(t, f) for f, _ in t._fields_}
 
-    def set_tuning(self, sweep_grid=4096, band_scan=32, sweeps=3, band_blocks=8192):
+    def set_tuning(self, sweep_grid=2048, band_scan=32, sweeps=3, band_blocks=2048):
         t = gapa_tuning(sweep_grid=sweep_grid, band_scan=band_scan, sweeps=sweeps, band_blocks=band_blocks)
         _check(lib().gapa_graph_set_tuning(self.handle, C.byref(t)))
 
@@ -625,7 +625,7 @@ class Batch:
         _check(lib().gapa_batch_get_tuning(self.handle, C.byref(t)))
         return {f: getattr(t, f) for f, _ in t._fields_}
 
-    def set_tuning(self, sweep_grid=4096, band_scan=32, sweeps=3, band_blocks=8192):
+    def set_tuning(self, sweep_grid=2048, band_scan=32, sweeps=3, band_blocks=2048):
         t = gapa_tuning(sweep_grid=sweep_grid, band_scan=band_scan, sweeps=sweeps, band_blocks=band_blocks)
         _check(lib().gapa_batch_set_tuning(self.handle, C.byref(t)))
 
