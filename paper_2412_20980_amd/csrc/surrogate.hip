@@ -18,6 +18,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <type_traits>
 #include <vector>
 
 #include "device_common.h"
@@ -172,46 +173,50 @@ __global__ void k_snapshot(SnapArgs a)
 
 // ------------------------------------------------------------- embedding ----
 
-// x(S) of each row, rounded to bf16: one 128-thread block per row.  Lane
-// (wave w, group g = lane / 8, q = lane % 8) adds dims 8q..8q+7 of genes
-// j = 16 i + 8 w + g in ascending i; the groups are then added in fours and
-// the fours one after the other.  The row's gene ids are staged in LDS
-// (kEmbedIds at a time, coalesced), so each lane keeps kEmbedUnroll
-// embedding rows in flight without waiting on their ids.
+// x(S) of each row, rounded to bf16: one block per row.  kLanes lanes (8 or 16)
+// share an embedding row, so a wave takes 64 / kLanes genes at a time and the
+// block's 16 kLanes threads 16: lane q of group r of the block adds its slice of
+// genes j = 16 i + r in ascending i; the groups are then added in fours and the
+// fours one after the other (either way the same additions in the same order).
+// The row's gene ids are staged in LDS (kEmbedIds at a time, coalesced), so
+// each lane keeps kEmbedUnroll embedding rows in flight without waiting on
+// their ids.
 //
-// Bound by L2: 262 MB of embedding rows for 1024 sets of 2000 nodes at
-// 11.9 TB/s, 22.0 us (26.4 with 8 bytes a lane and 256 threads a row, the
-// instructions around the loads being as many; 22.3 with two rows a block; 24.5
-// with 16 embedding rows in flight a lane, 24.8 with 4).
-constexpr int kEmbedIds = 2048;  // a multiple of 16: a chunk keeps each lane's residue j mod 16
-constexpr int kEmbedUnroll = 8;
-
+// Many rows are bound by L2 and take 16 bytes a lane: 262 MB of embedding rows
+// for 1024 sets of 2000 nodes at 11.9 TB/s, 22.0 us (26.4 with 8 bytes a lane,
+// the instructions around the loads being as many; 22.3 with two rows a block;
+// 24.5 with 16 embedding rows in flight a lane, 24.8 with 4).  Few rows are bound
+// by each lane's chain of additions and take 8: 64 sets of 2000 nodes with their
+// network pass 17.3 us against 19.4, 768 30.1 against 32.1; 1024 38.7 against 34.9.
 //
 // With kMask it also writes the row's removed-node bit set (a gene that is no
-// node is left out), built in LDS (mask [W] words) from the staged ids: 1024 rows of 200 genes, n =
-// 20,011, 7.1 us (5.5 for the sums and 4.3 for a launch of its own); of 2000, n =
-// 200k, 31.7 (24.7 and 10.3).
-constexpr int kEmbedThreads = 128;
+// node is left out), built in LDS (mask [W] words) from the staged ids: 1024 rows
+// of 200 genes, n = 20,011, 7.1 us (5.5 for the sums and 4.3 for a launch of its
+// own); of 2000, n = 200k, 31.7 (24.7 and 10.3).
+constexpr int kEmbedIds = 2048;  // a multiple of 16: a chunk keeps each lane's residue j mod 16
+constexpr int kEmbedUnroll = 8;
+constexpr int kEmbedMany = 1024;  // rows from which a launch takes 16 bytes a lane
 
-template <bool kMask>
-__global__ __launch_bounds__(kEmbedThreads) void k_embed(const int32_t *__restrict__ genes,
-                                                         const int32_t *__restrict__ rows, int32_t k,
-                                                         const uint16_t *__restrict__ Eb, uint16_t *__restrict__ xb,
-                                                         uint32_t *__restrict__ masks, int32_t W, int32_t n)
+template <int kLanes, bool kMask>
+__global__ __launch_bounds__(16 * kLanes) void k_embed(const int32_t *__restrict__ genes,
+                                                       const int32_t *__restrict__ rows, int32_t k,
+                                                       const uint16_t *__restrict__ Eb, uint16_t *__restrict__ xb,
+                                                       uint32_t *__restrict__ masks, int32_t W, int32_t n)
 {
+    constexpr int kDims = kD / kLanes;  // of a lane
+    using Slice = std::conditional_t<kLanes == 8, uint4, uint2>;
     extern __shared__ uint32_t mask[];
     __shared__ float s_part[4][kD];
     __shared__ int32_t s_ids[kEmbedIds];
     const int32_t row = rows ? rows[blockIdx.x] : (int32_t)blockIdx.x;
     const int32_t *g = genes + (int64_t)row * k;
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int grp = lane >> 3, q = lane & 7;
-    const int32_t r = 8 * wv + grp;
-    float a[8] = {};
-    auto add = [&](const uint4 e) {
-        const uint32_t w[4] = {e.x, e.y, e.z, e.w};
+    const int32_t r = threadIdx.x / kLanes, q = threadIdx.x % kLanes;
+    float a[kDims] = {};
+    auto slice = [&](int32_t v) { return *reinterpret_cast<const Slice *>(Eb + (int64_t)v * kD + kDims * q); };
+    auto add = [&](const Slice &e) {
+        const uint32_t *w = reinterpret_cast<const uint32_t *>(&e);
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
+        for (int c = 0; c < kDims / 2; ++c) {
             a[2 * c] += bf2f((uint16_t)w[c]);
             a[2 * c + 1] += bf2f((uint16_t)(w[c] >> 16));
         }
@@ -230,31 +235,45 @@ __global__ __launch_bounds__(kEmbedThreads) void k_embed(const int32_t *__restri
         __syncthreads();
         int32_t j = r;
         for (; j + 16 * (kEmbedUnroll - 1) < cn; j += 16 * kEmbedUnroll) {
-            uint4 e[kEmbedUnroll];
+            Slice e[kEmbedUnroll];
 #pragma unroll
-            for (int u = 0; u < kEmbedUnroll; ++u)
-                e[u] = *reinterpret_cast<const uint4 *>(Eb + (int64_t)s_ids[j + 16 * u] * kD + 8 * q);
+            for (int u = 0; u < kEmbedUnroll; ++u) e[u] = slice(s_ids[j + 16 * u]);
 #pragma unroll
             for (int u = 0; u < kEmbedUnroll; ++u) add(e[u]);
         }
-        for (; j < cn; j += 16) add(*reinterpret_cast<const uint4 *>(Eb + (int64_t)s_ids[j] * kD + 8 * q));
+        for (; j < cn; j += 16) add(slice(s_ids[j]));
     }
     if constexpr (kMask)
         for (int32_t x = threadIdx.x; x < W; x += blockDim.x) masks[(int64_t)blockIdx.x * W + x] = mask[x];
 #pragma unroll
-    for (int c = 0; c < 8; ++c) {
-        a[c] += __shfl_xor(a[c], 8, 64);
-        a[c] += __shfl_xor(a[c], 16, 64);
+    for (int c = 0; c < kDims; ++c) {
+        a[c] += __shfl_xor(a[c], kLanes, 64);
+        a[c] += __shfl_xor(a[c], 2 * kLanes, 64);
     }
-    if ((grp & 3) == 0)
+    if ((r & 3) == 0)
 #pragma unroll
-        for (int c = 0; c < 8; ++c) s_part[2 * wv + (grp >> 2)][8 * q + c] = a[c];
+        for (int c = 0; c < kDims; ++c) s_part[r >> 2][kDims * q + c] = a[c];
     __syncthreads();
     if (threadIdx.x < kD) {
-        const int t = threadIdx.x;
-        const float x = ((s_part[0][t] + s_part[1][t]) + s_part[2][t]) + s_part[3][t];
-        xb[(int64_t)blockIdx.x * kD + t] = f2bf(x);
+        const int d = threadIdx.x;
+        const float x = ((s_part[0][d] + s_part[1][d]) + s_part[2][d]) + s_part[3][d];
+        xb[(int64_t)blockIdx.x * kD + d] = f2bf(x);
     }
+}
+
+// Embedding sums of N rows (those of rows[], or the first N); with masks, their
+// bit sets of W words too.
+int launch_embed(const int32_t *genes, const int32_t *rows, int32_t N, int32_t k, const uint16_t *Eb, uint16_t *xb,
+                 uint32_t *masks, int32_t W, int32_t n, hipStream_t s)
+{
+    const bool many = N >= kEmbedMany;
+    const size_t lds = masks ? (size_t)W * 4 : 0;
+    if (many && masks) hipLaunchKernelGGL((k_embed<8, true>), dim3(N), dim3(128), lds, s, genes, rows, k, Eb, xb, masks, W, n);
+    else if (many) hipLaunchKernelGGL((k_embed<8, false>), dim3(N), dim3(128), lds, s, genes, rows, k, Eb, xb, masks, W, n);
+    else if (masks) hipLaunchKernelGGL((k_embed<16, true>), dim3(N), dim3(256), lds, s, genes, rows, k, Eb, xb, masks, W, n);
+    else hipLaunchKernelGGL((k_embed<16, false>), dim3(N), dim3(256), lds, s, genes, rows, k, Eb, xb, masks, W, n);
+    GAPA_HIP(hipGetLastError());
+    return GAPA_OK;
 }
 
 // ------------------------------------------------------------------- MLP ----
@@ -1263,8 +1282,8 @@ int predict_rows(SurrogateState &st, const int32_t *genes, const int32_t *rows, 
     const uint16_t *Eb = snapshot ? reinterpret_cast<const uint16_t *>(static_cast<char *>(st.snap.ptr) +
                                                                        snap_layout(st.n).eb)
                                   : st.Eb.as<uint16_t>();
-    hipLaunchKernelGGL(k_embed<false>, dim3(N), dim3(kEmbedThreads), 0, s, genes, rows, st.k, Eb, st.xb.as<uint16_t>(),
-                       nullptr, 0, 0);
+    const int rc_embed = launch_embed(genes, rows, N, st.k, Eb, st.xb.as<uint16_t>(), nullptr, 0, 0, s);
+    if (rc_embed != GAPA_OK) return rc_embed;
     MlpArgs a = mlp_args(st, st.xb.as<uint16_t>(), yhat, N, snapshot);
     if (snapshot) {
         a.musd_src = reinterpret_cast<const double *>(static_cast<char *>(st.snap.ptr) + snap_layout(st.n).musd);
@@ -1302,12 +1321,9 @@ int train_step(gapa_ga *ga, const int32_t *genes, const float *target, int32_t B
     // (a bit set that LDS takes beside the ids is built with the embedding sums)
     const size_t mask_lds = (size_t)st.W * 4;
     const bool masked = !pos && mask_lds <= kEmbedMaskLds;
-    if (masked)
-        hipLaunchKernelGGL(k_embed<true>, dim3(B), dim3(kEmbedThreads), mask_lds, s, genes, nullptr, st.k,
-                           st.Eb.as<uint16_t>(), st.xtrain.as<uint16_t>(), st.bmasks.as<uint32_t>(), st.W, st.n);
-    else
-        hipLaunchKernelGGL(k_embed<false>, dim3(B), dim3(kEmbedThreads), 0, s, genes, nullptr, st.k,
-                           st.Eb.as<uint16_t>(), st.xtrain.as<uint16_t>(), nullptr, 0, 0);
+    int rc = launch_embed(genes, nullptr, B, st.k, st.Eb.as<uint16_t>(), st.xtrain.as<uint16_t>(),
+                          masked ? st.bmasks.as<uint32_t>() : nullptr, st.W, st.n, s);
+    if (rc != GAPA_OK) return rc;
     MlpArgs a = mlp_args(st, st.xtrain.as<uint16_t>(), st.ytrain.as<float>(), B);
     a.target = target;
     a.dscale = 2.0f / B;
@@ -1342,7 +1358,6 @@ int train_step(gapa_ga *ga, const int32_t *genes, const float *target, int32_t B
     // their chunk start positions (batches sampled from the buffer), or else
     // the removed-node bit sets of the rows, transposed
     const int32_t Wb = B / 32;
-    int rc = GAPA_OK;
     if (pos) {
         const int32_t nchunks = (st.n + kBitChunk - 1) / kBitChunk;
         hipLaunchKernelGGL(k_batch_bits, dim3(nchunks), dim3(256), (size_t)kBitChunk * Wb * 4, s, genes, st.k, B, pos,

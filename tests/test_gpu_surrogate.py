@@ -84,18 +84,20 @@ def test_forward_matches_oracle(gp, P):
     assert np.max(np.abs(y - ref)) <= 3e-2 * scale
 
 
-@pytest.mark.parametrize("k", [1, 16, 135, 2049, 2200])
-def test_forward_at_row_length_edges(gp, k):
+@pytest.mark.parametrize("k, P", [(1, 33), (16, 33), (135, 33), (2049, 33), (2200, 33), (16, 1023), (16, 1024),
+                                 (135, 1025), (2049, 1024)])
+def test_forward_at_row_length_edges(gp, k, P):
     """Rows of one gene, of one gene a lane group, of a remainder after the
-    unrolled loads, and of more genes than one staged chunk; tolerances as
-    above."""
+    unrolled loads, and of more genes than one staged chunk, on both sides of
+    the number of rows from which a lane reads twice as much of an embedding;
+    tolerances as above."""
     import torch
     g = inputs.barabasi_albert(4500, 2, seed=4)
-    _, ga = make_ga(gp, g, k=k, pop=4, lam=32)
+    _, ga = make_ga(gp, g, k=k, pop=4, lam=max(32, P))
     p = random_weights(np.random.default_rng(k), g.n)
     p["E"] *= np.sqrt(20 / k)
     p = set_weights(ga, p)
-    sets = inputs.random_population(g.n, k, 33, seed=k)
+    sets = inputs.random_population(g.n, k, P, seed=k)
     y = ga.predict(torch.from_numpy(sets).cuda()).cpu().numpy().astype(np.float64)
     ref_b = S.forward(p, sets, bf16_ops=True)["yhat"]
     scale = 1.0 + np.max(np.abs(ref_b))
