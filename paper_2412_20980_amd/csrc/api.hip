@@ -327,10 +327,13 @@ constexpr int kMinBand = 16384;  // at n = 200k the 8.9k nodes of BFS levels 3+ 
 
 // Nine nodes in ten within three hops of the sources: graphs with hubs (at n = 100k
 // and 200k power laws of mean degree 6 to 10 and BA with m = 2 to 4: 93 to 100 %);
-// not: random graphs of mean degree 4 to 8 (8 to 69 %), lattices.  On BA with m = 2
-// the rounds would take 32 individuals from 0.96 to 0.15 ms (n = 100k, the hubs
-// removed), but 1024 from 0.20 to 0.27.
+// not: random graphs of mean degree 4 to 8 (8 to 69 %), lattices.
 constexpr int kFarLevel = 4;
+// Graphs with hubs whose sweeps may still be cut off from them, once the hubs are
+// removed, by long ways through few edges: BA with m = 2 (mean degree 4) is, m = 3
+// and 4 hardly, power laws of mean degree 6 to 10 not; those would pay 2 to 4 us a
+// pass for the closed gate of a launch they have no use for.
+constexpr int kSparseDegree = 5;
 
 // Also returns each source's index among its instance's sources (the t-th
 // source is order[voff[b] + t]; -1 for every other node) and, when band 0
@@ -520,6 +523,7 @@ int graph_build(int dev, int32_t n, int64_t nnz, const int32_t *row_ptr, const i
     graph_orderings(n, row_ptr, col_idx, voff, order, colD, band_v, g->band_off, src_idx, g->src_band,
                     g->levels, g->far);
     g->n_noniso = (int32_t)band_v.size();
+    g->sparse = !g->far && (int64_t)nnz <= (int64_t)kSparseDegree * g->n_noniso;
     std::vector<uint32_t> noniso_bits((size_t)g->words, 0u);
     for (int32_t v = 0; v < n; ++v)
         if (row_ptr[v + 1] > row_ptr[v]) noniso_bits[v >> 5] |= 1u << (v & 31);

@@ -462,18 +462,24 @@ __device__ __forceinline__ PullOut pull_node_rt(const int4 r, int Wd, int w, uin
     return out;
 }
 
+// What a sweep counts, and one block in how many does (each wave adds to the one
+// counter: with one block in 16 for the gains, 10 us of 160 at 8 words a node).
+constexpr int kCountPending = 1, kCountGains = 2;
+constexpr int kPendingSample = 16, kGainsSample = 64;
+constexpr int sample_step(int count) { return count == kCountGains ? kGainsSample : kPendingSample; }
+
 // The sweep loop of pull_sweep around pull_node_rt, for the worklist.
 // pflag[i] (worklist position i; pflag may be NULL): written after each
 // pull, 1 while the node has bits pending; read (read_flags) so that settled
 // nodes are skipped without loading their rows (a node's reach row changes
 // only by its own pull, so a settled node stays settled).
-// pending (with kCount): nodes this thread's group left pending (its first lane's
-// count).
-template <bool kCount>
+// counted (with kCount): nodes this thread's group left pending, or that gained a
+// bit (its first lane's count).
+template <int kCount>
 __device__ __forceinline__ bool pull_sweep_rt(const int4 *__restrict__ recs, int32_t count, int32_t Wd,
                                               const int32_t *__restrict__ colD, const uint32_t *__restrict__ dead,
                                               uint32_t *__restrict__ reach, int32_t max_scan,
-                                              uint8_t *__restrict__ pflag, bool read_flags, int32_t &pending)
+                                              uint8_t *__restrict__ pflag, bool read_flags, int32_t &counted)
 {
     const int lane = threadIdx.x & 63;
     const int w = lane & (Wd - 1);
@@ -487,7 +493,8 @@ __device__ __forceinline__ bool pull_sweep_rt(const int4 *__restrict__ recs, int
             const int4 r = recs[idx];
             if (pflag && read_flags && !pflag[idx]) continue;
             const PullOut o = pull_node_rt(r, Wd, w, gmask, colD, dead, reach, max_scan);
-            if constexpr (kCount) pending += w == 0 && o.pending;
+            if constexpr (kCount == kCountPending) counted += w == 0 && o.pending;
+            if constexpr (kCount == kCountGains) counted += w == 0 && o.gained;
             any_gain |= o.gained;
             if (pflag && w == 0) pflag[idx] = o.pending ? 1 : 0;
         }
@@ -604,10 +611,9 @@ __global__ __launch_bounds__(kBlk) void k_collect_pending(const uint8_t *__restr
 
 // Further sweeps over the worklist; sweep s runs only if sweep s - 1 changed
 // something (changed[s - 1] != 0; changed[0] is set by the caller).  With
-// kCount, one block in kPendingSample adds the nodes it leaves pending to sample.
-constexpr int kPendingSample = 16;
-
-template <bool kCount>
+// kCount, one block in sample_step adds the nodes it leaves pending, or those that
+// gained a bit, to sample.
+template <int kCount>
 __global__ void k_pull_worklist(const int4 *__restrict__ worklist, const int32_t *__restrict__ wl_count,
                                 int32_t Wd, const int32_t *__restrict__ colD, const uint32_t *__restrict__ dead,
                                 uint32_t *__restrict__ reach, int32_t *__restrict__ changed, int32_t s,
@@ -615,14 +621,14 @@ __global__ void k_pull_worklist(const int4 *__restrict__ worklist, const int32_t
 {
     if (ld_relaxed(changed + s - 1) == 0) return;
     const int32_t count = ld_relaxed(wl_count);
-    int32_t pending = 0;
+    int32_t counted = 0;
     // with flags (pflag not NULL) the first sweep writes every worklist
     // position's flag, later ones skip the nodes it (or they) left settled
-    const bool any_gain = pull_sweep_rt<kCount>(worklist, count, Wd, colD, dead, reach, INT_MAX, pflag, s > 1, pending);
-    if constexpr (kCount) {
-        if (blockIdx.x % kPendingSample == 0) {
-            pending = wave_sum(pending);
-            if ((threadIdx.x & 63) == 0 && pending) atomicAdd(sample, pending);
+    const bool any_gain = pull_sweep_rt<kCount>(worklist, count, Wd, colD, dead, reach, INT_MAX, pflag, s > 1, counted);
+    if constexpr (kCount != 0) {
+        if (blockIdx.x % sample_step(kCount) == 0) {
+            counted = wave_sum(counted);
+            if ((threadIdx.x & 63) == 0 && counted) atomicAdd(sample, counted);
         }
     }
     // one flag for the whole grid: set it with a plain store, and only if no
@@ -647,6 +653,17 @@ __global__ void k_pull_worklist(const int4 *__restrict__ worklist, const int32_t
 // of 100k nodes, 256 individuals 7.5 and 0.39.  Lattices and paths stop after
 // rounds that cost what they save, or a little less.
 //
+// Graphs with hubs but few edges (gapa_graph::sparse), once their hubs are removed,
+// end the sweeps in the same way; there the launch goes on where half of the
+// worklist gained a bit in the last sweep:
+// nodes left pending are no sign, as they may be parts that no root reaches.  BA
+// with m = 2, n = 100k, 64 individuals of 2500 nodes: nine in ten hubs (0.93 of the
+// worklist gained) 938 us without, 194 with; four in ten (0.87) 506 and 160; none
+// (0.61) 238 and 130; n = 200k, 5000 nodes, four in ten (0.47) 188 and 204, kept
+// out.  203 individuals, nine in ten (0.95) 615 and 270.  A closed gate costs 2 to
+// 4 us.  From 16 words on the sweeps do the work: n = 100k, 1024 individuals 301
+// and 369, n = 200k, 500 individuals 335 and 343, though n = 70k, 500 400 and 269.
+//
 // A quarter of the chip's waves, and an eighth for one or two words a node: nodes
 // that follow one another in a wave pass bits on within a round, which nodes
 // pulled at the same time do not (mean degree 4: 203 individuals 0.56 ms with all
@@ -655,19 +672,20 @@ __global__ void k_pull_worklist(const int4 *__restrict__ worklist, const int32_t
 constexpr int kRoundBlocks = 512;
 constexpr int kRounds = 256, kFirstRounds = 3;
 constexpr int kGainSlot = 40;       // of the pass's counters: nodes that gained a bit, over all blocks and rounds
-constexpr int kPendingSlot = 41;    // and: nodes the last sweep's sampled blocks left pending
+constexpr int kSampleSlot = 41;     // and: nodes the last sweep's sampled blocks left pending, or let gain a bit
+constexpr int kSparseWords = 8;     // sparse graphs: words a node up to which the launch is made
 
 __global__ __launch_bounds__(kBlk) void k_pull_rounds(const int4 *__restrict__ worklist,
                                                       const int32_t *__restrict__ wl_count, int32_t Wd,
                                                       const int32_t *__restrict__ colD,
                                                       const uint32_t *__restrict__ dead, uint32_t *__restrict__ reach,
-                                                      const int32_t *__restrict__ pending, int32_t *__restrict__ gains,
-                                                      uint8_t *__restrict__ pflag)
+                                                      const int32_t *__restrict__ sample, int32_t part,
+                                                      int32_t *__restrict__ gains, uint8_t *__restrict__ pflag)
 {
     __shared__ int32_t s_gain, s_open, s_go;
     const int32_t count = ld_relaxed(wl_count);
-    // (the last sweep's sampled blocks found few nodes pending)
-    if (ld_relaxed(pending) < count / (128 * kPendingSample)) return;
+    // (the last sweep's sampled blocks counted fewer than one node in `part`)
+    if (ld_relaxed(sample) < count / part) return;
     const int lane = threadIdx.x & 63;
     const int w = lane & (Wd - 1);
     const uint64_t gmask = group_mask(Wd);
@@ -1173,19 +1191,20 @@ int run_pass(gapa_graph *g, FitnessWorkspace &ws, const PassShape &sh, const Ins
         {
             TimedScope ts(timer, "k_pull_worklist", s);
             uint8_t *flags = settled_flags ? ws.pflag.as<uint8_t>() : nullptr;
-            const bool rounds = g->far && settled_flags;
+            const bool rounds = settled_flags && (g->far || (g->sparse && Wd <= kSparseWords));
             for (int32_t sw = 1; sw <= tu.sweeps; ++sw) {
                 if (rounds && sw == tu.sweeps)
-                    hipLaunchKernelGGL(k_pull_worklist<true>, dim3(grid), dim3(kBlk), 0, s, worklist, wl_count, Wd,
-                                       g->d_colD, dead, reach, changed, sw, flags, ctr + kPendingSlot);
+                    hipLaunchKernelGGL(g->far ? k_pull_worklist<kCountPending> : k_pull_worklist<kCountGains>,
+                                       dim3(grid), dim3(kBlk), 0, s, worklist, wl_count, Wd, g->d_colD, dead, reach,
+                                       changed, sw, flags, ctr + kSampleSlot);
                 else
-                    hipLaunchKernelGGL(k_pull_worklist<false>, dim3(grid), dim3(kBlk), 0, s, worklist, wl_count, Wd,
+                    hipLaunchKernelGGL(k_pull_worklist<0>, dim3(grid), dim3(kBlk), 0, s, worklist, wl_count, Wd,
                                        g->d_colD, dead, reach, changed, sw, flags, nullptr);
             }
             if (rounds)
                 hipLaunchKernelGGL(k_pull_rounds, dim3(Wd <= 2 ? kRoundBlocks / 2 : kRoundBlocks), dim3(kBlk), 0, s,
-                                   worklist, wl_count, Wd, g->d_colD, dead, reach, ctr + kPendingSlot,
-                                   ctr + kGainSlot, flags);
+                                   worklist, wl_count, Wd, g->d_colD, dead, reach, ctr + kSampleSlot,
+                                   g->far ? 128 * kPendingSample : 2 * kGainsSample, ctr + kGainSlot, flags);
         }
         {
             TimedScope ts(timer, "k_collect_pairs", s);

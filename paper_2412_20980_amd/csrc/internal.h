@@ -196,6 +196,7 @@ struct gapa_graph {
     int32_t list_chunks = 0;
     int32_t n_hub = 0;          // nodes of more than kHubDegree neighbours
     bool far = false;           // most nodes are kFarLevel hops or more from every high-degree node
+    bool sparse = false;        // not far, but kSparseDegree neighbours or fewer a node that has any
     int32_t algorithm = 0;      // 0: bit-parallel sweeps, 1: edge-parallel union-find
     gapa::Tuning tune;
     int32_t tune_version = 0;   // bumped by every tuning change (recorded graphs are re-recorded)

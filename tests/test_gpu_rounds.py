@@ -70,3 +70,22 @@ def test_ga_and_batch_match_oracle(gp):
         batch.step(1)
         for r in refs:
             r.step()
+
+
+@pytest.mark.parametrize("P", [1, 33, 128, 129, 256, 257])
+@pytest.mark.parametrize("hubs", [0.0, 0.9])
+def test_sparse_graph_with_hubs_matches_oracle(gp, hubs, P):
+    # rounds where the sweeps still gain (hubs removed), none where they do not;
+    # one to eight words a node, and sixteen (no such launch)
+    import torch
+    g = inputs.barabasi_albert(70_000, 2, seed=6)
+    rows = inputs.hub_biased_population(g, 900, P, seed=P, hub_frac=hubs) if hubs else \
+        inputs.random_population(g.n, 900, P, seed=P)
+    print(f"hubs={hubs} P={P}", flush=True)
+    graph = gp.Graph.from_csr(g)
+    fit, mcn = graph.eval(rows, want_mcn=True)
+    ref, ref_mcn = O.eval_population(g, rows, want_mcn=True)
+    assert np.array_equal(fit, ref) and np.array_equal(mcn, ref_mcn)
+    d = torch.from_numpy(rows).cuda()
+    f = gp.gapa_eval_population_noalloc(graph.handle, d)
+    assert np.array_equal(f.cpu().numpy(), ref)
