@@ -144,7 +144,8 @@ GAPA_API int gapa_eval_population(gapa_graph *g, const int32_t *genes, int32_t P
  *
  * Every buffer the evaluation needs comes from a fixed scratch array of
  * GAPA_NOALLOC_SCRATCH_BYTES that the library holds on every GPU it runs on
- * from the library's load to the end of the process.  Larger graphs than one
+ * from the library's load to the end of the process; the gene check comes back
+ * through page-locked words taken with the first graph made.  Larger graphs than one
  * workgroup's LDS holds (more than 65 535 nodes; or 18 000 if the longest
  * shortest paths are of dozens of hops) are evaluated in chunks of 32 Wd
  * individuals, Wd the largest power of two <= 32

@@ -115,6 +115,35 @@ void Mailbox::close()
     host = dev = nullptr;
 }
 
+// Where the gene check of the allocation-free entry point comes back: 64 bytes a
+// device (its calls on one device share the scratch, and so do not overlap) of one
+// page that is page-locked with the first graph made, as that call may not, and
+// kept to the end of the process, as the scratch is.
+static Mailbox check_slot(int device)
+{
+    constexpr size_t kSlot = 64, kSlots = 64;
+    static std::mutex mu;
+    static unsigned char *page = nullptr;
+    Mailbox m;
+    if (device < 0 || device >= (int)kSlots) return m;
+    std::lock_guard<std::mutex> lock(mu);
+    if (!page && hipHostMalloc(reinterpret_cast<void **>(&page), kSlot * kSlots,
+                               hipHostMallocMapped | hipHostMallocPortable | hipHostMallocCoherent) != hipSuccess) {
+        (void)hipGetLastError();
+        page = nullptr;
+    }
+    void *d = nullptr;
+    if (page && hipHostGetDevicePointer(&d, page, 0) != hipSuccess) {
+        (void)hipGetLastError();
+        d = nullptr;
+    }
+    if (d) {
+        m.host = page + device * kSlot;
+        m.dev = static_cast<unsigned char *>(d) + device * kSlot;
+    }
+    return m;
+}
+
 // ------------------------------------------------------------------ timer ----
 
 hipEvent_t KernelTimer::take()
@@ -675,8 +704,10 @@ int gapa_graph_create(int32_t n, int64_t nnz, const int32_t *row_ptr, const int3
     if (!(flags & GAPA_TRUST_INPUT)) API_TRY(validate_graph(n, nnz, row_ptr, col_idx));
     int dev = 0;
     API_TRY(check_device(&dev));
-    return graph_build(dev, n, nnz, row_ptr, col_idx, std::vector<int32_t>{0, n}, (flags & GAPA_UNIONFIND) ? 1 : 0,
-                       out);
+    API_TRY(graph_build(dev, n, nnz, row_ptr, col_idx, std::vector<int32_t>{0, n}, (flags & GAPA_UNIONFIND) ? 1 : 0,
+                        out));
+    (*out)->check = check_slot(dev);
+    return GAPA_OK;
 }
 
 int gapa_graph_destroy(gapa_graph *g)
@@ -685,22 +716,22 @@ int gapa_graph_destroy(gapa_graph *g)
     return GAPA_OK;
 }
 
-// The gene flag to hflag and, with host arrays, P results to them; waits for the
-// stream.
-static int copy_back(gapa_graph *g, const int32_t *flag, int32_t hflag[4], const int64_t *d_fit, int64_t *fitness,
-                     const int32_t *d_mcn, int32_t *mcn, int32_t P, hipStream_t s)
+// The gene flag to hflag and, with host arrays, P results to them, through mail
+// unless that is NULL or too small; waits for the stream.
+static int copy_back(gapa_graph *g, const Mailbox *mail, const int32_t *flag, int32_t hflag[4], const int64_t *d_fit,
+                     int64_t *fitness, const int32_t *d_mcn, int32_t *mcn, int32_t P, hipStream_t s)
 {
     const size_t nf = fitness ? (size_t)P * 8 : 0, nm = mcn ? (size_t)P * 4 : 0;
-    if (16 + nf + nm <= Mailbox::kBytes && g->mail.open()) {
+    if (mail && 16 + nf + nm <= Mailbox::kBytes) {
         // (the graph's own flag is left clear for the next call)
         const bool own = flag == g->ws.flag.ptr;
-        const int rc = mail_collect(g->mail, {flag, 16}, {d_fit, nf}, {d_mcn, nm}, s,
+        const int rc = mail_collect(*mail, {flag, 16}, {d_fit, nf}, {d_mcn, nm}, s,
                                     own ? g->ws.flag.as<uint32_t>() : nullptr);
         if (rc != GAPA_OK) return rc;
         if (own) g->flag_clear = true;
-        std::memcpy(hflag, g->mail.host, 16);
-        if (nf) std::memcpy(fitness, g->mail.host + 16, nf);
-        if (nm) std::memcpy(mcn, g->mail.host + 16 + nf, nm);
+        std::memcpy(hflag, mail->host, 16);
+        if (nf) std::memcpy(fitness, mail->host + 16, nf);
+        if (nm) std::memcpy(mcn, mail->host + 16 + nf, nm);
         return GAPA_OK;
     }
     GAPA_HIP(hipMemcpyAsync(hflag, flag, 16, hipMemcpyDeviceToHost, s));
@@ -788,8 +819,8 @@ int gapa_eval_population(gapa_graph *g, const int32_t *genes, int32_t P, int32_t
         return fail_handle(&g->failed, rc);
     if (!check) return GAPA_OK;
     int32_t hflag[4] = {0, 0, 0, 0};
-    if ((rc = copy_back(g, w.flag.as<int32_t>(), hflag, d_fit, dev_ptrs ? nullptr : fitness, d_mcn,
-                        dev_ptrs || !want_mcn ? nullptr : mcn, P, s)) != GAPA_OK)
+    if ((rc = copy_back(g, g->mail.open() ? &g->mail : nullptr, w.flag.as<int32_t>(), hflag, d_fit,
+                        dev_ptrs ? nullptr : fitness, d_mcn, dev_ptrs || !want_mcn ? nullptr : mcn, P, s)) != GAPA_OK)
         return fail_handle(&g->failed, rc);
     if (hflag[0]) {
         set_error("a gene is not a node id in [0, %d)", g->n);
@@ -881,7 +912,8 @@ int gapa_eval_population_noalloc(gapa_graph *g, const int32_t *genes, int32_t P,
     if (rc != GAPA_OK) return fail_handle(&g->failed, rc);
     if (flags & GAPA_TRUST_INPUT) return GAPA_OK;
     int32_t hflag[4] = {0, 0, 0, 0};
-    if ((rc = copy_back(g, flag, hflag, nullptr, nullptr, nullptr, nullptr, 0, s)) != GAPA_OK)
+    if ((rc = copy_back(g, g->check.host ? &g->check : nullptr, flag, hflag, nullptr, nullptr, nullptr, nullptr, 0,
+                        s)) != GAPA_OK)
         return fail_handle(&g->failed, rc);
     if (hflag[0]) {
         set_error("a gene is not a node id in [0, %d)", g->n);
@@ -966,8 +998,8 @@ int gapa_sixdst_eval(gapa_graph *g, const int32_t *genes, int32_t P, int32_t k, 
     }
     if (dev_ptrs && trust) return GAPA_OK;
     int32_t hflag[4] = {0, 0, 0, 0};
-    if ((rc = copy_back(g, w.flag.as<int32_t>(), hflag, d_pc, dev_ptrs ? nullptr : pc, d_mcn, dev_ptrs ? nullptr : mcn,
-                        P, s)) != GAPA_OK)
+    if ((rc = copy_back(g, g->mail.open() ? &g->mail : nullptr, w.flag.as<int32_t>(), hflag, d_pc,
+                        dev_ptrs ? nullptr : pc, d_mcn, dev_ptrs ? nullptr : mcn, P, s)) != GAPA_OK)
         return fail_handle(&g->failed, rc);
     if (hflag[0]) {
         set_error("a gene is not a node id in [0, %d)", g->n);

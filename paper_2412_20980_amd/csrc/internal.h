@@ -203,6 +203,7 @@ struct gapa_graph {
     gapa::FitnessWorkspace ws;
     gapa::KernelTimer timer;
     gapa::Mailbox mail;
+    gapa::Mailbox check;        // its device's slot for the checked allocation-free call (not owned), or empty
     bool flag_clear = false;    // ws.flag holds zeros
     bool failed = false;
 };
