@@ -1081,7 +1081,7 @@ int ga_allocate(gapa_ga *ga, int32_t count, const gapa_params *p, const int32_t 
     ga->hinst.assign(count, GaInst{});
     int64_t pop_el = 0, child_el = 0, mask_w = 0;
     int32_t fit_n = 0, noniso_w = 0, slots = 0;
-    size_t lds = 0, need = 0;
+    size_t lds = 0;
     for (int32_t b = 0; b < count; ++b) {
         GaInst &I = ga->hinst[b];
         const int32_t L = p[b].offspring > 0 ? p[b].offspring : p[b].pop;
@@ -1112,8 +1112,7 @@ int ga_allocate(gapa_ga *ga, int32_t count, const gapa_params *p, const int32_t 
         ga->max_pop = std::max(ga->max_pop, I.P);
         ga->max_lambda = std::max(ga->max_lambda, L);
         ga->max_pop_lambda = std::max(ga->max_pop_lambda, I.P + L);
-        need = std::max(need, ga_op_lds_bytes(n[b], p[b].k));
-        if (need <= kOpLdsMax) lds = std::max(lds, ga_op_lds_layout(n[b], p[b].k, &I.log_q));
+        lds = std::max(lds, ga_op_lds_layout(n[b], p[b].k, &I.log_q));
     }
     if (slot_stride > 0) slots = count * slot_stride;
     ga->op_lds_bytes = lds;
@@ -1121,8 +1120,8 @@ int ga_allocate(gapa_ga *ga, int32_t count, const gapa_params *p, const int32_t 
         set_error("population too large");
         return GAPA_E_INVALID_ARG;
     }
-    if (need > kOpLdsMax) {
-        set_error("n and k need %zu bytes of LDS for the operator kernels (limit 160 KiB)", need);
+    if (lds + kOpStaticLds > kOpLdsMax) {
+        set_error("n and k need %zu bytes of LDS for the operator kernels (limit 160 KiB)", lds + kOpStaticLds);
         return GAPA_E_INVALID_ARG;
     }
     int rc = GAPA_OK;

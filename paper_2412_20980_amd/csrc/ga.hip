@@ -236,27 +236,6 @@ static int32_t op_threads(const gapa_ga *ga)
     return k > 1024 ? kOpBlock : kOpBlock / 2;
 }
 
-size_t ga_op_lds_bytes(int32_t n, int32_t k)
-{
-    const size_t W = ((size_t)n + 31) / 32;
-    const size_t KW = ((size_t)k + 31) / 32;
-    return 4 * (W + (size_t)k + 3 * KW) + 2 * (((size_t)k + 1) & ~(size_t)1);
-}
-
-// Quads of more than four words keep the counts within the room that there is
-// on the largest graphs (more than a million nodes): never more LDS than the
-// limit for sizes that ga_op_lds_bytes lets through.
-size_t ga_op_lds_layout(int32_t n, int32_t k, int32_t *log_q)
-{
-    const size_t W4 = ((size_t)n + 127) / 128, k2 = ((size_t)k + 1) & ~(size_t)1;
-    const size_t fixed = 16 * W4 + 4 * ((size_t)k + 3 * (((size_t)k + 31) / 32));
-    for (*log_q = 2;; ++*log_q) {
-        const size_t quads = (W4 >> (*log_q - 2)) + 1;
-        const size_t bytes = fixed + 2 * std::max(k2, (quads + 1) & ~(size_t)1);
-        if (bytes + 64 <= kOpLdsMax || quads <= k2) return bytes;
-    }
-}
-
 int ga_prepare_kernels(size_t lds)
 {
     if (lds > 64 * 1024) {

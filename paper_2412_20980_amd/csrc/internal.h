@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <atomic>
 #include <map>
 #include <string>
@@ -360,13 +361,26 @@ int launch_mask_build(const int32_t *genes, const int32_t *rows, int32_t P, int3
 
 // ------------------------------------------------------------------- GA -----
 
-// Dynamic LDS of the operator kernels for n nodes and budget k, and the
-// function attributes they need when it exceeds the default 64 KiB.
-// LDS an operator block needs at least for n and k, at most kOpLdsMax; and the
-// LDS it takes, with the quads of its member counts.
-constexpr size_t kOpLdsMax = 160 * 1024;
-size_t ga_op_lds_bytes(int32_t n, int32_t k);
-size_t ga_op_lds_layout(int32_t n, int32_t k, int32_t *log_q);
+// LDS a compute unit has for a block of the operators, and what their kernels take
+// of it besides the dynamic part (the flags of a block and the sums of its waves).
+constexpr size_t kOpLdsMax = 160 * 1024, kOpStaticLds = 48;
+
+// Dynamic LDS of the operator kernels for n nodes and budget k (the membership
+// bits in whole 16 bytes, the row, three bit sets over its slots and the list of
+// slots, whose room takes the member counts of the quads later), and the words
+// of a quad as a power of two.  Quads of more than four words keep the counts
+// within the room that there is on the largest graphs (more than a million
+// nodes).  Sizes that fit no block come out above kOpLdsMax - kOpStaticLds.
+inline size_t ga_op_lds_layout(int32_t n, int32_t k, int32_t *log_q)
+{
+    const size_t W4 = ((size_t)n + 127) / 128, k2 = ((size_t)k + 1) & ~(size_t)1;
+    const size_t fixed = 16 * W4 + 4 * ((size_t)k + 3 * (((size_t)k + 31) / 32));
+    for (*log_q = 2;; ++*log_q) {
+        const size_t quads = (W4 >> (*log_q - 2)) + 1;
+        const size_t bytes = fixed + 2 * std::max(k2, (quads + 1) & ~(size_t)1);
+        if (bytes + kOpStaticLds <= kOpLdsMax || quads <= k2) return bytes;
+    }
+}
 int ga_prepare_kernels(size_t lds);
 
 // Device table entry of one GA instance: where its rows live in the shared

@@ -196,11 +196,13 @@ __device__ __forceinline__ void wave_draw_in_order(const OpLds &l, const Op &a, 
     }
 }
 
+constexpr int kScanWaves = 16;  // waves of a block, at most
+
 // Exclusive prefix sum over the block (blockDim.x <= 1024, a multiple of 64) of
 // counts that add up to less than 65536; also returns the block total.  Every thread must call it.
 __device__ __forceinline__ int32_t block_exclusive_scan(int32_t x, int32_t *total)
 {
-    __shared__ uint16_t s_wave[16];
+    __shared__ uint16_t s_wave[kScanWaves];
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int32_t incl = wave_scan(x);
     if (lane == 63) s_wave[wv] = (uint16_t)incl;
@@ -246,13 +248,13 @@ __device__ __forceinline__ int32_t popc4(const uint4 x)
     return __popc(x.x) + __popc(x.y) + __popc(x.z) + __popc(x.w);
 }
 
-// Flags of one operator block.  (LDS declared here and the scan's take 48 bytes:
-// no more than the 160 KiB of a compute unit leave at the largest n and k.)
+// Flags of one operator block.
 struct OpSums {
     int32_t donor;
     int32_t dups, muts;  // whether any slot is a duplicate, or mutates
     int32_t gone;        // removed non-isolated nodes
 };
+static_assert(sizeof(OpSums) + sizeof(uint16_t) * kScanWaves == kOpStaticLds, "LDS declared in the operator kernels");
 
 // The finished individual leaves as its row in ascending order and, where the
 // fitness kernels consume them, its membership bit set (the removed-node mask)
