@@ -490,7 +490,8 @@ GAPA_API int gapa_graph_set_tuning(gapa_graph *g, const gapa_tuning *t);
  * fastest on the evaluating graph and returns it
  * through best_out (may be NULL).  Work is enqueued on `stream` and waited
  * for.  It overwrites only scratch fitness values; the GA state is
- * untouched. */
+ * untouched.  Where workgroups evaluate the individuals there is nothing to
+ * choose: the shapes stay, and so do recorded generations. */
 GAPA_API int gapa_ga_autotune(gapa_ga *ga, int32_t reps, void *stream, gapa_tuning *best_out);
 GAPA_API int gapa_batch_autotune(gapa_batch *b, int32_t reps, void *stream, gapa_tuning *best_out);
 /* Launch shapes of a batch's fitness pass (its disjoint-union graph), as

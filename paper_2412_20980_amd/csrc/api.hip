@@ -1729,11 +1729,14 @@ int gapa_ga_autotune(gapa_ga *ga, int32_t reps, void *stream, gapa_tuning *best_
         set_error("GA handle is in a failed state");
         return GAPA_E_STATE;
     }
-    DeviceGuard dg(ga->graph->device);
-    hipStream_t s = static_cast<hipStream_t>(stream);
     gapa_graph *g = ga->graph;
+    DeviceGuard dg(g->device);
+    hipStream_t s = static_cast<hipStream_t>(stream);
     hipError_t e = hipDeviceSynchronize();
     if (e != hipSuccess) return fail_handle(&ga->failed, hip_fail(e, "hipDeviceSynchronize"));
+    // no kernel of a GA evaluated by workgroups reads the shapes: nothing to time, and
+    // recordings stay as they are
+    if (ga->by_rows) return best_out ? gapa_graph_get_tuning(g, best_out) : GAPA_OK;
     const bool init = ga->generation == 0;
     const Tuning saved = g->tune;
     Tuning best = saved;
