@@ -140,14 +140,17 @@ GAPA_API int gapa_eval_population(gapa_graph *g, const int32_t *genes, int32_t P
  * GAPA_MAXIMISE_COMPONENTS): genes, fitness and mcn are device pointers and
  * the call enqueues its work on `stream`; without GAPA_TRUST_INPUT it waits
  * for the device's gene check (pass GAPA_TRUST_INPUT under graph capture).
- * The graph's bit-parallel algorithm is used whatever it was created with.
+ * GAPA_UNIONFIND makes no difference to it.
  *
  * Every buffer the evaluation needs comes from a fixed scratch array of
  * GAPA_NOALLOC_SCRATCH_BYTES that the library holds on every GPU it runs on
  * from the library's load to the end of the process; the gene check comes back
- * through page-locked words taken with the first graph made.  Larger graphs than one
- * workgroup's LDS holds (more than 65 535 nodes; or 18 000 if the longest
- * shortest paths are of dozens of hops) are evaluated in chunks of 32 Wd
+ * through page-locked words taken with the first graph made.  Graphs that
+ * workgroups evaluate an individual each need none of it but for nodes that do
+ * not fit LDS.  The others (more than 65 535 nodes; or 18 000 where the paths
+ * from the node of highest degree are of dozens of hops; or with fewer than
+ * 128 individuals and more than 24 000 nodes outside the component of that
+ * node) are evaluated by the bit-parallel pass, in chunks of 32 Wd
  * individuals, Wd the largest power of two <= 32
  * whose buffers fit: about 32 Wd (8.25 n + 8 n_noniso + 4 W + 4 sweep_grid)
  * bytes for n nodes, n_noniso of them with an edge, W = ceil(n / 32) and the
@@ -455,9 +458,9 @@ GAPA_API int gapa_ga_kernel_times(gapa_ga *ga, gapa_kernel_time *out, int32_t ca
 GAPA_API int gapa_batch_set_timing(gapa_batch *b, int32_t enable);
 GAPA_API int gapa_batch_kernel_times(gapa_batch *b, gapa_kernel_time *out, int32_t cap, int32_t *count);
 
-/* Counters of the last chunk the bit-parallel fitness (graphs larger than one
- * workgroup evaluates, and batches) evaluated on a handle
- * (waits for outstanding work): out[0] individuals per chunk, out[1] nodes
+/* Counters of the last chunk the bit-parallel fitness evaluated on a handle
+ * (graphs and batches that workgroups evaluate have none; waits for
+ * outstanding work): out[0] individuals per chunk, out[1] nodes
  * still pending after the ordered sweep, out[2] (individual, node) pairs left
  * to the union-find pass, out[3] follow-up sweeps that still changed
  * something.  All zero before the first evaluation. */

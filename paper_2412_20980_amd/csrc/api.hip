@@ -364,6 +364,11 @@ constexpr int kFarLevel = 4;
 // pass for the closed gate of a launch they have no use for.
 constexpr int kSparseDegree = 5;
 
+// Graphs not for one workgroup an individual (components_fit): of more than
+// kDeepNodes nodes, with paths of more than kDeep hops from the node of highest
+// degree; with more than kLooseNodes nodes outside the component of that node.
+constexpr int32_t kDeep = 48, kDeepNodes = 18000, kLooseNodes = 24000;
+
 // Also returns each source's index among its instance's sources (the t-th
 // source is order[voff[b] + t]; -1 for every other node) and, when band 0
 // holds exactly the sources (no merge took them into band 1), its size in
@@ -616,7 +621,7 @@ int graph_build(int dev, int32_t n, int64_t nnz, const int32_t *row_ptr, const i
             off[r + 1] = (int32_t)(ids.size() / 4);
         }
         g->list_chunks = off[n];
-        {
+        if (g->n_noniso > kDeepNodes) {
             std::vector<int32_t> hop((size_t)n, -1), queue(1, order[0]);
             hop[order[0]] = 0;
             for (size_t q = 0; q < queue.size(); ++q)
@@ -625,7 +630,8 @@ int graph_build(int dev, int32_t n, int64_t nnz, const int32_t *row_ptr, const i
                         hop[col_idx[e2]] = hop[queue[q]] + 1;
                         queue.push_back(col_idx[e2]);
                     }
-            g->depth = hop[queue.back()];
+            g->deep = hop[queue.back()] > kDeep;
+            g->loose = g->n_noniso - (int32_t)queue.size() > kLooseNodes;
         }
         const size_t b_ids = ids.size() * 2, b_off = off.size() * 4, b_rank = rank.size() * 2;
         std::vector<unsigned char> host((size_t)n * 8 + b_ids + b_off + b_rank);
@@ -1057,11 +1063,14 @@ bool params_ok(const gapa_params *p, int32_t n)
            p->reserved == 0;
 }
 
-// Whether a GA on g evaluates its rows directly (eval_rows_components).
-bool rows_fit(const gapa_graph *g)
+// Whether a GA on g with this many children a generation evaluates its rows
+// directly (eval_rows_components).
+bool rows_fit(const gapa_graph *g, int64_t children)
 {
-    return g->algorithm == 0 && components_fit(g);
+    return g->algorithm == 0 && components_fit(g, children);
 }
+
+int32_t children_of(const gapa_params &p) { return p.offspring > 0 ? p.offspring : p.pop; }
 
 // Fills the instance table and sizes every buffer of a GA over `count`
 // instances; instance b has parameters p[b], n[b] nodes, n_noniso[b]
@@ -1408,7 +1417,7 @@ int gapa_ga_create(gapa_graph *g, const gapa_params *p, void *stream, gapa_ga **
         gapa_ga_destroy(ga);
         return code;
     };
-    int rc = ga_allocate(ga, 1, p, &g->n, &g->n_noniso, 0, rows_fit(g));
+    int rc = ga_allocate(ga, 1, p, &g->n, &g->n_noniso, 0, rows_fit(g, children_of(*p)));
     if (rc != GAPA_OK) return fail(rc);
     hipStream_t s = static_cast<hipStream_t>(stream);
     if ((rc = launch_fill_u32(ga->flag.ptr, 0u, 4, s)) != GAPA_OK) return fail(rc);
@@ -1640,7 +1649,7 @@ int gapa_ga_load(gapa_graph *g, const char *path, void *stream, gapa_ga **out)
         gapa_ga_destroy(ga);
         return code;
     };
-    int rc = ga_allocate(ga, 1, &h.params, &g->n, &g->n_noniso, 0, rows_fit(g));
+    int rc = ga_allocate(ga, 1, &h.params, &g->n, &g->n_noniso, 0, rows_fit(g, children_of(h.params)));
     if (rc != GAPA_OK) return fail(rc);
     hipStream_t s = static_cast<hipStream_t>(stream);
     if ((rc = launch_fill_u32(ga->flag.ptr, 0u, 4, s)) != GAPA_OK) return fail(rc);
@@ -1959,7 +1968,7 @@ int gapa_batch_create(int32_t count, gapa_graph *const *graphs, const gapa_param
     std::vector<int32_t> ns(count), nonisos(count), voff(count + 1, 0);
     std::vector<int64_t> eoff(count + 1, 0);
     int32_t slots_needed = 1;
-    bool by_rows = true;  // every instance graph fits a workgroup
+    int64_t children = 0;
     for (int32_t b = 0; b < count; ++b) {
         const gapa_graph *g = graphs[b];
         if (!g || g->failed || g->device != graphs[0]->device) {
@@ -1971,13 +1980,13 @@ int gapa_batch_create(int32_t count, gapa_graph *const *graphs, const gapa_param
             set_error("invalid GA parameters of instance %d", b);
             return GAPA_E_INVALID_ARG;
         }
-        const int32_t L = p.offspring > 0 ? p.offspring : p.pop;
+        const int32_t L = children_of(p);
         if (std::max(p.pop, L) > 1024) {
             set_error("instance %d: max(pop, offspring) = %d exceeds 1024", b, std::max(p.pop, L));
             return GAPA_E_INVALID_ARG;
         }
         slots_needed = std::max(slots_needed, std::max(p.pop, L));
-        by_rows = by_rows && (count == 1 ? rows_fit(g) : components_fit(g));
+        children += L;
         ns[b] = g->n;
         nonisos[b] = g->n_noniso;
         if ((int64_t)voff[b] + g->n > (1 << 30) || eoff[b] + g->nnz >= (1ll << 31)) {
@@ -1987,6 +1996,9 @@ int gapa_batch_create(int32_t count, gapa_graph *const *graphs, const gapa_param
         voff[b + 1] = voff[b] + g->n;
         eoff[b + 1] = eoff[b] + g->nnz;
     }
+    bool by_rows = true;  // every instance graph fits a workgroup
+    for (int32_t b = 0; b < count; ++b)
+        by_rows = by_rows && (count == 1 ? rows_fit(graphs[b], children) : components_fit(graphs[b], children));
     int32_t bseg = 32;
     while (bseg < slots_needed) bseg <<= 1;
     DeviceGuard dg(graphs[0]->device);

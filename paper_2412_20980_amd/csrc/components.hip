@@ -865,12 +865,26 @@ int launch_components(const CompShape &c, const CompView &a, int32_t P, hipStrea
 // On a graph of long paths (a lattice, a road network) the sweeps leave most
 // nodes to the union-find; where LDS does not hold them all, the bit-parallel
 // pass, which spreads the union-finds over the whole chip, is kept (shuffled
-// lattice of 250 x 250: 32 individuals 1.4 ms against 2.3, 256 4.5 against 3.2;
-// random geometric graph, n = 30k: 32 individuals 1.4 ms against 1.8).
-bool components_fit(const gapa_graph *g)
+// lattice of 240 x 240: 8 individuals 1.3 ms against 2.2, 1024 3.4 against 12.8).
+//
+// So it is for few individuals on graphs with more nodes than LDS lists outside
+// the component of the node of highest degree: they go through a slice of global
+// memory of each workgroup, which pays once enough workgroups do that side by
+// side.  n = 60k, bit-parallel pass against workgroups: stars of 50 nodes, 8
+// individuals 209 us against 979, 64 630 against 1053, 128 1173 against 1191, 256
+// 2224 against 1477; paths of 20, 64 776 against 1152, 256 2436 against 1609;
+// random graph of mean degree 0.8, 8 305 against 538, 64 550 against 567, 128 800
+// against 630; a star beside a path, 64 846 against 1177, 128 1448 against 1347;
+// beside a lattice, 32 1.4 ms against 2.2, 1024 13.9 against 12.0.
+//
+// (Trees fall into pieces only without their hubs.  With and without most of
+// those, 8 individuals: BA m = 1 0.98 ms against 0.21, 0.67 against 0.82; random
+// recursive tree 0.84 against 1.41, 0.40 against 0.93.  From 64 individuals on
+// workgroups are 0.9 to 4 times as fast.)
+bool components_fit(const gapa_graph *g, int64_t P)
 {
-    constexpr int32_t kDeep = 48, kDeepNodes = 18000;
-    return g->d_lists && !(g->depth > kDeep && g->n_noniso > kDeepNodes);
+    constexpr int64_t kLooseRows = 128;
+    return g->d_lists && (g->loose ? P >= kLooseRows : !g->deep);
 }
 
 size_t components_spill_bytes(const gapa_graph *g, int32_t P)

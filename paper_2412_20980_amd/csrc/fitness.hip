@@ -323,7 +323,7 @@ int eval_genes(gapa_graph *g, const int32_t *genes, int32_t P, int32_t k, int64_
                int32_t *flag, FitnessWorkspace &ws, KernelTimer *timer, hipStream_t s, Measure measure)
 {
     if (P <= 0) return GAPA_OK;
-    if (g->algorithm == 0 && components_fit(g))
+    if (g->algorithm == 0 && components_fit(g, P))
         return eval_rows_components_ws(g, genes, P, k, fitness, mcn, flag, ws, timer, s, measure);
     int rc;
     if ((rc = ws.masks.reserve((size_t)P * g->words * 4)) != GAPA_OK) return rc;

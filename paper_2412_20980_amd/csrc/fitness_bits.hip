@@ -1292,7 +1292,7 @@ int eval_genes_bits_scratch(gapa_graph *g, const int32_t *genes, int32_t P, int3
                             int32_t *mcn, Measure measure, void *scratch, size_t bytes, int32_t **flag_out,
                             hipStream_t s)
 {
-    if (components_fit(g)) {
+    if (components_fit(g, P)) {
         // one workgroup an individual; the scratch past the flag takes the
         // leftover nodes that do not fit LDS
         int32_t *flag = static_cast<int32_t *>(scratch);

@@ -186,7 +186,8 @@ struct gapa_graph {
     uint32_t *d_noniso = nullptr; // [words] bit v set: v has at least one edge
     int8_t *d_src_idx = nullptr;  // [n] index of a band source among its instance's (order[voff + t]), else -1
     std::vector<int32_t> band_off;  // host: band b is d_band_rec[band_off[b], band_off[b+1])
-    int32_t depth = 0;          // hops from the first of d_order to the farthest node it reaches (with d_lists)
+    bool deep = false;          // with d_lists: many nodes, and long paths from the first of d_order
+    bool loose = false;         // with d_lists: many nodes outside the component of the first of d_order
     int32_t levels = 0;         // breadth-first levels from the highest-degree nodes
     int32_t src_band = 0;       // size of band 0 when it holds exactly the sources, else 0
     int32_t n_noniso = 0;       // nodes with at least one edge
@@ -323,8 +324,9 @@ inline NeighbourLists neighbour_lists(const gapa_graph *g)
 // Fitness of P gene rows (device, [P][k]) by one workgroup each
 // (components.hip), on graphs with neighbour lists: one launch.  A gene outside
 // [0, n) sets flag[0] and is ignored.  spill: components_spill_bytes of
-// device memory (fewer: fewer workgroups side by side).
-bool components_fit(const gapa_graph *g);
+// device memory (fewer: fewer workgroups side by side).  components_fit: whether
+// that is the way for P individuals at a time.
+bool components_fit(const gapa_graph *g, int64_t P);
 size_t components_spill_bytes(const gapa_graph *g, int32_t P);
 int eval_rows_components(gapa_graph *g, const int32_t *genes, int32_t P, int32_t k, int64_t *fitness, int32_t *mcn,
                          int32_t *flag, void *spill, size_t spill_bytes, KernelTimer *timer, hipStream_t s,
