@@ -650,8 +650,18 @@ __global__ void k_pull_worklist(const int4 *__restrict__ worklist, const int32_t
 // sweeps leave nothing there; the sampled count of pending nodes ends the launch
 // at once, where running it for whatever the last sweep changed took 10 us);
 // mean degree 4, 203 individuals 10.2 and 0.36, 1024 24 and 0.59.  Small world
-// of 100k nodes, 256 individuals 7.5 and 0.39.  Lattices and paths stop after
-// rounds that cost what they save, or a little less.
+// of 100k nodes, 256 individuals 7.5 and 0.39.  Trees of 100k nodes: with most of
+// their hubs BA m = 1, 8 individuals 1.42 and 0.65, 128 2.3 and 1.4, random recursive
+// 1.3 and 1.0, 3.2 and 2.1; without, where the roots' parts are small, 0.96 and 1.04,
+// 2.3 and 2.6, 0.53 and 0.66, 2.2 and 2.6.
+//
+// On lattices and their like a round gets the roots' sets a hop or two further.
+// It pays with several nodes a group, which pass bits on in turn (150 x 150,
+// 128 individuals 0.97 and 0.77, 1.83 with as many groups as there is room for;
+// 1024 5.1 and 2.0; random geometric graph, n = 30k, 128 2.2, 1.3 and 3.1), and not at
+// one word a node (32 individuals 1.18 and 1.69): graphs of more than kLongLevels
+// breadth-first levels from the sources (lattices 37 to 87, random graphs of mean
+// degree 1.5 to 8 and small worlds 7 to 30) have no rounds there.
 //
 // Graphs with hubs but few edges (gapa_graph::sparse), once their hubs are removed,
 // end the sweeps in the same way; there the launch goes on where half of the
@@ -668,8 +678,10 @@ __global__ void k_pull_worklist(const int4 *__restrict__ worklist, const int32_t
 // that follow one another in a wave pass bits on within a round, which nodes
 // pulled at the same time do not (mean degree 4: 203 individuals 0.56 ms with all
 // waves, 0.36 with a quarter, 0.41 with an eighth; mean degree 8, 32 individuals
-// 0.25, 0.20 and 0.17).
-constexpr int kRoundBlocks = 512;
+// 0.25, 0.20 and 0.17); fewer where a group would have less than three nodes (n =
+// 100k, 8 individuals: mean degree 4 172 us and 152, BA m = 1 0.70 ms and 0.65).
+constexpr int kRoundBlocks = 512, kRoundNodes = 3;
+constexpr int kLongLevels = 32;
 constexpr int kRounds = 256, kFirstRounds = 3;
 constexpr int kGainSlot = 40;       // of the pass's counters: nodes that gained a bit, over all blocks and rounds
 constexpr int kSampleSlot = 41;     // and: nodes the last sweep's sampled blocks left pending, or let gain a bit
@@ -1191,7 +1203,9 @@ int run_pass(gapa_graph *g, FitnessWorkspace &ws, const PassShape &sh, const Ins
         {
             TimedScope ts(timer, "k_pull_worklist", s);
             uint8_t *flags = settled_flags ? ws.pflag.as<uint8_t>() : nullptr;
-            const bool rounds = settled_flags && (g->far || (g->sparse && Wd <= kSparseWords));
+            // (a graph in pieces has most of its leftover nodes where no root reaches)
+            const bool rounds = settled_flags && !g->loose &&
+                                (g->far ? Wd > 1 || g->levels <= kLongLevels : g->sparse && Wd <= kSparseWords);
             for (int32_t sw = 1; sw <= tu.sweeps; ++sw) {
                 if (rounds && sw == tu.sweeps)
                     hipLaunchKernelGGL(g->far ? k_pull_worklist<kCountPending> : k_pull_worklist<kCountGains>,
@@ -1201,8 +1215,10 @@ int run_pass(gapa_graph *g, FitnessWorkspace &ws, const PassShape &sh, const Ins
                     hipLaunchKernelGGL(k_pull_worklist<0>, dim3(grid), dim3(kBlk), 0, s, worklist, wl_count, Wd,
                                        g->d_colD, dead, reach, changed, sw, flags, nullptr);
             }
+            const int64_t round_blocks = std::clamp<int64_t>((int64_t)g->n_noniso * Wd / (kRoundNodes * kBlk), 1,
+                                                             Wd <= 2 ? kRoundBlocks / 2 : kRoundBlocks);
             if (rounds)
-                hipLaunchKernelGGL(k_pull_rounds, dim3(Wd <= 2 ? kRoundBlocks / 2 : kRoundBlocks), dim3(kBlk), 0, s,
+                hipLaunchKernelGGL(k_pull_rounds, dim3((unsigned)round_blocks), dim3(kBlk), 0, s,
                                    worklist, wl_count, Wd, g->d_colD, dead, reach, ctr + kSampleSlot,
                                    g->far ? 128 * kPendingSample : 2 * kGainsSample, ctr + kGainSlot, flags);
         }
