@@ -842,7 +842,7 @@ CompShape comp_shape(const gapa_graph *g, int32_t P, size_t spill_bytes)
     c.group = comp_group(g->n, P, 256 * per_cu);
     c.bits = c.group <= 4 ? 4 : 8;
     c.cap = comp_cap(c.bits, g->n, g->n_noniso, kCompLds / per_cu, &c.lds);
-    const int32_t groups = (P + c.group - 1) / c.group;
+    const int32_t groups = (P - 1) / c.group + 1;
     c.blocks = std::min(groups, 256 * comp_per_cu(c.threads, c.lds));
     if (c.cap <= g->n_noniso)
         c.blocks = (int32_t)std::min<size_t>((size_t)c.blocks, spill_bytes / (((size_t)g->n_noniso + 1) * 4));
@@ -898,6 +898,13 @@ int eval_rows_components(gapa_graph *g, const int32_t *genes, int32_t P, int32_t
                          Measure measure)
 {
     if (P <= 0) return GAPA_OK;
+    constexpr int32_t kMost = 1 << 30;  // of a launch: its blocks step past the last individual
+    if (P > kMost) {
+        const int rc = eval_rows_components(g, genes, kMost, k, fitness, mcn, flag, spill, spill_bytes, timer, s, measure);
+        if (rc != GAPA_OK) return rc;
+        return eval_rows_components(g, genes ? genes + (int64_t)kMost * k : nullptr, P - kMost, k, fitness + kMost,
+                                    mcn ? mcn + kMost : nullptr, flag, spill, spill_bytes, timer, s, measure);
+    }
     const CompShape c = comp_shape(g, P, spill_bytes);
     if (c.blocks < 1) return GAPA_E_INVALID_ARG;
     const CompView a{genes, k, neighbour_lists(g), g->n_noniso, c.cap,

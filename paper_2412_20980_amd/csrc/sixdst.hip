@@ -207,7 +207,7 @@ __global__ void k_six_final(const unsigned long long *__restrict__ total, int32_
 // Clears the outputs of P individuals and the gene flag.
 __global__ void k_six_clear(int64_t *__restrict__ pc, int32_t *__restrict__ mcn, int32_t P, int32_t *__restrict__ flag)
 {
-    const int32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < P) {
         pc[i] = 0;
         mcn[i] = 0;
@@ -558,7 +558,8 @@ int sixdst_eval_genes(gapa_graph *g, const int32_t *genes, int32_t P, int32_t k,
     // as many blocks as the chip holds at once, each with its run of tasks
     const int32_t per_cu = (int32_t)std::max<size_t>(1, std::min<size_t>(2048 / r.threads, (160 * 1024) / (r.lds + 1024)));
     const int32_t blocks = (int32_t)std::min<int64_t>(tasks, 256 * per_cu);
-    hipLaunchKernelGGL(k_six_clear, dim3((std::max(P, 4) + 255) / 256), dim3(256), 0, s, pc, mcn, P, flag);
+    hipLaunchKernelGGL(k_six_clear, dim3((unsigned)((std::max<int64_t>(P, 4) + 255) / 256)), dim3(256), 0, s, pc, mcn,
+                       P, flag);
     GAPA_HIP(hipGetLastError());
     if (r.NW == 4)
         return r.lds_graph ? launch_reach<4, true>(r, blocks, genes, k, g, hops, nsb, tasks, pc, mcn, flag, s)
