@@ -634,16 +634,19 @@ __device__ __forceinline__ void eval_group(const CompView &a, const CompLds<kBit
                 count_open<kBits, false>(a, l, sm, Parents<false>{a.spill}, count, i, i + 1, settled);
         __syncthreads();
     }
+    // MCN where nothing with an edge survives: 1 if an isolated node does
+    int32_t least = 0;
+    if (wv == 0 && a.mcn)
+        for (uint64_t bare = __ballot(lane < members && sm.root[min(lane, kGroup - 1)] >= n1); bare; bare &= bare - 1) {
+            const int32_t i = (int32_t)__ffsll((unsigned long long)bare) - 1;
+            bool any = false;
+            for (int32_t v = n1; v < n && !any; v += 64)
+                any = __ballot(v + lane < n && !((l.st.removed(min(v + lane, n - 1)) >> i) & 1u)) != 0;
+            if (lane == i) least = any;
+        }
     if (tid < members) {
         const int32_t z = z0 + tid;
-        int32_t least = 0;
-        int64_t s = 0;
-        if (sm.root[tid] < n1) {
-            s = n1 - sm.removed[tid] - sm.outside[tid];
-        } else if (a.mcn) {
-            // nothing with an edge survives: MCN is 1 if an isolated node does
-            for (int32_t v = n1; v < n && !least; ++v) least = !((l.st.removed(v) >> tid) & 1u);
-        }
+        const int64_t s = sm.root[tid] < n1 ? n1 - sm.removed[tid] - sm.outside[tid] : 0;
         a.fitness[z] = (int64_t)sm.sum[tid] + (s > 0 ? (a.forest ? s - 1 : s * (s - 1) / 2) : 0);
         if (a.mcn) a.mcn[z] = max(max((int32_t)s, sm.big[tid]), least);
     }

@@ -42,3 +42,19 @@ def test_matches_union_find_and_oracle(n, size, star, P):
     idx = [0, 1, P - 1]
     Fo, Mo = O.eval_population(g, rows[idx], want_mcn=True)
     assert np.array_equal(F[idx], Fo) and np.array_equal(M[idx], Mo)
+
+
+@pytest.mark.parametrize("n,edges", [(63, 0), (64, 3), (65, 0), (20_001, 150)])
+def test_isolated_survivors_decide_mcn(n, edges):
+    """Every node with an edge removed, and of the isolated ones all but the last,
+    the first, one or none, for as many individuals as a block takes."""
+    from paper_2412_20980_amd import gapa
+    g = inputs.csr_from_edges(n, np.arange(edges), np.arange(edges) + edges)
+    order = np.argsort(-g.degrees(), kind="stable").astype(np.int32)
+    keep = [n - 1, 2 * edges, (n + 2 * edges) // 2, None]
+    rows = np.stack([order if z is None else np.where(order == order[z], order[(z + 1) % n], order) for z in keep])
+    rows = np.tile(rows, (513, 1))
+    F, M = gapa.Graph.from_csr(g).eval(rows, want_mcn=True)
+    Fo, Mo = O.eval_population(g, rows[:4], want_mcn=True)
+    assert not F.any() and not Fo.any() and M[:4].tolist() == Mo.tolist() == [1, 1, 1, 0]
+    assert np.array_equal(M, np.tile(M[:4], 513))
