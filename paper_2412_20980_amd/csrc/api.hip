@@ -802,7 +802,7 @@ int gapa_eval_population(gapa_graph *g, const int32_t *genes, int32_t P, int32_t
     hipStream_t s = static_cast<hipStream_t>(stream);
     FitnessWorkspace &w = g->ws;
     int rc;
-    if ((rc = w.flag.reserve(16)) != GAPA_OK) return rc;
+    if ((rc = w.flag.reserve(32)) != GAPA_OK) return rc;
     const int32_t *d_genes = genes;
     int64_t *d_fit = fitness;
     int32_t *d_mcn = want_mcn ? mcn : nullptr;
@@ -815,17 +815,18 @@ int gapa_eval_population(gapa_graph *g, const int32_t *genes, int32_t P, int32_t
     }
     // (nobody reads the gene flag of trusted device rows: without the launch that
     // clears it, n = 200, P = 32 takes 9.5 us a call instead of 13.0; other calls
-    // find it clear, or clear it, and may leave it set until it is read)
+    // find it clear, or clear it, and may leave it set until it is read.  Trusted rows
+    // have words of their own: they may run, on another stream, while a check does)
     const bool check = !(dev_ptrs && trust);
-    if (check && !g->flag_clear && (rc = launch_fill_u32(w.flag.ptr, 0u, 4, s)) != GAPA_OK)
+    int32_t *flag = w.flag.as<int32_t>() + (check ? 0 : 4);
+    if (check && !g->flag_clear && (rc = launch_fill_u32(flag, 0u, 4, s)) != GAPA_OK)
         return fail_handle(&g->failed, rc);
-    g->flag_clear = false;
-    if ((rc = eval_genes(g, d_genes, P, k, d_fit, d_mcn, w.flag.as<int32_t>(), w, &g->timer, s, measure)) !=
-        GAPA_OK)
+    if (check) g->flag_clear = false;
+    if ((rc = eval_genes(g, d_genes, P, k, d_fit, d_mcn, flag, w, &g->timer, s, measure)) != GAPA_OK)
         return fail_handle(&g->failed, rc);
     if (!check) return GAPA_OK;
     int32_t hflag[4] = {0, 0, 0, 0};
-    if ((rc = copy_back(g, g->mail.open() ? &g->mail : nullptr, w.flag.as<int32_t>(), hflag, d_fit,
+    if ((rc = copy_back(g, g->mail.open() ? &g->mail : nullptr, flag, hflag, d_fit,
                         dev_ptrs ? nullptr : fitness, d_mcn, dev_ptrs || !want_mcn ? nullptr : mcn, P, s)) != GAPA_OK)
         return fail_handle(&g->failed, rc);
     if (hflag[0]) {
@@ -970,7 +971,7 @@ int gapa_sixdst_eval(gapa_graph *g, const int32_t *genes, int32_t P, int32_t k, 
     FitnessWorkspace &w = g->ws;
     const bool sparse = sixdst_sparse(g, hops);
     int rc;
-    if ((rc = w.flag.reserve(16)) != GAPA_OK) return rc;
+    if ((rc = w.flag.reserve(32)) != GAPA_OK) return rc;
     const int32_t *d_genes = genes;
     int64_t *d_pc = pc;
     int32_t *d_mcn = mcn;
@@ -981,9 +982,12 @@ int gapa_sixdst_eval(gapa_graph *g, const int32_t *genes, int32_t P, int32_t k, 
         d_pc = w.fitness.as<int64_t>();
         d_mcn = w.mcn.as<int32_t>();
     }
-    g->flag_clear = false;
+    // (as for eval_population: trusted rows have words of their own)
+    const bool check = !(dev_ptrs && trust);
+    int32_t *flag = w.flag.as<int32_t>() + (check ? 0 : 4);
+    if (check) g->flag_clear = false;
     if (sparse) {
-        if ((rc = sixdst_eval_genes(g, d_genes, P, k, hops, d_pc, d_mcn, w.flag.as<int32_t>(), s)) != GAPA_OK)
+        if ((rc = sixdst_eval_genes(g, d_genes, P, k, hops, d_pc, d_mcn, flag, s)) != GAPA_OK)
             return fail_handle(&g->failed, rc);
     } else {
         // individuals in flight: three dense matrices each, within a 2 GiB workspace
@@ -994,17 +998,17 @@ int gapa_sixdst_eval(gapa_graph *g, const int32_t *genes, int32_t P, int32_t k, 
             (rc = w.six_mats.reserve((size_t)chunk * per)) != GAPA_OK ||
             (rc = w.six_tot.reserve((size_t)chunk * 8)) != GAPA_OK)
             return rc;
-        if ((rc = launch_fill_u32(w.flag.ptr, 0u, 4, s)) != GAPA_OK) return fail_handle(&g->failed, rc);
+        if ((rc = launch_fill_u32(flag, 0u, 4, s)) != GAPA_OK) return fail_handle(&g->failed, rc);
         if ((rc = launch_mask_build(d_genes, nullptr, P, k, g->n, g->words, g->d_noniso, g->n_noniso, w.masks.as<uint32_t>(),
-                                    w.alive.as<int32_t>(), w.flag.as<int32_t>(), s)) != GAPA_OK)
+                                    w.alive.as<int32_t>(), flag, s)) != GAPA_OK)
             return fail_handle(&g->failed, rc);
         if ((rc = sixdst_eval_masks(g, w.masks.as<uint32_t>(), P, hops, chunk, w.six_mats.as<uint8_t>(),
                                     w.six_tot.as<unsigned long long>(), d_pc, d_mcn, s)) != GAPA_OK)
             return fail_handle(&g->failed, rc);
     }
-    if (dev_ptrs && trust) return GAPA_OK;
+    if (!check) return GAPA_OK;
     int32_t hflag[4] = {0, 0, 0, 0};
-    if ((rc = copy_back(g, g->mail.open() ? &g->mail : nullptr, w.flag.as<int32_t>(), hflag, d_pc,
+    if ((rc = copy_back(g, g->mail.open() ? &g->mail : nullptr, flag, hflag, d_pc,
                         dev_ptrs ? nullptr : pc, d_mcn, dev_ptrs ? nullptr : mcn, P, s)) != GAPA_OK)
         return fail_handle(&g->failed, rc);
     if (hflag[0]) {

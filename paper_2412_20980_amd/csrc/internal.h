@@ -142,7 +142,7 @@ struct FitnessWorkspace {
     DevBuf spill;    // int32 union-find parents of eval_rows_components beyond LDS
     DevBuf fitness;  // int64 [P]
     DevBuf mcn;      // int32 [P]
-    DevBuf flag;     // int32 [4]     device error flags
+    DevBuf flag;     // int32 [4]     device error flags, and as many of trusted rows, which nobody reads
     DevBuf six_mats; // int8 [3][chunk][n_pad][n_pad] dense reachability matrices
     DevBuf six_tot;  // uint64 [chunk] their entry sums
     // extra lanes (owned): chunks of a population wider than one pass run
@@ -206,7 +206,7 @@ struct gapa_graph {
     gapa::KernelTimer timer;
     gapa::Mailbox mail;
     gapa::Mailbox check;        // its device's slot for the checked allocation-free call (not owned), or empty
-    bool flag_clear = false;    // ws.flag holds zeros
+    bool flag_clear = false;    // the first four words of ws.flag hold zeros
     bool failed = false;
 };
 
