@@ -1307,7 +1307,7 @@ AdamArgs adam_args(SurrogateState &st)
     return o;
 }
 
-constexpr size_t kEmbedMaskLds = 32 * 1024;  // four blocks' bit sets to a compute unit at least
+constexpr size_t kEmbedMaskLds = 32 * 1024;  // three blocks to a compute unit at least, 9 KiB of ids and sums each besides
 
 // One Adam step on B rows of genes (device, [B][k]) with standardised
 // targets (device): embeddings, MLP forward and backward, gradients, Adam.
@@ -1490,9 +1490,12 @@ int surrogate_attach(gapa_ga *ga, const gapa_surrogate_params *sp, hipStream_t s
     res(st->buf_genes, (size_t)sp->buffer * st->k * 4);
     res(st->buf_y, (size_t)sp->buffer * 8);
     res(st->pool, (size_t)L * 4);
-    if (ga->by_rows) res(st->crows, (size_t)(sp->screen + kJudgeExtra) * st->k * 4);
-    res(st->cmasks, (size_t)(sp->screen + kJudgeExtra) * st->W * 4);
-    res(st->calive, (size_t)(sp->screen + kJudgeExtra) * 4);
+    if (ga->by_rows) {
+        res(st->crows, (size_t)(sp->screen + kJudgeExtra) * st->k * 4);
+    } else {
+        res(st->cmasks, (size_t)(sp->screen + kJudgeExtra) * st->W * 4);
+        res(st->calive, (size_t)(sp->screen + kJudgeExtra) * 4);
+    }
     res(st->dstats, 64);
     res(st->jpart, (size_t)8 * 4 * (kJudgeMax / kJudgeKeys));
     res(st->dloss, 5 * 8);
