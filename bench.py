@@ -46,6 +46,7 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0  # MI355X HBM3E
+LDS_PEAK_GWORDS = 256 * 32 * 2.4  # MI355X LDS: 128 bytes a clock and compute unit, at 2.4 GHz
 METRIC = "population fitness evals/s + HBM GB/s at n=200k; time-to-target PC surrogate vs plain"
 
 
@@ -382,7 +383,7 @@ def run_sixdst(args, torch, gapa, inputs):
         "config": {"workload": f"sixdst_ba{n}_k{k}_p{P}_hops{hops}", "n": n, "k": k, "pop": P, "hops": hops,
                    "parallelism": "single GPU"},
         "roofline": {"bound": "lds", "kernel": "k_six_reach (reachable sets)", "achieved": achieved,
-                     "peak": None, "unit": "G word ORs/s", "frac": None, "traffic": None,
+                     "peak": LDS_PEAK_GWORDS, "unit": "G word ORs/s", "frac": achieved / LDS_PEAK_GWORDS, "traffic": None,
                      "avg_launch_ms": ms, "ops_per_launch": ops},
         "cpu_baseline": cpu,
     }
