@@ -565,11 +565,34 @@ __device__ __forceinline__ void eval_group(const CompView &a, const CompLds<kBit
         if (open <= few || now == 0 || (now < open / 8 && now < found / 2)) break;
         found += now;
     }
-    // Sweeps over the list of the nodes still open (those that fit it; the first
-    // one over all nodes if they do not).  A node whose neighbours are all removed
-    // is a component of its own and counts as removed from here on.  (A star of
-    // 60k nodes without its centre, 8 individuals 73 us, 1024 126; the first sweep,
-    // too, over those listed and a union-find over the others 264 and 951.)
+    // A look at node v's list: reaches it in the individuals one of its neighbours
+    // is reached in.  One whose neighbours are all removed is a component of its
+    // own; it counts as removed from here on, and is returned.  Sets seen's bit 0 if
+    // something was reached, 1 if the node stays open, 2 if its list was cut short.
+    auto look = [&](int32_t v, int32_t &seen) {
+        const uint2 x = l.st.get(v);
+        const uint32_t want = ~(x.x | x.y) & kAll;
+        uint32_t single = 0;
+        if (want) {
+            const int32_t c0 = off[v], c1 = off[v + 1], ce = min(c1, c0 + kLaterChunks);
+            uint32_t acc = 0, gone = kAll;  // reached in some neighbour; removed in every neighbour
+            for (int32_t c = c0; c < ce && (acc & want) != want; ++c) {
+                const uint2 q = ids[c];
+                const uint2 y0 = l.st.get(q.x & 0xFFFFu), y1 = l.st.get(q.x >> 16);
+                const uint2 y2 = l.st.get(q.y & 0xFFFFu), y3 = l.st.get(q.y >> 16);
+                acc |= y0.x | y1.x | y2.x | y3.x;
+                gone &= y0.y & y1.y & y2.y & y3.y;
+            }
+            acc &= want;
+            if (ce == c1) single = want & ~acc & gone;
+            if (acc | single) l.st.put(v, x.x | acc, x.y | single);
+            seen |= (acc ? 1 : 0) | ((acc | single) == want ? 0 : ce < c1 ? 6 : 2);
+        }
+        return single;
+    };
+    // Sweeps over the list of the nodes still open (those that fit it; if they do
+    // not, after one over all nodes.  A star of 60k nodes without its centre, 8
+    // individuals 73 us, 1024 126; without that sweep 264 and 951).
     int32_t count = n1;
     if (n1 <= T) {
         // one round holds every node
@@ -581,35 +604,23 @@ __device__ __forceinline__ void eval_group(const CompView &a, const CompLds<kBit
         __syncthreads();
     } else {
         count = list_open(l, sm, n1, a.cap);
-    }
-    bool settled = true, left = false;  // no open node touches a reached one; some node is open
-    for (int32_t s = 0; count > 0 && s < kSweeps; ++s) {
-        int32_t seen = 0;  // bit 0: something reached, 1: a node stays open, 2: its list was cut short
-        const bool every = s == 0 && count > a.cap, whole = every || count <= a.cap;
-        const int32_t nodes = every ? n1 : min(count, a.cap);
-        for (int32_t t0 = 0; t0 < nodes; t0 += T) {
-            const int32_t t = t0 + tid;
-            uint32_t single = 0;
-            if (t < nodes) {
-                const int32_t v = every ? t : l.list[t];
-                const uint2 x = l.st.get(v);
-                const uint32_t want = ~(x.x | x.y) & kAll;
-                if (want) {
-                    const int32_t c0 = off[v], c1 = off[v + 1], ce = min(c1, c0 + kLaterChunks);
-                    uint32_t acc = 0, gone = kAll;  // reached in some neighbour; removed in every neighbour
-                    for (int32_t c = c0; c < ce && (acc & want) != want; ++c) {
-                        const uint2 q = ids[c];
-                        const uint2 y0 = l.st.get(q.x & 0xFFFFu), y1 = l.st.get(q.x >> 16);
-                        const uint2 y2 = l.st.get(q.y & 0xFFFFu), y3 = l.st.get(q.y >> 16);
-                        acc |= y0.x | y1.x | y2.x | y3.x;
-                        gone &= y0.y & y1.y & y2.y & y3.y;
-                    }
-                    acc &= want;
-                    if (ce == c1) single = want & ~acc & gone;
-                    if (acc | single) l.st.put(v, x.x | acc, x.y | single);
-                    seen |= (acc ? 1 : 0) | ((acc | single) == want ? 0 : ce < c1 ? 6 : 2);
-                }
+        if (count > a.cap) {
+            for (int32_t v0 = 0; v0 < n1; v0 += T) {
+                int32_t seen = 0;
+                const uint32_t single = v0 + tid < n1 ? look(v0 + tid, seen) : 0u;
+                count_singles(sm, single, members);
             }
+            __syncthreads();
+            count = list_open(l, sm, n1, a.cap);
+        }
+    }
+    bool settled = count <= a.cap;  // no open node touches a reached one
+    bool left = count > a.cap;      // some node is open
+    for (int32_t s = 0; count > 0 && s < kSweeps; ++s) {
+        int32_t seen = 0;
+        for (int32_t t0 = 0; t0 < min(count, a.cap); t0 += T) {
+            const int32_t t = t0 + tid;
+            const uint32_t single = t < min(count, a.cap) ? look(l.list[t], seen) : 0u;
             count_singles(sm, single, members);
         }
         const uint64_t m0 = __ballot(seen & 1), m1 = __ballot(seen & 2), m2 = __ballot(seen & 4);
@@ -617,10 +628,11 @@ __device__ __forceinline__ void eval_group(const CompView &a, const CompLds<kBit
         if (tid == 0) sm.seen[(s + 1) % 3] = 0;
         __syncthreads();
         const int32_t all = sm.seen[s % 3];
-        settled = whole && !(all & 5);
-        left = !whole || (all & 2);
-        if (s + 1 == kSweeps || !(all & 1)) break;
-        if (every) count = list_open(l, sm, n1, a.cap);
+        if (s + 1 == kSweeps || !(all & 1)) {
+            settled = settled && !(all & 5);
+            left = left || (all & 2);
+            break;
+        }
     }
     if (left) {  // uniform over the block
         // a list that is mostly closed again, or did not fit, is made anew
