@@ -470,7 +470,8 @@ GAPA_API int gapa_ga_fitness_stats(gapa_ga *ga, int64_t out[4]);
 /* Launch shapes of the bit-parallel fitness pass (without effect where
  * workgroups evaluate the individuals).  They change speed only:
  * results never depend on them.
- *   sweep_grid   blocks of the worklist, pair and union-find kernels, 1..65535
+ *   sweep_grid   blocks of the worklist and pair kernels (twice as many hook
+ *                the leftover pairs), 1..65535
  *   band_scan    neighbours a node reads in the ordered sweep, >= 1
  *   sweeps       follow-up sweeps over the nodes still pending, 0..32
  *   band_blocks  block cap of one band launch, 1..65535

@@ -161,7 +161,7 @@ struct FitnessWorkspace {
 // sweeps or 16 neighbours are up to 5 % faster on these and ten times slower
 // without hubs, or 20 % on BA with m = 2.)
 struct Tuning {
-    int32_t sweep_grid = 2048;   // blocks of the worklist, pair and union-find kernels
+    int32_t sweep_grid = 2048;   // blocks of the worklist and pair kernels (twice as many hook pairs)
     int32_t band_scan = 32;      // neighbours read per node in the ordered sweep
     int32_t sweeps = 3;          // follow-up sweeps over the pending nodes
     int32_t band_blocks = 2048;  // block cap of one band launch
