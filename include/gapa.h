@@ -417,8 +417,8 @@ GAPA_API int gapa_surrogate_tensor(gapa_ga *ga, int32_t which, int32_t kind, flo
  * Instance b evolves exactly as gapa_ga_create(graphs[b], &params[b]) and
  * its generation steps would alone: same draws, same populations, same
  * fitness, generation by generation.  One generation of the batch is one
- * operator launch over all instances' offspring, one bit-parallel fitness
- * pass over all of them and one elitism launch.  Enqueue semantics and
+ * operator launch over all instances' offspring, one fitness pass over all
+ * of them and one elitism launch.  Enqueue semantics and
  * host-pointer waits are those of the single-GA calls (gapa_batch_record as
  * gapa_ga_record); idx selects an instance (0 <= idx < count).
  * ------------------------------------------------------------------------- */

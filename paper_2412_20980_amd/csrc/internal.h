@@ -260,11 +260,12 @@ int eval_masks_bits(gapa_graph *g, const uint32_t *masks, const int32_t *alive, 
 // individuals on graph g (every buffer of one pass plus the chunk's bit sets,
 // each part 256-byte aligned).
 size_t bits_scratch_bytes(const gapa_graph *g, int32_t Wd);
-// Bit-parallel fitness of P gene rows (device, [P][k]) with every buffer
-// carved from `scratch` (`bytes` long): chunks of 32 * Wd rows, Wd the widest
-// power of two <= 32 that fits, one after another on stream s; a gene outside
-// [0, n) sets flag[0] (flag: 4 int32 in the scratch, cleared here unless
-// flag_out is NULL: then nobody reads it).  Nothing is allocated; GAPA_E_INVALID_ARG if not even 32 rows fit.
+// Fitness of P gene rows (device, [P][k]) with every buffer carved from
+// `scratch` (`bytes` long), by workgroups (components_fit) or the bit-parallel
+// pass: chunks of 32 * Wd rows, Wd the widest power of two <= 32 that fits, one
+// after another on stream s; a gene outside [0, n) sets flag[0] (flag: 4 int32
+// in the scratch, cleared here unless flag_out is NULL: then nobody reads it).
+// Nothing is allocated; GAPA_E_INVALID_ARG if not even 32 rows fit.
 int eval_genes_bits_scratch(gapa_graph *g, const int32_t *genes, int32_t P, int32_t k, int64_t *fitness,
                             int32_t *mcn, Measure measure, void *scratch, size_t bytes, int32_t **flag_out,
                             hipStream_t s);
